@@ -131,7 +131,7 @@ def _params(case):
 def _samples(case):
     """Samples a pass evaluates: about three quarters of the budget where the scene fills the
     frame, fewer where options drop them (measured averages of the listed cases)."""
-    part = {"prop": 0.29, "ess": 0.18, "hs": 0.5}.get(case["option"], 0.44 if case["scene"] == "large" else 0.75)
+    part = {"prop": 0.22, "ess": 0.19, "hs": 0.29}.get(case["option"], 0.44 if case["scene"] == "large" else 0.75)
     return part * _n_rays(case) * case["s_max"]
 
 
