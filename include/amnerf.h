@@ -381,9 +381,8 @@ typedef struct {
   int64_t n_nonfinite;    /* rays whose rgb, depth or opacity is not finite */
   int64_t n_fallback;     /* rays rendered with every plain slot under a proposal */
   int64_t n_plain_samples;/* samples the plain sampler would have taken */
-  int64_t n_unreached;    /* interval entries the traversal's emission pass did not reach and
-                             filled with zero-length entries (0 unless its two passes disagree;
-                             such entries add samples of zero weight to leaf 0's bucket) */
+  int64_t n_unreached;    /* interval entries the traversal left unwritten: always 0 (it walks
+                             every ray once, writing what it counts) */
   int64_t n_composited;   /* samples composited before early termination (the stop sample
                              included); n_samples - n_composited were evaluated by the MLPs
                              but lie past the termination point */

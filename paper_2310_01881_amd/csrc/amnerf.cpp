@@ -935,7 +935,9 @@ struct Carve {
 };
 
 struct Work {
-  uint32_t *cnt_iv, *cnt_smp, *iv_off, *smp_off, *scan_tmp;
+  uint64_t* chain;        // state words of the pass's chained scans
+  uint64_t chain_words;
+  uint32_t *iv_off, *smp_off, *scan_tmp;
   float *iv_t0, *iv_dt;
   uint32_t *iv_key, *iv_ray, *iv_base;
   uint32_t *mat, *mat_scan, *sidx, *sn, *ssb, *bucket_off, *tile_off;
@@ -952,8 +954,8 @@ struct Work {
 size_t carve(char* base, uint64_t nr, uint64_t niv, uint64_t ns, const SortPlan& sp, Work& w, bool rounds) {
   Carve c{base};
   uint64_t scan_n = std::max<uint64_t>({nr, niv, (uint64_t)sp.n_leaves * sp.nseg_max});
-  w.cnt_iv = c.take<uint32_t>(nr);
-  w.cnt_smp = c.take<uint32_t>(nr);
+  w.chain_words = trav_state_words(nr);
+  w.chain = c.take<uint64_t>(w.chain_words);
   w.iv_off = c.take<uint32_t>(nr + 1);
   w.smp_off = c.take<uint32_t>(nr + 1);
   w.scan_tmp = c.take<uint32_t>(scan_tmp_words(scan_n));
@@ -1120,10 +1122,9 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
     if (rc) return rc;
     carve((char*)ctx->lanes[i - 1].arena, chunk, niv_max, ns_max, sp, ws[i], rounds);
   }
-  HIP_TRY(launch_counts_reset(ctx->counts, st));
+  if (R == 0) HIP_TRY(launch_pass_begin(ctx->counts, true, nullptr, 0, st));
   for (int i = 1; i < n_lanes; ++i) {
     auto& ln = ctx->lanes[i - 1];
-    HIP_TRY(launch_counts_reset(ln.counts, st));
     HIP_TRY(hipEventRecord(ln.fork, st));
     HIP_TRY(hipStreamWaitEvent(ln.stream, ln.fork, 0));
   }
@@ -1144,8 +1145,8 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
     int li;
     EvSet* ev;
   };
-  // phase 1: traversal, and the plain interval count on its way to the host (lane li's slot)
-  auto phase1 = [&](int64_t r0, uint32_t nr, int li, Pending* pd) -> int {
+  // phase 1 (first: of the lane's first chunk, which resets its counters): traversal, and the plain interval count on its way to the host (lane li's slot)
+  auto phase1 = [&](int64_t r0, uint32_t nr, int li, bool first, Pending* pd) -> int {
     const hipStream_t cs = li ? ctx->lanes[li - 1].stream : st;
     ChunkCounts* const cc = li ? ctx->lanes[li - 1].counts : ctx->counts;
     Work& w = ws[li];
@@ -1156,10 +1157,11 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
     }
     auto mark = [&](int k) -> hipError_t { return ev ? hipEventRecord(ev->ev[k], cs) : hipSuccess; };
     HIP_TRY(mark(0));
-    HIP_TRY(launch_trav_count(tree->dev_nodes, ahs_tab, p->hcheck_footprint, (uint32_t)n_nodes, tree->depth, rays->o_dev, rays->d_dev, R, r0, nr, p->s_max, w.cnt_iv, w.cnt_smp, cs));
-    HIP_TRY(launch_scan_u32_pair(w.cnt_iv, w.iv_off, w.cnt_smp, w.smp_off, nr, w.scan_tmp, cs));
-    HIP_TRY(launch_trav_emit(tree->dev_nodes, ahs_tab, p->hcheck_footprint, (uint32_t)n_nodes, tree->depth, rays->o_dev, rays->d_dev, R, r0, nr, w.cnt_iv, w.cnt_smp, w.iv_off,
-                             w.smp_off, w.iv_t0, w.iv_dt, w.iv_key, w.iv_ray, w.iv_base, cc, cs));
+    HIP_TRY(launch_pass_begin(cc, first, w.chain, w.chain_words, cs));
+    // the MLP outputs' buffer (16 bytes per possible sample) is free until the MLPs run: the
+    // traversal keeps its scratch rows (12 bytes per possible interval) there
+    HIP_TRY(launch_trav(tree->dev_nodes, ahs_tab, p->hcheck_footprint, (uint32_t)n_nodes, tree->depth, rays->o_dev, rays->d_dev, R, r0, nr, p->s_max, (uint32_t)iv_per_ray, w.smp_out, w.chain, w.iv_off,
+                        w.smp_off, w.iv_t0, w.iv_dt, w.iv_key, w.iv_ray, w.iv_base, cs));
     HIP_TRY(mark(1));
     if (wait_count)
       HIP_TRY(hipMemcpyAsync(&ctx->counts_host[li].n_iv, w.iv_off + nr, sizeof(uint32_t), hipMemcpyDeviceToHost, cs));
@@ -1271,7 +1273,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
   for (int64_t r0 = 0; r0 < R; r0 += (int64_t)chunk, ++n_chunks) {
     const uint32_t nr = (uint32_t)std::min<int64_t>((int64_t)chunk, R - r0);
     Pending cur;
-    rc = phase1(r0, nr, (int)(n_chunks % n_lanes), &cur);
+    rc = phase1(r0, nr, (int)(n_chunks % n_lanes), n_chunks < n_lanes, &cur);
     if (rc) return rc;
     if (n_lanes == 1) {   // one workspace: the next chunk's traversal must wait for this chunk
       rc = phase2(cur);

@@ -254,10 +254,14 @@ __global__ void k_counts_merge(ChunkCounts* a, const ChunkCounts* b) {
   a->evaluated += b->evaluated;
 }
 
-__global__ void k_counts_reset(ChunkCounts* counts) {
-  if (threadIdx.x != 0) return;
-  ChunkCounts z = {};
-  *counts = z;
+__global__ __launch_bounds__(kThreads) void k_pass_begin(ChunkCounts* counts, int reset, uint64_t* __restrict__ state,
+                                                         uint64_t words) {
+  if (reset && blockIdx.x == 0 && threadIdx.x == 0) {
+    ChunkCounts z = {};
+    *counts = z;
+  }
+  for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < words; i += (uint64_t)gridDim.x * kThreads)
+    state[i] = 0ull;
 }
 
 }  // namespace
@@ -306,8 +310,9 @@ hipError_t launch_counts_merge(ChunkCounts* a, const ChunkCounts* b, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t launch_counts_reset(ChunkCounts* counts, hipStream_t st) {
-  hipLaunchKernelGGL(k_counts_reset, dim3(1), dim3(64), 0, st, counts);
+hipError_t launch_pass_begin(ChunkCounts* counts, bool reset, uint64_t* state, uint64_t words, hipStream_t st) {
+  const uint64_t blocks = std::min<uint64_t>(256u, words / (4 * kThreads) + 1);
+  hipLaunchKernelGGL(k_pass_begin, dim3((uint32_t)blocks), dim3(kThreads), 0, st, counts, reset ? 1 : 0, state, words);
   return hipGetLastError();
 }
 

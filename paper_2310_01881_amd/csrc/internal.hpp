@@ -34,8 +34,7 @@ struct ChunkCounts {
   uint64_t nonfinite;   // rays with a non-finite output (accumulated over chunks)
   uint64_t fallback;    // rays that fell back to plain sampling under a proposal
   uint64_t plain_smp;   // samples of the plain sampler (before any proposal)
-  uint64_t unreached;   // interval entries the emission walk did not reach (filled with
-                        // zero-length slot-0 entries; 0 unless the two traversal passes disagree)
+  uint64_t unreached;   // always 0 (the traversal walks once, so no entry can be left unwritten)
   uint64_t composited;  // samples composited before early termination (accumulated)
   uint64_t evaluated;   // samples the leaf MLPs evaluated (accumulated)
 };
@@ -52,18 +51,17 @@ constexpr int kSegTiles = 16;           // tiles per backward work segment (one 
 constexpr int kScanItems = 2048;        // elements per scan block (256 threads x 8)
 
 // ---- traversal (Algorithm 1: Traverse) -------------------------------------------------
-// Pass 1: per ray, the number of leaf intervals that receive samples (min(m, s_max)) and
-// the number of samples.  Pass 2: the intervals themselves, ray-major, at iv_off.
-// `ahs` NULL: leaf intervals; else hierarchical sampling with the given footprint.
-hipError_t launch_trav_count(const DevNode* nodes, const DevNodeAhs* ahs, float footprint, uint32_t n_nodes, int depth,
-                             const float* o, const float* d, int64_t ray_stride, int64_t r0, uint32_t nr, int s_max,
-                             uint32_t* cnt_iv, uint32_t* cnt_smp, hipStream_t st);
-hipError_t launch_trav_emit(const DevNode* nodes, const DevNodeAhs* ahs, float footprint, uint32_t n_nodes, int depth,
-                            const float* o, const float* d, int64_t ray_stride, int64_t r0, uint32_t nr,
-                            const uint32_t* cnt_iv, const uint32_t* cnt_smp,
-                            const uint32_t* iv_off, const uint32_t* smp_off, float* iv_t0,
-                            float* iv_dt, uint32_t* iv_key, uint32_t* iv_ray, uint32_t* iv_base,
-                            ChunkCounts* counts, hipStream_t st);
+// The intervals of every ray (min(m, s_max) of them), ray-major, and the per-ray interval and
+// sample offsets with their totals at [nr].  `ahs` NULL: leaf intervals; else hierarchical
+// sampling with the given footprint.  iv_cap: at least the intervals a ray can have (up to
+// s_max).  scratch: 3 * nr * iv_cap floats, 8-byte aligned, free during the launch.  state:
+// trav_state_words(nr) zeroed words (launch_pass_begin).
+uint64_t trav_state_words(uint64_t nr);
+hipError_t launch_trav(const DevNode* nodes, const DevNodeAhs* ahs, float footprint, uint32_t n_nodes, int depth,
+                       const float* o, const float* d, int64_t ray_stride, int64_t r0, uint32_t nr, int s_max,
+                       uint32_t iv_cap, float* scratch, uint64_t* state, uint32_t* iv_off, uint32_t* smp_off,
+                       float* iv_t0, float* iv_dt, uint32_t* iv_key, uint32_t* iv_ray, uint32_t* iv_base,
+                       hipStream_t st);
 
 // Intervals of one chunk, ray-major: per ray the interval range [iv_off[r], iv_off[r+1]) and
 // sample range [smp_off[r], smp_off[r+1]); per interval t0, length dt, key (slot | n << 16),
@@ -255,7 +253,8 @@ hipError_t launch_prop_train(const void* packed, const IvSet& iv, const float* o
 
 // ---- small helpers ----------------------------------------------------------------------
 hipError_t launch_counts_merge(ChunkCounts* a, const ChunkCounts* b, hipStream_t st);
-hipError_t launch_counts_reset(ChunkCounts* counts, hipStream_t st);
+// Start of a pass: zeroes the chained scans' state words, and the counters when `reset`.
+hipError_t launch_pass_begin(ChunkCounts* counts, bool reset, uint64_t* state, uint64_t words, hipStream_t st);
 hipError_t launch_chunk_begin(ChunkCounts* counts, const uint32_t* iv_total, uint32_t seg, uint32_t n_leaves,
                               hipStream_t st);
 hipError_t launch_chunk_finish(ChunkCounts* counts, const uint32_t* smp_off_total,

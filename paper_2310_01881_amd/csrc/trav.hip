@@ -20,6 +20,7 @@
 #include <atomic>
 
 #include "internal.hpp"
+#include "chain.hpp"
 #include "devcommon.hpp"
 
 namespace amn {
@@ -67,9 +68,12 @@ __device__ __forceinline__ DF plane_t_div(float s, float o, float d) {
 // (bitwise: three compares and two mask operations, no branch)
 __device__ __forceinline__ bool df_lt(DF a, DF b) { return (a.hi < b.hi) | ((a.hi == b.hi) & (a.lo < b.lo)); }
 
-constexpr int kBlock = 256;
+// Blocks of kBlock rays, or of kBlockSmall (one wave) for launches that would otherwise leave
+// compute units without a block.
+constexpr int kBlock = 256, kBlockSmall = 64;
+constexpr uint32_t kSmallRays = 65536;   // 256 compute units x 256 rays
 // LDS per block: the node table (when staged), then the traversal stack of `stack_n` =
-// tree depth + 1 8-byte entries per thread, strided by kBlock (a wave's entries of one level
+// tree depth + 1 8-byte entries per thread, strided by the block size (a wave's entries of one level
 // are consecutive): the node index (16 bits) packed with the exit parameter's low part
 // rounded to bfloat16 (the pair then still carries about 2^-32 relative precision, far below
 // the 1e-6 perturbation under which node ids are compared), and the exit parameter's high
@@ -115,18 +119,18 @@ struct AhsMem {
   __device__ uint32_t slot(int i) const { return p[i].slot; }
 };
 
-// Traverses one ray.  EMIT = false: returns the interval count, stopping once it exceeds
-// cap.  EMIT = true: writes the first `cap` intervals through the output pointers.  AHS:
-// stop the descent by HCheck, and key intervals by the node's preorder slot.
+// Traverses one ray: hands its first `cap` intervals to put(m, t0, dt, slot) and returns the
+// interval count, stopping once it exceeds cap.  AHS: stop the descent by HCheck, and key
+// intervals by the node's preorder slot.  B: the block size (the stack's stride).
 __device__ __forceinline__ uint32_t push_word(int node, float lo) {
   return (uint32_t)node | ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)lo) << 16);
 }
 __device__ __forceinline__ float word_lo(uint32_t w) { return (float)__builtin_bit_cast(__bf16, (uint16_t)(w >> 16)); }
 
 // TINY: crossings by division (see plane_t_div).
-template <bool EMIT, bool AHS, bool TINY, typename Ahs, typename Put>
-__device__ int traverse_one(const DevNode* nodes, const Ahs ahs, const V3 o, const V3 dir, int cap, uint32_t n_per,
-                        uint2* st, Put put) {
+template <int B, bool AHS, bool TINY, typename Ahs, typename Put>
+__device__ int traverse_one(const DevNode* nodes, const Ahs ahs, const V3 o, const V3 dir, int cap, uint2* st,
+                            Put put) {
   // root box [0,1]^3
   const V3 inv = {1.f / dir.x, 1.f / dir.y, 1.f / dir.z};
   auto cross = [&](float s, float oa, float da, float ia) {
@@ -175,7 +179,7 @@ __device__ int traverse_one(const DevNode* nodes, const Ahs ahs, const V3 o, con
       // the entry above the top is written in any case and kept only when both children are
       // crossed (at depth k at most k entries are held, so it exists)
       const bool both = !only_before & !only_after;
-      st[sp * kBlock] = make_uint2(push_word(after, t1.lo), __float_as_uint(t1.hi));
+      st[sp * B] = make_uint2(push_word(after, t1.lo), __float_as_uint(t1.hi));
       sp += both ? 1 : 0;
       t1.hi = both ? ts.hi : t1.hi;
       t1.lo = both ? ts.lo : t1.lo;
@@ -184,21 +188,17 @@ __device__ int traverse_one(const DevNode* nodes, const Ahs ahs, const V3 o, con
       nd.plane = upper ? c1.plane : c0.plane;
       nd.info = upper ? c1.info : c0.info;
     }
-    const int info = nd.info;
     // interval [t0, t1] of a leaf (or, with AHS, of a node HCheck stopped at), t1 > t0 by
     // construction
-    if (EMIT) {
-      if (m < cap) {
-        float dh = t1.hi - t0.hi;
-        float dt = dh + (t1.lo - t0.lo);
-        const uint32_t slot = AHS ? ahs.slot(node) : (uint32_t)(-(info + 1));
-        put(m, t0.hi, dt, slot | (n_per << 16));
-      }
+    if (m < cap) {
+      float dh = t1.hi - t0.hi;
+      float dt = dh + (t1.lo - t0.lo);
+      put(m, t0.hi, dt, AHS ? ahs.slot(node) : (uint32_t)(-(nd.info + 1)));
     }
     ++m;
-    if (m >= cap + (EMIT ? 0 : 1) || sp == 0) break;
+    if (m > cap || sp == 0) break;
     --sp;
-    const uint2 w = st[sp * kBlock];
+    const uint2 w = st[sp * B];
     node = (int)(w.x & 0xFFFFu);
     t0 = t1;
     t1 = {__uint_as_float(w.y), word_lo(w.x)};
@@ -206,14 +206,14 @@ __device__ int traverse_one(const DevNode* nodes, const Ahs ahs, const V3 o, con
   return m;
 }
 
-template <bool EMIT, bool AHS, typename Ahs, typename Put>
+template <int B, bool AHS, typename Ahs, typename Put>
 __device__ __forceinline__ int traverse(const DevNode* nodes, const Ahs ahs, const V3 o, const V3 dir, int cap,
-                                        uint32_t n_per, uint2* st, Put put) {
+                                        uint2* st, Put put) {
   // some ray of the wave has a nonzero component whose reciprocal overflows
   auto tiny = [](float v) { return v != 0.f && fabsf(v) < 1.1754944e-38f; };
   if (__ballot(tiny(dir.x) || tiny(dir.y) || tiny(dir.z)) != 0)
-    return traverse_one<EMIT, AHS, true>(nodes, ahs, o, dir, cap, n_per, st, put);
-  return traverse_one<EMIT, AHS, false>(nodes, ahs, o, dir, cap, n_per, st, put);
+    return traverse_one<B, AHS, true>(nodes, ahs, o, dir, cap, st, put);
+  return traverse_one<B, AHS, false>(nodes, ahs, o, dir, cap, st, put);
 }
 
 // The block's copy of the node table (LDS = true) or the table in memory, the per-node
@@ -224,7 +224,7 @@ struct TravLds {
   uint2* st;
 };
 
-template <bool LDS, bool AHS>
+template <int B, bool LDS, bool AHS>
 __device__ __forceinline__ TravLds stage(const DevNode* __restrict__ nodes, const DevNodeAhs* __restrict__ ahs,
                                          float footprint, uint32_t n_nodes, int stack_n, uint8_t* dyn) {
   TravLds t;
@@ -232,12 +232,12 @@ __device__ __forceinline__ TravLds stage(const DevNode* __restrict__ nodes, cons
   t.ahs = nullptr;
   if (LDS) {
     DevNode* s = reinterpret_cast<DevNode*>(p);
-    for (uint32_t i = threadIdx.x; i < n_nodes; i += kBlock) s[i] = nodes[i];
+    for (uint32_t i = threadIdx.x; i < n_nodes; i += B) s[i] = nodes[i];
     p += sizeof(DevNode) * n_nodes;
     t.nodes = s;
     if (AHS) {
       float2* a = reinterpret_cast<float2*>(p);
-      for (uint32_t i = threadIdx.x; i < n_nodes; i += kBlock) {
+      for (uint32_t i = threadIdx.x; i < n_nodes; i += B) {
         const DevNodeAhs v = ahs[i];
         a[i] = make_float2(__fdiv_rn(v.size, footprint), __builtin_bit_cast(float, v.slot));
       }
@@ -248,13 +248,12 @@ __device__ __forceinline__ TravLds stage(const DevNode* __restrict__ nodes, cons
     t.nodes = nodes;
   }
   t.st = reinterpret_cast<uint2*>(p) + threadIdx.x;
-  if (LDS) __syncthreads();
-  return t;
+  return t;   // (the caller synchronises the block)
 }
 
-__host__ __device__ constexpr uint32_t trav_lds_bytes(bool lds, bool ahs, uint32_t n_nodes, int stack_n) {
+__host__ __device__ constexpr uint32_t trav_lds_bytes(int block, bool lds, bool ahs, uint32_t n_nodes, int stack_n) {
   return (lds ? (uint32_t)(sizeof(DevNode) + (ahs ? sizeof(float2) : 0u)) * n_nodes : 0u) +
-         8u * (uint32_t)stack_n * kBlock;
+         8u * (uint32_t)stack_n * (uint32_t)block;
 }
 
 // Runs `f` with the hierarchical-sampling view that matches the staging.
@@ -265,212 +264,191 @@ __device__ __forceinline__ int with_ahs(const TravLds& tl, const DevNodeAhs* ahs
   else return f(AhsMem{ahs, footprint});
 }
 
-// Counts.  Samples per interval follow the ray's leaf-interval count m (s_max / m, or 1
-// when m > s_max); with AHS the intervals are those of the HCheck traversal, so a node that
-// stops the descent gets one interval's share however many leaves it covers.
-template <bool LDS, bool AHS>
-__global__ __launch_bounds__(kBlock) void k_trav_count(const DevNode* __restrict__ nodes,
-                                                       const DevNodeAhs* __restrict__ ahs, float footprint,
-                                                       uint32_t n_nodes,
-                                                       int stack_n, const float* __restrict__ o,
-                                                       const float* __restrict__ d,
-                                                       int64_t stride, int64_t r0, uint32_t nr,
-                                                       int s_max, uint32_t* __restrict__ cnt_iv,
-                                                       uint32_t* __restrict__ cnt_smp) {
+// Traversal in one pass.  Samples per interval follow the ray's leaf-interval count m (s_max /
+// m, or 1 when m > s_max); with AHS the intervals are those of the HCheck traversal, so a node
+// that stops the descent gets one interval's share however many leaves it covers (the leaves
+// are counted by a walk of their own first).
+//
+// Where a ray's intervals go depends on the counts of every ray before it.  Each wave puts its
+// intervals, as it finds them, into scratch rows of its own (row m = the m-th interval of its
+// rays, so a row is one coalesced write); the block's totals then go through the chained scan,
+// and the wave writes its part of the ray-major arrays with consecutive lanes on consecutive
+// entries, reading its rows back while they are still in cache.  Walking twice (a counting
+// pass, three scan launches and an emitting pass) cost the whole chain a second time; whole
+// renders: 4096-ray tile 153 -> 125 us, 800x800 planned frame 1.82 -> 1.72 ms, 1920x1080 frame
+// of 4096 leaves 9.02 -> 8.01 ms.
+template <int B, bool LDS, bool AHS>
+__global__ __launch_bounds__(B) void k_trav(
+    const DevNode* __restrict__ nodes, const DevNodeAhs* __restrict__ ahs, float footprint, uint32_t n_nodes,
+    int stack_n, const float* __restrict__ o, const float* __restrict__ d, int64_t stride, int64_t r0, uint32_t nr,
+    int s_max, uint32_t iv_cap, float2* scratch_t, uint32_t* scratch_slot, uint64_t* __restrict__ state,
+    uint32_t* __restrict__ iv_off, uint32_t* __restrict__ smp_off, float* __restrict__ iv_t0,
+    float* __restrict__ iv_dt, uint32_t* __restrict__ iv_key, uint32_t* __restrict__ iv_ray,
+    uint32_t* __restrict__ iv_base) {
   extern __shared__ __align__(16) uint8_t dyn[];
-  const TravLds tl = stage<LDS, AHS>(nodes, ahs, footprint, n_nodes, stack_n, dyn);
-  uint32_t r = blockIdx.x * kBlock + threadIdx.x;
-  bool live = r < nr;
-  V3 oo = {0.f, 0.f, 0.f}, dd = {0.f, 0.f, 1.f};
-  if (live) {
-    const int64_t ri = r0 + r;
-    oo = {o[ri], o[stride + ri], o[2 * stride + ri]};
-    dd = {d[ri], d[stride + ri], d[2 * stride + ri]};
-  }
+  constexpr int W = B / 64;
+  __shared__ uint32_t s_blk;
+  __shared__ uint64_t s_sum[W], s_before;
+  __shared__ int s_mark[W][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (threadIdx.x == 0) s_blk = chain_ticket(state);
+  const TravLds tl = stage<B, LDS, AHS>(nodes, ahs, footprint, n_nodes, stack_n, dyn);
+  __syncthreads();
+  const uint32_t blk = __builtin_amdgcn_readfirstlane(s_blk);
+  const uint32_t rw = blk * B + 64u * (uint32_t)wave;   // the wave's first ray
+  const uint32_t r = rw + (uint32_t)lane;
+  const uint32_t width = rw < nr ? (nr - rw < 64u ? nr - rw : 64u) : 0u;   // its rays = its rows' length
+  float2* const row_t = scratch_t + (uint64_t)rw * iv_cap;
+  uint32_t* const row_slot = scratch_slot + (uint64_t)rw * iv_cap;
   int m = 0, mi = 0;
-  // skip the descent for a wave whose rays are all out of range
-  if (__ballot(live) != 0 && live) {
-    auto none = [](int, float, float, uint32_t) {};
-    m = traverse<false, false>(tl.nodes, AhsNone{}, oo, dd, s_max, 0, tl.st, none);
-    mi = m;
-    if (AHS && m > 0)
-      mi = with_ahs<LDS, AHS>(tl, ahs, footprint, [&](auto av) {
-        return traverse<false, AHS>(tl.nodes, av, oo, dd, s_max, 0, tl.st, none);
-      });
-  }
-  if (live) {
-    uint32_t meff = mi <= s_max ? (uint32_t)mi : (uint32_t)s_max;
-    uint32_t nper = m == 0 ? 0u : (m <= s_max ? (uint32_t)(s_max / m) : 1u);
-    cnt_iv[r] = meff;
-    cnt_smp[r] = meff * nper;
-  }
-}
-
-// Emission: the block's rays are consecutive, so its intervals fill one contiguous range of
-// the output.  Each lane puts its intervals into an LDS copy of the first `stage_n` entries
-// of that range (entries past it go straight to memory), and the block then writes the
-// staged entries out with consecutive threads on consecutive entries, so every cache line
-// is written whole at once instead of piecewise by lanes that finish at different times.
-template <bool LDS, bool AHS>
-__global__ __launch_bounds__(kBlock) void k_trav_emit(const DevNode* __restrict__ nodes,
-                                                      const DevNodeAhs* __restrict__ ahs, float footprint,
-                                                      uint32_t n_nodes,
-                                                      int stack_n, uint32_t stage_n, const float* __restrict__ o,
-                                                      const float* __restrict__ d, int64_t stride,
-                                                      int64_t r0, uint32_t nr,
-                                                      const uint32_t* __restrict__ cnt_iv,
-                                                      const uint32_t* __restrict__ cnt_smp,
-                                                      const uint32_t* __restrict__ iv_off,
-                                                      const uint32_t* __restrict__ smp_off,
-                                                      float* __restrict__ iv_t0,
-                                                      float* __restrict__ iv_dt,
-                                                      uint32_t* __restrict__ iv_key,
-                                                      uint32_t* __restrict__ iv_ray,
-                                                      uint32_t* __restrict__ iv_base,
-                                                      ChunkCounts* __restrict__ counts) {
-  extern __shared__ __align__(16) uint8_t dyn[];
-  const TravLds tl = stage<LDS, AHS>(nodes, ahs, footprint, n_nodes, stack_n, dyn);
-  uint8_t* sp = dyn + trav_lds_bytes(LDS, AHS, n_nodes, stack_n);
-  float* s_t0 = reinterpret_cast<float*>(sp);
-  float* s_dt = s_t0 + stage_n;
-  uint32_t* s_key = reinterpret_cast<uint32_t*>(s_dt + stage_n);
-  uint32_t* s_ray = s_key + stage_n;
-  uint32_t* s_base = s_ray + stage_n;
-  const uint32_t rb = blockIdx.x * kBlock;                      // first ray of the block
-  const uint32_t re = rb + kBlock < nr ? rb + kBlock : nr;      // one past its last ray
-  const uint32_t b0 = iv_off[rb], b1 = iv_off[re];              // the block's output range
-  const uint32_t r = rb + threadIdx.x;
-  const uint32_t meff = r < nr ? cnt_iv[r] : 0u;
-  if (__ballot(meff != 0) != 0 && meff != 0) {
+  if ((uint32_t)lane < width) {
     const int64_t ri = r0 + r;
     const V3 oo = {o[ri], o[stride + ri], o[2 * stride + ri]}, dd = {d[ri], d[stride + ri], d[2 * stride + ri]};
-    const uint32_t nper = cnt_smp[r] / meff;
-    const uint32_t pos0 = iv_off[r] - b0;
-    const uint32_t base = smp_off[r];
-    auto put = [&](int m, float t0, float dt, uint32_t key) {
-      const uint32_t q = pos0 + (uint32_t)m;
-      const uint32_t smp = base + (uint32_t)m * nper;
-      if (q < stage_n) {
-        s_t0[q] = t0; s_dt[q] = dt; s_key[q] = key; s_ray[q] = r; s_base[q] = smp;
-      } else {
-        iv_t0[b0 + q] = t0; iv_dt[b0 + q] = dt; iv_key[b0 + q] = key; iv_ray[b0 + q] = r;
-        iv_base[b0 + q] = smp;
-      }
+    auto put = [&](int k, float t0, float dt, uint32_t slot) {
+      row_t[(uint32_t)k * width + lane] = make_float2(t0, dt);
+      row_slot[(uint32_t)k * width + lane] = slot;
     };
-    const int got = with_ahs<LDS, AHS>(tl, ahs, footprint, [&](auto av) {
-      return traverse<true, AHS>(tl.nodes, av, oo, dd, (int)meff, nper, tl.st, put);
-    });
-    // The count pass walks the same way, so `got` equals meff.  Should a walk ever end
-    // early, the rest of the ray's range still gets well-formed entries (zero length,
-    // slot 0), so later stages never read an unwritten key, and the filled entries are
-    // counted (reported by the render statistics; every test requires 0).
-    if ((uint32_t)got < meff) {
-      for (uint32_t q = (uint32_t)got; q < meff; ++q) put((int)q, 0.f, 0.f, nper << 16);
-      atomicAdd(reinterpret_cast<unsigned long long*>(&counts->unreached), (unsigned long long)(meff - (uint32_t)got));
+    if constexpr (AHS) {
+      m = traverse<B, false>(tl.nodes, AhsNone{}, oo, dd, s_max, tl.st, [](int, float, float, uint32_t) {});
+      if (m > 0)
+        mi = with_ahs<LDS, AHS>(tl, ahs, footprint,
+                                [&](auto av) { return traverse<B, AHS>(tl.nodes, av, oo, dd, s_max, tl.st, put); });
+    } else {
+      mi = m = traverse<B, false>(tl.nodes, AhsNone{}, oo, dd, s_max, tl.st, put);
     }
   }
+  const uint32_t meff = mi <= s_max ? (uint32_t)mi : (uint32_t)s_max;
+  const uint32_t nper = m == 0 ? 0u : (m <= s_max ? (uint32_t)(s_max / m) : 1u);
+  // intervals in the high and samples in the low part of one sum (both stay below 2^31)
+  const uint64_t own = ((uint64_t)meff << 31) | (meff * nper);
+  uint64_t incl = own;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint64_t y = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += y;
+  }
+  if (lane == 63) s_sum[wave] = incl;
   __syncthreads();
-  const uint32_t n = b1 - b0 < stage_n ? b1 - b0 : stage_n;
-  for (uint32_t q = threadIdx.x; q < n; q += kBlock) {
-    iv_t0[b0 + q] = s_t0[q];
-    iv_dt[b0 + q] = s_dt[q];
-    iv_key[b0 + q] = s_key[q];
-    iv_ray[b0 + q] = s_ray[q];
-    iv_base[b0 + q] = s_base[q];
+  uint64_t sum = 0, first = 0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    if (w < wave) first += s_sum[w];
+    sum += s_sum[w];
+  }
+  if (wave == 0) {
+    const uint64_t before = chain_prefix(state + 1, blk, sum, lane);
+    if (lane == 0) s_before = before;
+  }
+  __syncthreads();
+  const uint64_t at_wave = s_before + first, at = at_wave + (incl - own);
+  constexpr uint32_t kLow = 0x7FFFFFFFu;
+  const uint32_t base = (uint32_t)at & kLow;
+  if ((uint32_t)lane < width) {
+    iv_off[r] = (uint32_t)(at >> 31);
+    smp_off[r] = base;
+  }
+  if (r + 1 == nr) {   // (the last ray of the launch)
+    iv_off[nr] = (uint32_t)((at + own) >> 31);
+    smp_off[nr] = (uint32_t)(at + own) & kLow;
+  }
+  // the wave's intervals, ray-major: entry q belongs to the last ray that starts at or before
+  // it (rays mark their first entry in a 64-entry window, a prefix maximum spreads the marks)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  const uint32_t iv_w = (uint32_t)(at_wave >> 31);
+  const uint32_t pos = (uint32_t)(at >> 31) - iv_w;   // this ray's first entry among the wave's
+  const uint32_t n_w = (uint32_t)(__shfl(incl, 63, 64) >> 31);
+  for (uint32_t q0 = 0; q0 < n_w; q0 += 64) {
+    s_mark[wave][lane] = -1;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (meff != 0 && pos >= q0 && pos < q0 + 64u) s_mark[wave][pos - q0] = lane;
+    const uint64_t started = __ballot(meff != 0 && pos <= q0);   // ray 0 of them at least
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int src = max(wave_max_incl(s_mark[wave][lane]), 63 - (int)__builtin_clzll(started));
+    const uint32_t k = q0 + (uint32_t)lane - __shfl(pos, src, 64);
+    const uint32_t np = __shfl(nper, src, 64), sb = __shfl(base, src, 64);
+    if (q0 + (uint32_t)lane < n_w) {
+      const float2 t = row_t[k * width + (uint32_t)src];
+      const uint32_t slot = row_slot[k * width + (uint32_t)src];
+      const uint32_t q = iv_w + q0 + (uint32_t)lane;
+      iv_t0[q] = t.x;
+      iv_dt[q] = t.y;
+      iv_key[q] = slot | (np << 16);
+      iv_ray[q] = rw + (uint32_t)src;
+      iv_base[q] = sb + k * np;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
-}  // namespace
-
-static hipError_t allow_lds(const void* kern) {
-  return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
-}
-
-template <bool AHS>
-static hipError_t trav_setup_one() {
-  hipError_t e = allow_lds((const void*)k_trav_count<true, AHS>);
-  if (e == hipSuccess) e = allow_lds((const void*)k_trav_count<false, AHS>);
-  if (e == hipSuccess) e = allow_lds((const void*)k_trav_emit<true, AHS>);
-  if (e == hipSuccess) e = allow_lds((const void*)k_trav_emit<false, AHS>);
+template <int B, bool AHS>
+hipError_t trav_setup_one() {
+  auto allow = [](const void* k) {
+    return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+  };
+  hipError_t e = allow((const void*)k_trav<B, true, AHS>);
+  if (e == hipSuccess) e = allow((const void*)k_trav<B, false, AHS>);
   return e;
 }
 
 // Once per device (the attribute is set on the current device).
-static hipError_t trav_setup() {
+hipError_t trav_setup() {
   static std::atomic<uint64_t> done{0};
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   const uint64_t bit = dev < 64 ? 1ull << dev : 0ull;
   if (bit && (done.load() & bit)) return hipSuccess;
-  e = trav_setup_one<false>();
-  if (e == hipSuccess) e = trav_setup_one<true>();
+  e = trav_setup_one<kBlock, false>();
+  if (e == hipSuccess) e = trav_setup_one<kBlock, true>();
+  if (e == hipSuccess) e = trav_setup_one<kBlockSmall, false>();
+  if (e == hipSuccess) e = trav_setup_one<kBlockSmall, true>();
   if (e == hipSuccess) done.fetch_or(bit);
   return e;
 }
 
-template <bool LDS, bool AHS>
-static void count_launch(uint32_t grid, uint32_t bytes, hipStream_t st, const DevNode* nodes, const DevNodeAhs* ahs,
-                         float footprint, uint32_t n_nodes, int stack_n, const float* o, const float* d,
-                         int64_t ray_stride, int64_t r0, uint32_t nr, int s_max, uint32_t* cnt_iv, uint32_t* cnt_smp) {
-  hipLaunchKernelGGL((k_trav_count<LDS, AHS>), dim3(grid), dim3(kBlock), bytes, st, nodes, ahs, footprint, n_nodes,
-                     stack_n, o, d, ray_stride, r0, nr, s_max, cnt_iv, cnt_smp);
+}  // namespace
+
+uint64_t trav_state_words(uint64_t nr) {
+  // enough for any launch of at most nr rays (the last pass of a call is a smaller one)
+  const uint64_t small = (std::min<uint64_t>(nr, kSmallRays) + kBlockSmall - 1) / kBlockSmall;
+  return 1 + std::max<uint64_t>(small, (nr + kBlock - 1) / kBlock);
 }
 
-hipError_t launch_trav_count(const DevNode* nodes, const DevNodeAhs* ahs, float footprint, uint32_t n_nodes, int depth,
-                             const float* o, const float* d, int64_t ray_stride, int64_t r0, uint32_t nr, int s_max,
-                             uint32_t* cnt_iv, uint32_t* cnt_smp, hipStream_t st) {
+hipError_t launch_trav(const DevNode* nodes, const DevNodeAhs* ahs, float footprint, uint32_t n_nodes, int depth,
+                       const float* o, const float* d, int64_t ray_stride, int64_t r0, uint32_t nr, int s_max,
+                       uint32_t iv_cap, float* scratch, uint64_t* state, uint32_t* iv_off, uint32_t* smp_off,
+                       float* iv_t0, float* iv_dt, uint32_t* iv_key, uint32_t* iv_ray, uint32_t* iv_base,
+                       hipStream_t st) {
   if (nr == 0) return hipSuccess;
   hipError_t e = trav_setup();
   if (e != hipSuccess) return e;
   const int stack_n = depth + 1;
-  const uint32_t grid = (nr + kBlock - 1) / kBlock;
-  const bool lds = n_nodes <= (uint32_t)kLdsNodes, hs = ahs != nullptr;
-  const uint32_t bytes = trav_lds_bytes(lds, hs, n_nodes, stack_n);
-  auto go = [&](auto fn) { fn(grid, bytes, st, nodes, ahs, footprint, n_nodes, stack_n, o, d, ray_stride, r0, nr, s_max,
-                              cnt_iv, cnt_smp); };
-  if (lds && hs) go(count_launch<true, true>);
-  else if (lds) go(count_launch<true, false>);
-  else if (hs) go(count_launch<false, true>);
-  else go(count_launch<false, false>);
-  return hipGetLastError();
-}
-
-template <bool LDS, bool AHS>
-static void emit_launch(uint32_t grid, uint32_t bytes, hipStream_t st, const DevNode* nodes, const DevNodeAhs* ahs,
-                        float footprint, uint32_t n_nodes, int stack_n, uint32_t stage_n, const float* o,
-                        const float* d, int64_t ray_stride, int64_t r0, uint32_t nr, const uint32_t* cnt_iv,
-                        const uint32_t* cnt_smp, const uint32_t* iv_off, const uint32_t* smp_off, float* iv_t0,
-                        float* iv_dt, uint32_t* iv_key, uint32_t* iv_ray, uint32_t* iv_base, ChunkCounts* counts) {
-  hipLaunchKernelGGL((k_trav_emit<LDS, AHS>), dim3(grid), dim3(kBlock), bytes, st, nodes, ahs, footprint, n_nodes,
-                     stack_n, stage_n, o, d, ray_stride, r0, nr, cnt_iv, cnt_smp, iv_off, smp_off, iv_t0, iv_dt,
-                     iv_key, iv_ray, iv_base, counts);
-}
-
-hipError_t launch_trav_emit(const DevNode* nodes, const DevNodeAhs* ahs, float footprint, uint32_t n_nodes, int depth,
-                            const float* o, const float* d, int64_t ray_stride, int64_t r0, uint32_t nr,
-                            const uint32_t* cnt_iv, const uint32_t* cnt_smp, const uint32_t* iv_off,
-                            const uint32_t* smp_off, float* iv_t0, float* iv_dt, uint32_t* iv_key, uint32_t* iv_ray,
-                            uint32_t* iv_base, ChunkCounts* counts, hipStream_t st) {
-  if (nr == 0) return hipSuccess;
-  hipError_t e = trav_setup();
-  if (e != hipSuccess) return e;
-  const int stack_n = depth + 1;
-  const uint32_t grid = (nr + kBlock - 1) / kBlock;
-  const bool lds = n_nodes <= (uint32_t)kLdsNodes, hs = ahs != nullptr;
-  // staging sized so that two blocks still fit in a CU's 160 KiB of LDS (the traversal
-  // needs the occupancy), at most 2048 entries of 20 bytes
-  const uint32_t fixed = trav_lds_bytes(lds, hs, n_nodes, stack_n);
-  const uint32_t budget = 80u * 1024u;
-  uint32_t stage_n = fixed + 20u * 256u <= budget ? (budget - fixed) / 20u : 256u;
-  stage_n = std::min<uint32_t>(stage_n, 2048u) & ~63u;
-  const uint32_t bytes = fixed + 20u * stage_n;
-  auto go = [&](auto fn) { fn(grid, bytes, st, nodes, ahs, footprint, n_nodes, stack_n, stage_n, o, d, ray_stride, r0,
-                              nr, cnt_iv, cnt_smp, iv_off, smp_off, iv_t0, iv_dt, iv_key, iv_ray, iv_base, counts); };
-  if (lds && hs) go(emit_launch<true, true>);
-  else if (lds) go(emit_launch<true, false>);
-  else if (hs) go(emit_launch<false, true>);
-  else go(emit_launch<false, false>);
+  const bool lds = n_nodes <= (uint32_t)kLdsNodes, hs = ahs != nullptr, small = nr < kSmallRays;
+  const int block = small ? kBlockSmall : kBlock;
+  const uint32_t grid = (nr + (uint32_t)block - 1) / (uint32_t)block;
+  const uint32_t bytes = trav_lds_bytes(block, lds, hs, n_nodes, stack_n);
+  float2* const scratch_t = reinterpret_cast<float2*>(scratch);
+  uint32_t* const scratch_slot = reinterpret_cast<uint32_t*>(scratch + 2 * (uint64_t)nr * iv_cap);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(block), bytes, st, nodes, ahs, footprint, n_nodes, stack_n, o, d,
+                       ray_stride, r0, nr, s_max, iv_cap, scratch_t, scratch_slot, state, iv_off, smp_off, iv_t0, iv_dt,
+                       iv_key, iv_ray, iv_base);
+  };
+  if (small) {
+    if (lds && hs) go(k_trav<kBlockSmall, true, true>);
+    else if (lds) go(k_trav<kBlockSmall, true, false>);
+    else if (hs) go(k_trav<kBlockSmall, false, true>);
+    else go(k_trav<kBlockSmall, false, false>);
+  } else {
+    if (lds && hs) go(k_trav<kBlock, true, true>);
+    else if (lds) go(k_trav<kBlock, true, false>);
+    else if (hs) go(k_trav<kBlock, false, true>);
+    else go(k_trav<kBlock, false, false>);
+  }
   return hipGetLastError();
 }
 
