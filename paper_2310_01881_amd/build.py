@@ -17,7 +17,7 @@ BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libamnerf.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["amnerf.cpp", "trav.hip", "scan.hip", "sort.hip", "mlp.hip", "mlp8.hip", "mlp_bwd.hip", "comp.hip",
+SOURCES = ["amnerf.cpp", "trav.hip", "scan.hip", "sort.hip", "mlp.hip", "mlp32.hip", "mlp8.hip", "mlp_bwd.hip", "comp.hip",
            "train.hip", "prop.hip", "err.hip", "ess.hip", "ert.hip"]
 # Packed fp32 arithmetic is disabled for all device code.
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
@@ -28,6 +28,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-u
 # copied out (one v_accvgpr_read per value).
 PER_FILE = {"prop.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
             "mlp_bwd.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
+            "mlp32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"],
             "mlp8.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 

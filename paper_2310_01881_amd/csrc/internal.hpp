@@ -154,6 +154,14 @@ hipError_t launch_mlp(const MlpGeom& g, const void* packed, uint32_t n_leaves,
                       const uint32_t* perm, const float* o, const float* d, int64_t ray_stride,
                       int64_t r0, float* out, hipStream_t st);
 
+// ---- float32 leaf MLPs on the bfloat16 matrix cores (values split in three) ----------------
+// Whether the split weights of a leaf fit a compute unit's LDS (n_hidden <= 7 at hidden 64).
+bool mlp32_fits(int n_hidden, int hidden);
+hipError_t launch_mlp32(int n_hidden, int hidden, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
+                        const uint32_t* tile_off, const ChunkCounts* counts, const uint32_t* srec_ray,
+                        const float* srec_t, const uint32_t* perm, const float* o, const float* d, int64_t stride,
+                        int64_t r0, float* out, hipStream_t st);
+
 // ---- float8 weights and activations on the float8 matrix cores (hidden width 64,
 // n_hidden 1..4) ----------------------------------------------------------------------------
 size_t mlp8_block_bytes(int n_hidden);

@@ -14,7 +14,8 @@
 // packer orders each layer's K index so that exactly those values are the next layer's B
 // operand for that lane.  Activations therefore never leave registers between layers.
 // Biases enter as the C operand of the first MFMA of each output block.
-//   F32  : v_mfma_f32_16x16x4_f32  (fp32 in, fp32 accumulate)
+//   F32  : v_mfma_f32_16x16x4_f32  (fp32 in, fp32 accumulate); only for the one shape whose
+//          split weights do not fit the LDS (8 layers of 64), the others run in mlp32.hip
 //   BF16 : v_mfma_f32_16x16x32_bf16 (bf16 in, fp32 accumulate)
 //   FP8  : the BF16 kernel; the leaf's e4m3 weights are widened to bf16 (times the layer's
 //          scale) while they are staged into LDS, so the block in memory is half the size.
@@ -600,8 +601,12 @@ hipError_t launch_mlp(const MlpGeom& g, const void* packed, uint32_t n_leaves, c
     if (g.hidden == 64) return launch_typed<64, true>(L, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, ray_stride, r0, out, st);
     return launch_typed<32, true>(L, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, ray_stride, r0, out, st);
   }
-  if (g.hidden == 64) return launch_typed<64, false>(L, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, ray_stride, r0, out, st);
-  return launch_typed<32, false>(L, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, ray_stride, r0, out, st);
+  // float32: the split kernel (twice as fast) wherever its weights fit a compute unit's LDS,
+  // which leaves 8 layers of 64 to the float32 matrix instructions
+  if (mlp32_fits(g.n_hidden, g.hidden))
+    return launch_mlp32(g.n_hidden, g.hidden, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d,
+                        ray_stride, r0, out, st);
+  return launch_typed<64, false>(L, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, ray_stride, r0, out, st);
 }
 
 }  // namespace amn
