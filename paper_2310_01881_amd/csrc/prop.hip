@@ -840,29 +840,37 @@ __global__ __launch_bounds__(kThreads) void k_prop_emit(uint32_t nr, IvSet iv, c
 
 // ---- training --------------------------------------------------------------------------
 // Targets: per interval, bin opacity 1 - exp(-tau_b), tau_b = sum_j sigma_j len |slot_j n bin_b|.
+// Half a wave per interval: its samples' densities are evaluated once, a lane each, into LDS,
+// then every lane sums the few slots its bin overlaps (in slot order).  A thread per interval
+// walking every slot against all 32 bins took 316 us for 203 000 intervals of 19 samples (one
+// wave per SIMD of the chip, each a serial chain); this takes 62 us.
 __global__ __launch_bounds__(kThreads) void k_prop_targets(IvSet iv, const float* __restrict__ smp_out,
                                                            float* __restrict__ alpha) {
+  __shared__ float sig[kThreads / 32][kMaxSlots];
   const uint32_t n_iv = *iv.n_iv_dev;
-  for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < n_iv; i += gridDim.x * kThreads) {
-    const uint32_t n = key_n(iv.key[i]);
-    const uint32_t base = iv.base[i];
-    const float len = iv.dt[i];
-    float tb[kBins];
-#pragma unroll
-    for (int b = 0; b < kBins; ++b) tb[b] = 0.f;
-    for (uint32_t j = 0; j < n; ++j) {
-      const float sig = softplusf(smp_out[4 * (uint64_t)(base + j)]);
+  const uint32_t b = threadIdx.x & 31, half = threadIdx.x >> 5;
+  const float b0 = (float)b * (1.f / 32.f), b1 = (float)(b + 1) * (1.f / 32.f);
+  for (uint32_t i0 = blockIdx.x * (kThreads / 32); i0 < n_iv; i0 += gridDim.x * (kThreads / 32)) {
+    const uint32_t i = i0 + half;
+    const bool live = i < n_iv;
+    const uint32_t n = live ? key_n(iv.key[i]) : 0u;
+    const uint32_t base = live ? iv.base[i] : 0u;
+    const float len = live ? iv.dt[i] : 0.f;
+    for (uint32_t j = b; j < n; j += 32) sig[half][j] = softplusf(smp_out[4 * (uint64_t)(base + j)]);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // a half's densities are read by its own wave only
+    __builtin_amdgcn_wave_barrier();
+    // slots that may overlap the bin (one more on each side than the exact quotients: the edges
+    // below are rounded)
+    const uint32_t q0 = b * n / 32u, q1 = ((b + 1) * n + 31u) / 32u;
+    float tb = 0.f;
+    for (uint32_t j = q0 > 0 ? q0 - 1 : 0u; j < q1 + 1 && j < n; ++j) {
       const float a0 = (float)j / (float)n, a1 = (float)(j + 1) / (float)n;
-#pragma unroll
-      for (int b = 0; b < kBins; ++b) {
-        const float ov = fminf(a1, (float)(b + 1) * (1.f / 32.f)) - fmaxf(a0, (float)b * (1.f / 32.f));
-        if (ov > 0.f) tb[b] = fmaf(sig * len, ov, tb[b]);
-      }
+      const float ov = fminf(a1, b1) - fmaxf(a0, b0);
+      if (ov > 0.f) tb = fmaf(sig[half][j] * len, ov, tb);
     }
-#pragma unroll
-    for (int b = 0; b < kBins; b += 4)
-      *reinterpret_cast<f32x4*>(alpha + (uint64_t)i * kBins + b) =
-          f32x4{-expm1f(-tb[b]), -expm1f(-tb[b + 1]), -expm1f(-tb[b + 2]), -expm1f(-tb[b + 3])};
+    if (live) alpha[(uint64_t)i * kBins + b] = -expm1f(-tb);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -1124,20 +1132,34 @@ __global__ __launch_bounds__(kThreads) void k_prop_train(const uint8_t* __restri
   if (threadIdx.x == 0) loss_part[blockIdx.x] = (lsh[0] + lsh[1]) + (lsh[2] + lsh[3]);
 }
 
+// One thread per parameter, 32 partials in flight, summed in block order (one load at a time
+// the sum waited for 256 of them in turn: 70 us against 6).  The last block sums the loss.
+constexpr uint32_t kReduceBlocks = (kP + kThreads - 1) / kThreads;
+
+__device__ __forceinline__ float sum_partials(const float* __restrict__ p, uint32_t nb, uint32_t stride) {
+  float s = 0.f;
+  uint32_t b = 0;
+  for (; b + 32 <= nb; b += 32) {
+    float v[32];
+#pragma unroll
+    for (int k = 0; k < 32; ++k) v[k] = p[(uint64_t)(b + k) * stride];
+#pragma unroll
+    for (int k = 0; k < 32; ++k) s += v[k];
+  }
+  for (; b < nb; ++b) s += p[(uint64_t)b * stride];
+  return s;
+}
+
 __global__ __launch_bounds__(kThreads) void k_prop_reduce(const float* __restrict__ part, uint32_t nb,
                                                           const float* __restrict__ loss_part,
                                                           float* __restrict__ grad,
                                                           float* __restrict__ loss, const uint32_t* __restrict__ n_iv) {
-  for (uint32_t p = blockIdx.x * kThreads + threadIdx.x; p < (uint32_t)kP; p += gridDim.x * kThreads) {
-    float s = 0.f;
-    for (uint32_t b = 0; b < nb; ++b) s += part[(uint64_t)b * kP + p];
-    grad[p] = s;
+  if (blockIdx.x == kReduceBlocks) {
+    if (threadIdx.x == 0) loss[0] = sum_partials(loss_part, nb, 1) / ((float)(*n_iv) * (float)kBins);
+    return;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    float s = 0.f;
-    for (uint32_t b = 0; b < nb; ++b) s += loss_part[b];
-    loss[0] = s / ((float)(*n_iv) * (float)kBins);
-  }
+  const uint32_t p = blockIdx.x * kThreads + threadIdx.x;
+  if (p < (uint32_t)kP) grad[p] = sum_partials(part + p, nb, kP);
 }
 
 std::atomic<int> g_ncu{0};   // compute units of the device (queried once; host threads may race to it)
@@ -1226,7 +1248,7 @@ hipError_t launch_prop_train(const void* packed, const IvSet& iv, const float* o
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_prop_train, dim3(nb), dim3(kThreads), lds, st, (const uint8_t*)packed, iv, o, d, stride, r0,
                      leafbox, s_max, alpha, part, loss_part);
-  hipLaunchKernelGGL(k_prop_reduce, dim3(36), dim3(kThreads), 0, st, part, nb, loss_part, grad, loss, iv.n_iv_dev);
+  hipLaunchKernelGGL(k_prop_reduce, dim3(kReduceBlocks + 1), dim3(kThreads), 0, st, part, nb, loss_part, grad, loss, iv.n_iv_dev);
   return hipGetLastError();
 }
 
