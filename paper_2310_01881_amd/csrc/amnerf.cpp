@@ -1241,7 +1241,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
       HIP_TRY(launch_mlp(g, mlp->packed_dev, L, w.bucket_off, w.tile_off, cc, w.srec_ray, w.srec_t, w.perm,
                          rays->o_dev, rays->d_dev, R, r0, w.smp_out, cs));
       HIP_TRY(mark(5));
-      HIP_TRY(launch_composite(nr, use, w.smp_out, r0, jitter, p->jitter_seed, p->ert_eps, out->rgb_dev,
+      HIP_TRY(launch_composite(nr, use, !wait_count, w.smp_out, r0, jitter, p->jitter_seed, p->ert_eps, out->rgb_dev,
                                out->depth_dev, out->opacity_dev, out->weights_dev, w.ray_used, cc, cs));
     } else {
       // round k: the samples of window k of the rays still marching, compacted in sorted
@@ -1257,7 +1257,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
         HIP_TRY(launch_mlp(g, mlp->packed_dev, L, w.c_boff, w.c_toff, cc, w.c_ray, w.c_t, w.c_perm, rays->o_dev,
                            rays->d_dev, R, r0, w.smp_out, cs));
         if (k + 1 == n_rounds) HIP_TRY(mark(5));
-        HIP_TRY(launch_composite_round(nr, use, w.smp_out, r0, jitter, p->jitter_seed, p->ert_eps, out->rgb_dev,
+        HIP_TRY(launch_composite_round(nr, use, !wait_count, w.smp_out, r0, jitter, p->jitter_seed, p->ert_eps, out->rgb_dev,
                                        out->depth_dev, out->opacity_dev, out->weights_dev, w.ray_used, cc, w.carry,
                                        k, cs));
       }

@@ -50,160 +50,215 @@ __device__ __forceinline__ DF df_add(DF a, DF b) {
 // exp(-(hi + lo)) for |lo| << 1: exp(-hi) * (1 - lo).
 __device__ __forceinline__ float df_exp_neg(DF a) { return exp_neg(a.hi) * (1.f - a.lo); }
 
-// Inclusive compensated prefix sum over the wave on wave_scan_incl's shift pattern (within
-// rows of 16 by 1, 2, 4, 8, then the last lane of row 0 (2) into row 1 (3) and the last
-// lane of row 1 into rows 2 and 3; lanes whose source is outside the pattern add 0).  The
-// high parts are added with an exact TwoSum; the low parts, and each TwoSum's rounding
-// error, go into a plain running sum of low parts, normalised once at the end.
-template <int CTRL, int ROW_MASK>
+// Inclusive compensated prefix sum over the 16 lanes of a row (shifts by 1, 2, 4, 8; lanes
+// whose source is outside the row add 0).  The high parts are added with an exact TwoSum; the
+// low parts, and each TwoSum's rounding error, go into a plain running sum of low parts,
+// normalised once at the end.
+template <int CTRL>
 __device__ __forceinline__ void df_scan_step(float& hi, float& lo) {
-  const float b = dpp_or_zero<CTRL, ROW_MASK>(hi);
+  const float b = dpp_or_zero<CTRL, 0xF>(hi);
   const float s = hi + b;
   const float bb = s - hi;
   const float e = (hi - (s - bb)) + (b - bb);
-  lo = lo + dpp_or_zero<CTRL, ROW_MASK>(lo) + e;
+  lo = lo + dpp_or_zero<CTRL, 0xF>(lo) + e;
   hi = s;
 }
 
-__device__ __forceinline__ DF df_scan_incl(DF v) {
-  float hi = v.hi, lo = v.lo;
-  df_scan_step<0x111, 0xF>(hi, lo);
-  df_scan_step<0x112, 0xF>(hi, lo);
-  df_scan_step<0x114, 0xF>(hi, lo);
-  df_scan_step<0x118, 0xF>(hi, lo);
-  df_scan_step<0x142, 0xA>(hi, lo);
-  df_scan_step<0x143, 0xC>(hi, lo);
+__device__ __forceinline__ DF row_scan_incl(float v) {
+  float hi = v, lo = 0.f;
+  df_scan_step<0x111>(hi, lo);
+  df_scan_step<0x112>(hi, lo);
+  df_scan_step<0x114>(hi, lo);
+  df_scan_step<0x118>(hi, lo);
   const float h = hi + lo;
   return {h, lo - (h - hi)};
 }
 
-__device__ __forceinline__ float wave_sum(float v) { return lane_value(wave_scan_incl(v), 63); }
+// Sum over the row, in its last lane (the other lanes hold partial sums).
+__device__ __forceinline__ float row_sum_last(float v) {
+  v += dpp_or_zero<0x111, 0xF>(v);
+  v += dpp_or_zero<0x112, 0xF>(v);
+  v += dpp_or_zero<0x114, 0xF>(v);
+  v += dpp_or_zero<0x118, 0xF>(v);
+  return v;
+}
+__device__ __forceinline__ float row_last(float v) { return dpp_or_zero<0x15F, 0xF>(v); }   // row_newbcast:15
 
-// One wave per ray, 64 samples per step.  Lane j of a step handles sample base + j:
-// tau_j, then S_j = sum_{i<j} tau_i by a compensated (float pair) prefix scan across the
-// wave plus the running total of earlier steps; T_j = exp(-S_j), w_j = T_j (1 - e^-tau_j).
-// Early termination: the first lane whose T_{j+1} < eps keeps its sample and later lanes
-// (and steps) contribute nothing.  T_j is the neighbouring lane's T_{j+1} (the exclusive
-// sum of lane j is the inclusive sum of lane j - 1), so one exponential per sample serves
-// both.  Each step's weighted sums are reduced across the wave and added to the ray's
-// running totals, so the state carried from one step to the next is a handful of scalars.
-// Lane j finds its interval by binary search over the intervals' first-sample indices.
+// Four rays per wave, a row of 16 lanes each, 16 samples of every ray per step.  Lane c of a
+// row handles sample base + c: tau_j, then S_j = sum_{i<j} tau_i by a compensated (float pair)
+// prefix scan across the row plus the running total of earlier steps; T_j = exp(-S_j), w_j =
+// T_j (1 - e^-tau_j).  Early termination: the first lane whose T_{j+1} < eps keeps its sample
+// and later lanes (and steps) of its ray contribute nothing.  T_j is the neighbouring lane's
+// T_{j+1}, so one exponential per sample serves both.  Each lane keeps its own weighted sums;
+// they are reduced across the row once per window of 64 samples.
 //
-// ROUND: one 64-sample window (step `round`) of every ray that is still marching, the state
-// of the earlier windows read from and written back to `carry`; a ray's outputs are written
-// when it terminates or its last window is done.  The arithmetic of each step is the same
-// as in the single pass, so a render in rounds is bit-identical to one in a single pass.
-constexpr uint32_t kStage = 256;   // intervals of a ray searched in LDS (more: in memory)
+// What bounds it is the latency of a ray's chain (offsets -> interval records and samples ->
+// scan) and the vector work per ray.  One wave per ray (64 samples per step, a 6-step scan and
+// five 6-step reductions for rays that composite 26 to 52 samples on average, most of them
+// stopping in their first step) issued about three times the instructions per ray and held a
+// quarter of the rays in flight: 800x800 frame 334 -> 201 us (61 M samples, 3.0 -> 4.9
+// TB/s), planned 267 -> 140 us.  A step's samples are loaded two steps ahead.
+//
+// The ray's interval records are staged in LDS (kStage of them; the rest are read from
+// memory).  UNIFORM: every interval of a ray has the same number of samples (all but planned
+// intervals), so a sample's interval is a quotient; otherwise a binary search over the
+// intervals' first samples.
+//
+// ROUND: one 64-sample window (`round`) of every ray that is still marching, the state of the
+// earlier windows read from and written back to `carry`; a ray's outputs are written when it
+// terminates or its last window is done.  The arithmetic of a window is the same as in the
+// single pass, so a render in rounds is bit-identical to one in a single pass.
+constexpr uint32_t kStage = 64;
+constexpr uint32_t kRays = 4;      // per wave
 constexpr uint32_t kDone = 0x80000000u;
 
-template <bool ROUND>
-__global__ __launch_bounds__(kThreads) void k_composite(
+template <bool ROUND, bool UNIFORM>
+__global__ __launch_bounds__(kThreads, 8) void k_composite(
     uint32_t nr, IvSet iv, const float* __restrict__ smp_out, int64_t r0, int jitter,
     uint64_t seed, float eps, float* __restrict__ rgb, float* __restrict__ depth,
     float* __restrict__ opac, float* __restrict__ weights, uint32_t* __restrict__ ray_used,
     ChunkCounts* __restrict__ counts, CompCarry* __restrict__ carry_st, uint32_t round) {
-  __shared__ uint32_t sbase[kThreads / 64][kStage];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t r = blockIdx.x * (kThreads / 64) + wave;
-  if (r >= nr) return;
-  const uint32_t i0 = iv.iv_off[r], i1 = iv.iv_off[r + 1];
-  const uint32_t s0 = iv.smp_off[r], ns = iv.smp_off[r + 1] - s0;
+  constexpr uint32_t kRows = kThreads / 64 * kRays;
+  __shared__ float s_t0[kRows][kStage], s_delta[kRows][kStage];
+  __shared__ uint32_t s_base[UNIFORM ? 1 : kRows][kStage];   // first sample, relative to the ray's
+  const int lane = threadIdx.x & 63, row = threadIdx.x >> 4;
+  const uint32_t c = (uint32_t)lane & 15u;
+  const uint32_t r = blockIdx.x * kRows + (uint32_t)row;
+  const bool live = r < nr;
+  const uint32_t i0 = live ? iv.iv_off[r] : 0u, m = live ? iv.iv_off[r + 1] - i0 : 0u;
+  const uint32_t s0 = live ? iv.smp_off[r] : 0u, ns = live ? iv.smp_off[r + 1] - s0 : 0u;
   uint32_t sb = 0, se = ns;                    // this launch's samples of the ray
-  DF S = {0.f, 0.f};                           // sum of tau before sample sb
-  float tot[5] = {0.f, 0.f, 0.f, 0.f, 0.f};    // rgb, depth, opacity so far
+  bool marching = live;
+  DF S = {0.f, 0.f};                           // sum of tau before the current step
+  float tot[5] = {0.f, 0.f, 0.f, 0.f, 0.f};    // rgb, depth, opacity of the windows so far (last lane)
   if (ROUND) {
     sb = 64u * round;
-    if (sb >= ns && !(ns == 0 && round == 0)) return;   // finished in an earlier window
-    if (round > 0) {
-      const CompCarry c = carry_st[r];
-      if (c.state & kDone) return;
-      S = {c.s_hi, c.s_lo};
-      tot[0] = c.cr; tot[1] = c.cg; tot[2] = c.cb; tot[3] = c.dep; tot[4] = c.acc;
+    if (sb >= ns && !(ns == 0 && round == 0)) marching = false;   // finished in an earlier window
+    if (marching && round > 0) {
+      const CompCarry cy = carry_st[r];
+      if (cy.state & kDone) marching = false;
+      S = {cy.s_hi, cy.s_lo};
+      tot[0] = cy.cr; tot[1] = cy.cg; tot[2] = cy.cb; tot[3] = cy.dep; tot[4] = cy.acc;
     }
     se = sb + 64u < ns ? sb + 64u : ns;
   }
-  // the ray's interval start samples (relative to s0), searched in LDS
-  const uint32_t m = i1 - i0;
-  const bool staged = m <= kStage;
-  if (staged) {
-    for (uint32_t k = lane; k < m; k += 64) sbase[wave][k] = iv.base[i0 + k] - s0;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
+  if (__ballot(marching) == 0) return;
+  bool done = !marching;
+  auto load = [&](uint32_t j) {
+    float4 z = {0.f, 0.f, 0.f, 0.f};
+    if (!done && j < se) z = *reinterpret_cast<const float4*>(smp_out + 4 * (uint64_t)(s0 + j));
+    return z;
+  };
+  float4 z0 = load(sb + c), z1 = load(sb + 16u + c);
+  // samples per interval (UNIFORM) and floor(x / n) = umulhi(x, ceil(2^32 / n)), x < 2^16
+  const uint32_t n = UNIFORM && m > 0 ? ns / m : 1u;
+  const uint32_t m32 = n > 1u ? 0xFFFFFFFFu / n + 1u : 0u;
+  if (marching)
+    for (uint32_t k = c; k < m && k < kStage; k += 16u) {
+      s_t0[row][k] = iv.t0[i0 + k];
+      s_delta[row][k] = iv.dt[i0 + k] / (float)(UNIFORM ? n : key_n(iv.key[i0 + k]));
+      if (!UNIFORM) s_base[row][k] = iv.base[i0 + k] - s0;
+    }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   const uint64_t wbase = counts->smp_global + s0;
   uint32_t used = ns;   // samples composited: up to and including the stop sample
-  bool done = false;
   uint32_t next = sb;   // first sample after the last step processed
-  for (uint32_t base = sb; base < se; base += 64) {
-    next = base + 64u;
-    const uint32_t j = base + lane;
-    const bool valid = !done && j < ns;
-    float tau = 0.f, sig_c[3] = {0.f, 0.f, 0.f}, t = 0.f;
+  bool stopped = false;
+  float part[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+  for (uint32_t base = sb; __ballot(!done && base < se) != 0; base += 16u) {
+    const uint32_t j = base + c;
+    const float4 z = z0;
+    z0 = z1;
+    z1 = load(j + 32u);
+    const bool valid = !done && j < se;
+    uint32_t k = 0, jj = 0;
+    float t0 = 0.f, delta = 0.f;
     if (valid) {
-      uint32_t i;
-      if (staged) {
+      if (UNIFORM) {
+        k = n > 1u ? __umulhi(j, m32) : j;
+        jj = j - k * n;
+        if (k < kStage) {
+          t0 = s_t0[row][k];
+          delta = s_delta[row][k];
+        } else {
+          t0 = iv.t0[i0 + k];
+          delta = iv.dt[i0 + k] / (float)n;
+        }
+      } else if (m <= kStage) {
         uint32_t lo = 0, hi = m;
         while (hi - lo > 1) {
           const uint32_t mid = (lo + hi) >> 1;
-          if (sbase[wave][mid] <= j) lo = mid; else hi = mid;
+          if (s_base[row][mid] <= j) lo = mid; else hi = mid;
         }
-        i = i0 + lo;
+        k = lo;
+        jj = j - s_base[row][k];
+        t0 = s_t0[row][k];
+        delta = s_delta[row][k];
       } else {
-        i = find_interval(iv.base, i0, i1, s0 + j);
+        const uint32_t i = find_interval(iv.base, i0, i0 + m, s0 + j);
+        k = i - i0;
+        jj = s0 + j - iv.base[i];
+        t0 = iv.t0[i];
+        delta = iv.dt[i] / (float)key_n(iv.key[i]);
       }
-      const uint32_t jj = s0 + j - iv.base[i];
-      const float4 z = *reinterpret_cast<const float4*>(smp_out + 4 * (uint64_t)(s0 + j));
-      const float delta = iv.dt[i] / (float)key_n(iv.key[i]);
-      const float u = stratum_u(jitter, seed, (uint64_t)(r0 + r), i - i0);
-      t = sample_t(iv.t0[i], delta, jj, u);
-      tau = softplusf(z.x) * delta;       // sigma = softplus, rgb = logistic
-      sig_c[0] = logisticf(z.y);
-      sig_c[1] = logisticf(z.z);
-      sig_c[2] = logisticf(z.w);
     }
-    // inclusive compensated scan of tau across the wave; exclusive = shifted by one lane
-    const DF inc = df_scan_incl({tau, 0.f});
-    const DF Sn = df_add(S, inc);
-    const float Tn = df_exp_neg(Sn);                        // T_{j+1}
-    const float Tsh = dpp_or_zero<0x138, 0xF>(Tn);          // wave_shr:1: lane j - 1's T_j
-    const float T = lane == 0 ? df_exp_neg(S) : Tsh;
+    const float u = jitter ? stratum_u(1, seed, (uint64_t)(r0 + r), k) : 0.5f;
+    const float t = sample_t(t0, delta, jj, u);
+    const float tau = valid ? softplusf(z.x) * delta : 0.f;   // sigma = softplus, rgb = logistic
+    // inclusive compensated scan of tau across the row; exclusive = shifted by one lane
+    const DF Sn = df_add(S, row_scan_incl(tau));
+    const float Tn = df_exp_neg(Sn);                     // T_{j+1}
+    const float Tsh = dpp_or_zero<0x111, 0xF>(Tn);       // row_shr:1: lane c - 1's T_{j+1}
+    const float T = c == 0 ? df_exp_neg(S) : Tsh;
     float w = valid ? T * one_minus_exp_neg(tau) : 0.f;
     const bool stop = valid && eps > 0.f && Tn < eps;
-    const uint64_t stops = __ballot(stop);
-    if (stops) {
-      const int first = __ffsll((unsigned long long)stops) - 1;
-      if (lane > first) w = 0.f;
+    const uint32_t stops = (uint32_t)(__ballot(stop) >> (lane & 48)) & 0xFFFFu;
+    const bool now = stops != 0;
+    const uint32_t first = (uint32_t)__ffs((int)stops) - 1u;
+    if (now && c > first) w = 0.f;
+    part[0] = fmaf(w, logisticf(z.y), part[0]);
+    part[1] = fmaf(w, logisticf(z.z), part[1]);
+    part[2] = fmaf(w, logisticf(z.w), part[2]);
+    part[3] = fmaf(w, t, part[3]);
+    part[4] += w;
+    if (weights && valid) weights[wbase + j] = w;
+    S = {row_last(Sn.hi), row_last(Sn.lo)};
+    if (!done) next = base + 16u;
+    if (now) {
+      used = base + first + 1u;
+      stopped = true;
       done = true;
-      used = base + (uint32_t)first + 1u;
     }
-    tot[0] += wave_sum(w * sig_c[0]);
-    tot[1] += wave_sum(w * sig_c[1]);
-    tot[2] += wave_sum(w * sig_c[2]);
-    tot[3] += wave_sum(w * t);
-    tot[4] += wave_sum(w);
-    if (weights && j < ns) weights[wbase + j] = w;
-    S = {lane_value(Sn.hi, 63), lane_value(Sn.lo, 63)};
-    if (done) break;
+    if (((base - sb) & 63u) == 48u) {   // the window is complete
+#pragma unroll
+      for (int q = 0; q < 5; ++q) {
+        tot[q] += row_sum_last(part[q]);
+        part[q] = 0.f;
+      }
+    }
   }
+#pragma unroll
+  for (int q = 0; q < 5; ++q) tot[q] += row_sum_last(part[q]);   // what is left of the last window
+  if (!marching) return;
   // a ray that stopped has weight 0 on every later sample
-  if (weights && done)
-    for (uint32_t j = next + lane; j < ns; j += 64) weights[wbase + j] = 0.f;
-  if (ROUND && !done && se < ns) {
-    if (lane == 0) carry_st[r] = {S.hi, S.lo, tot[0], tot[1], tot[2], tot[3], tot[4], 0u};
+  if (weights && stopped)
+    for (uint32_t j = next + c; j < ns; j += 16) weights[wbase + j] = 0.f;
+  if (c != 15u) return;
+  if (ROUND && !stopped && se < ns) {
+    carry_st[r] = {S.hi, S.lo, tot[0], tot[1], tot[2], tot[3], tot[4], 0u};
     return;
   }
-  if (lane == 0) {
-    if (ROUND) carry_st[r].state = kDone;
-    ray_used[r] = used;
-    rgb[3 * (uint64_t)(r0 + r) + 0] = tot[0];
-    rgb[3 * (uint64_t)(r0 + r) + 1] = tot[1];
-    rgb[3 * (uint64_t)(r0 + r) + 2] = tot[2];
-    if (depth) depth[r0 + r] = tot[3];
-    if (opac) opac[r0 + r] = tot[4];
-    if (!isfinite(tot[0]) || !isfinite(tot[1]) || !isfinite(tot[2]) || !isfinite(tot[3]) || !isfinite(tot[4]))
-      atomicAdd(reinterpret_cast<unsigned long long*>(&counts->nonfinite), 1ull);
-  }
+  if (ROUND) carry_st[r].state = kDone;
+  ray_used[r] = used;
+  rgb[3 * (uint64_t)(r0 + r) + 0] = tot[0];
+  rgb[3 * (uint64_t)(r0 + r) + 1] = tot[1];
+  rgb[3 * (uint64_t)(r0 + r) + 2] = tot[2];
+  if (depth) depth[r0 + r] = tot[3];
+  if (opac) opac[r0 + r] = tot[4];
+  if (!isfinite(tot[0]) || !isfinite(tot[1]) || !isfinite(tot[2]) || !isfinite(tot[3]) || !isfinite(tot[4]))
+    atomicAdd(reinterpret_cast<unsigned long long*>(&counts->nonfinite), 1ull);
 }
 
 // counts->composited += sum of ray_used[0, nr): block sums in a fixed order, one integer
@@ -266,27 +321,27 @@ __global__ __launch_bounds__(kThreads) void k_pass_begin(ChunkCounts* counts, in
 
 }  // namespace
 
-hipError_t launch_composite(uint32_t nr, const IvSet& iv, const float* smp_out, int64_t r0,
+hipError_t launch_composite(uint32_t nr, const IvSet& iv, bool uniform, const float* smp_out, int64_t r0,
                             int jitter, uint64_t seed, float ert_eps, float* rgb, float* depth,
                             float* opac, float* weights, uint32_t* ray_used, ChunkCounts* counts,
                             hipStream_t st) {
   if (nr == 0) return hipSuccess;
-  const uint32_t rays_per_block = kThreads / 64;
-  uint32_t grid = (nr + rays_per_block - 1) / rays_per_block;
-  hipLaunchKernelGGL(k_composite<false>, dim3(grid), dim3(kThreads), 0, st, nr, iv, smp_out, r0, jitter, seed,
-                     ert_eps, rgb, depth, opac, weights, ray_used, counts, nullptr, 0u);
+  const uint32_t rays = kThreads / 64 * kRays;
+  hipLaunchKernelGGL((uniform ? k_composite<false, true> : k_composite<false, false>), dim3((nr + rays - 1) / rays),
+                     dim3(kThreads), 0, st, nr, iv, smp_out, r0, jitter, seed, ert_eps, rgb, depth, opac, weights,
+                     ray_used, counts, nullptr, 0u);
   return launch_sum_used(nr, ray_used, counts, st);
 }
 
-hipError_t launch_composite_round(uint32_t nr, const IvSet& iv, const float* smp_out, int64_t r0, int jitter,
-                                  uint64_t seed, float ert_eps, float* rgb, float* depth, float* opac,
+hipError_t launch_composite_round(uint32_t nr, const IvSet& iv, bool uniform, const float* smp_out, int64_t r0,
+                                  int jitter, uint64_t seed, float ert_eps, float* rgb, float* depth, float* opac,
                                   float* weights, uint32_t* ray_used, ChunkCounts* counts, CompCarry* carry,
                                   uint32_t round, hipStream_t st) {
   if (nr == 0) return hipSuccess;
-  const uint32_t rays_per_block = kThreads / 64;
-  uint32_t grid = (nr + rays_per_block - 1) / rays_per_block;
-  hipLaunchKernelGGL(k_composite<true>, dim3(grid), dim3(kThreads), 0, st, nr, iv, smp_out, r0, jitter, seed,
-                     ert_eps, rgb, depth, opac, weights, ray_used, counts, carry, round);
+  const uint32_t rays = kThreads / 64 * kRays;
+  hipLaunchKernelGGL((uniform ? k_composite<true, true> : k_composite<true, false>), dim3((nr + rays - 1) / rays),
+                     dim3(kThreads), 0, st, nr, iv, smp_out, r0, jitter, seed, ert_eps, rgb, depth, opac, weights,
+                     ray_used, counts, carry, round);
   return hipGetLastError();
 }
 

@@ -182,15 +182,16 @@ hipError_t launch_act_max(int n_hidden, const float* master, uint32_t n_leaves, 
 
 // ---- compositing (Section 3.1 -> NeRF quadrature, early ray termination) ---------------
 // ray_used[r] receives the number of samples of ray r that were composited (the stop
-// sample included), and counts->composited their sum.
-hipError_t launch_composite(uint32_t nr, const IvSet& iv, const float* smp_out, int64_t r0,
+// sample included), and counts->composited their sum.  uniform: every interval of a ray has
+// the same number of samples.
+hipError_t launch_composite(uint32_t nr, const IvSet& iv, bool uniform, const float* smp_out, int64_t r0,
                             int jitter, uint64_t seed, float ert_eps, float* rgb, float* depth,
                             float* opac, float* weights, uint32_t* ray_used, ChunkCounts* counts,
                             hipStream_t st);
 // One 64-sample window (`round`) of every ray still marching, continuing from `carry`;
 // ray_used and the outputs are written as rays finish.  counts->composited is added by
 // launch_sum_used once every round has run.
-hipError_t launch_composite_round(uint32_t nr, const IvSet& iv, const float* smp_out, int64_t r0, int jitter,
+hipError_t launch_composite_round(uint32_t nr, const IvSet& iv, bool uniform, const float* smp_out, int64_t r0, int jitter,
                                   uint64_t seed, float ert_eps, float* rgb, float* depth, float* opac,
                                   float* weights, uint32_t* ray_used, ChunkCounts* counts, CompCarry* carry,
                                   uint32_t round, hipStream_t st);
