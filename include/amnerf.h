@@ -438,7 +438,8 @@ int amnerf_render_inspect(amnerf_ctx* ctx, const amnerf_inspect* out, void* stre
 #define AMNERF_STAGE_TRAVERSE 0   /* both traversal passes and the per-ray offset scans */
 #define AMNERF_STAGE_PROPOSAL 1   /* proposal inference, selection and planned intervals */
 #define AMNERF_STAGE_SORT 2       /* slot histogram, scans, stable scatter, bucket/tile offsets */
-#define AMNERF_STAGE_EXPAND 3     /* sorted interval -> per-sample records */
+#define AMNERF_STAGE_EXPAND 3     /* sorted interval -> per-sample records (jittered renders and
+                                     renders in rounds; the others' MLPs read the intervals) */
 #define AMNERF_STAGE_MLP 4        /* grouped per-leaf MLP */
 #define AMNERF_STAGE_COMPOSITE 5  /* front-to-back compositing */
 #define AMNERF_N_STAGES 6
@@ -453,7 +454,8 @@ int amnerf_ctx_set_timing(amnerf_ctx* ctx, int enable);
 int amnerf_timing_collect(amnerf_ctx* ctx, double* stage_ms_host, int64_t* n_passes);
 
 /* Backward stages, timed the same way (events on the backward's stream) when timing is on. */
-#define AMNERF_BWD_STAGE_COMPOSITE 0  /* loss gradient (training step) and compositing backward */
+#define AMNERF_BWD_STAGE_COMPOSITE 0  /* loss gradient (training step), per-sample records and
+                                         compositing backward */
 #define AMNERF_BWD_STAGE_MLP 1        /* per-leaf MLP backward: segment offsets and k_mlp_bwd */
 #define AMNERF_BWD_STAGE_REDUCE 2     /* reduction of the per-segment weight gradients */
 #define AMNERF_BWD_STAGE_ADAM 3       /* Adam and the repack of the bfloat16 weights (training step) */

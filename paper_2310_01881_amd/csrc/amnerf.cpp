@@ -126,6 +126,8 @@ struct amnerf_ctx {
   // planned by the proposal) and the sorted sample arrays
   IvSet use = {};
   uint32_t *bucket_off = nullptr, *perm = nullptr, *tile_off = nullptr, *srec_ray = nullptr;
+  uint32_t *sidx = nullptr, *ssb = nullptr;   // sorted intervals
+  bool expanded = false;          // the sample records (srec_ray, srec_t, perm) are written
   float *smp_out = nullptr, *srec_t = nullptr;
   uint32_t* ray_used = nullptr;   // samples composited per ray (the early-termination count)
   bool last_uses_arena3 = false;  // the last render's intervals live in the third arena
@@ -935,51 +937,65 @@ struct Carve {
 };
 
 struct Work {
-  uint64_t* chain;        // state words of the pass's chained scans
-  uint64_t chain_words;
-  uint32_t *iv_off, *smp_off, *scan_tmp;
+  uint64_t* chain;        // state words of the pass's chained scans: traversal, then the sort
+  uint64_t trav_words, chain_words;
+  uint32_t *iv_off, *smp_off;
   float *iv_t0, *iv_dt;
   uint32_t *iv_key, *iv_ray, *iv_base;
-  uint32_t *mat, *mat_scan, *sidx, *sn, *ssb, *bucket_off, *tile_off;
+  uint32_t *mat, *mat_smp, *sidx, *ssb, *bucket_off, *tile_off, *win;
+  SortRec* rec;           // sorted interval records, in the memory of the sample records
+  uint64_t rec_cap;
   uint32_t *srec_ray, *perm;
   float *srec_t, *smp_out;
   uint32_t* ray_used;
   // early termination in rounds: selection flags and their scan, compacted sample records,
   // the compacted buckets' offsets, and each ray's state between windows
-  uint32_t *r_flags, *r_pos, *r_tmp, *c_ray, *c_perm, *c_boff, *c_toff;
+  uint32_t *r_flags, *r_pos, *c_ray, *c_perm, *c_boff, *c_toff;
+  uint64_t* r_chain;
   float* c_t;
   CompCarry* carry;
 };
 
-size_t carve(char* base, uint64_t nr, uint64_t niv, uint64_t ns, const SortPlan& sp, Work& w, bool rounds) {
+// fused: the MLPs read the sorted intervals (their records lie where the sample records would,
+// 16 bytes for an interval where those take 12 for a sample).
+size_t carve(char* base, uint64_t nr, uint64_t niv, uint64_t ns, const SortPlan& sp, Work& w, bool rounds, bool fused) {
   Carve c{base};
-  uint64_t scan_n = std::max<uint64_t>({nr, niv, (uint64_t)sp.n_leaves * sp.nseg_max});
-  w.chain_words = trav_state_words(nr);
+  const uint64_t mat_n = (uint64_t)sp.n_leaves * sp.nseg_max;
+  w.trav_words = trav_state_words(nr);
+  w.chain_words = w.trav_words + scan_state_words(mat_n);
   w.chain = c.take<uint64_t>(w.chain_words);
   w.iv_off = c.take<uint32_t>(nr + 1);
   w.smp_off = c.take<uint32_t>(nr + 1);
-  w.scan_tmp = c.take<uint32_t>(scan_tmp_words(scan_n));
   w.iv_t0 = c.take<float>(niv);
   w.iv_dt = c.take<float>(niv);
   w.iv_key = c.take<uint32_t>(niv);
   w.iv_ray = c.take<uint32_t>(niv);
   w.iv_base = c.take<uint32_t>(niv);
-  w.mat = c.take<uint32_t>((uint64_t)sp.n_leaves * sp.nseg_max);
-  w.mat_scan = c.take<uint32_t>((uint64_t)sp.n_leaves * sp.nseg_max + 1);
+  w.mat = c.take<uint32_t>(mat_n + 1);
+  w.mat_smp = c.take<uint32_t>(mat_n + 1);
   w.sidx = c.take<uint32_t>(niv);
-  w.sn = c.take<uint32_t>(niv);
   w.ssb = c.take<uint32_t>(niv + 1);
   w.bucket_off = c.take<uint32_t>(sp.n_leaves + 1);
   w.tile_off = c.take<uint32_t>(sp.n_leaves + 1);
+  w.win = c.take<uint32_t>(fused ? 4 * (ns / kMlpTileRows + sp.n_leaves) : 0);
+  const size_t rec_at = (c.off + 255) / 256 * 256;
   w.srec_ray = c.take<uint32_t>(ns);
   w.srec_t = c.take<float>(ns);
   w.perm = c.take<uint32_t>(ns);
+  w.rec = nullptr;
+  w.rec_cap = 0;
+  if (fused) {
+    w.rec = reinterpret_cast<SortRec*>(w.srec_ray);
+    const uint64_t have = c.off - rec_at, want = niv * sizeof(SortRec);
+    if (want > have) c.off = rec_at + want;
+    w.rec_cap = (c.off - rec_at) / sizeof(SortRec);
+  }
   w.smp_out = c.take<float>(4 * ns);
   w.ray_used = c.take<uint32_t>(nr);
   const uint64_t nsr = rounds ? ns : 0, nrr = rounds ? nr : 0, lr = rounds ? sp.n_leaves + 1 : 0;
   w.r_flags = c.take<uint32_t>(nsr + 1);
   w.r_pos = c.take<uint32_t>(nsr + 1);
-  w.r_tmp = c.take<uint32_t>(rounds ? scan_tmp_words(ns) : 0);
+  w.r_chain = c.take<uint64_t>(rounds ? scan_state_words(ns) : 0);
   w.c_ray = c.take<uint32_t>(nsr);
   w.c_t = c.take<float>(nsr);
   w.c_perm = c.take<uint32_t>(nsr);
@@ -996,7 +1012,9 @@ struct PropWork {
   uint64_t* mask;
   float *pt0, *pdt;
   uint32_t *pkey, *pray, *pbase;
-  uint32_t *mat, *mat_scan, *sidx, *sn, *ssb, *scan_tmp;
+  uint32_t *mat, *mat_smp, *sidx, *ssb;
+  uint64_t* chain;        // state words: the planned offsets' scan, then the sort's
+  uint64_t off_words, chain_words;
 };
 
 size_t carve_prop(char* base, uint64_t nr, uint64_t niv_plain, uint64_t niv_plan, const SortPlan& sp, PropWork& w) {
@@ -1013,12 +1031,14 @@ size_t carve_prop(char* base, uint64_t nr, uint64_t niv_plain, uint64_t niv_plan
   w.pkey = c.take<uint32_t>(niv_plan);
   w.pray = c.take<uint32_t>(niv_plan);
   w.pbase = c.take<uint32_t>(niv_plan);
-  w.mat = c.take<uint32_t>((uint64_t)sp.n_leaves * sp.nseg_max);
-  w.mat_scan = c.take<uint32_t>((uint64_t)sp.n_leaves * sp.nseg_max + 1);
+  const uint64_t mat_n = (uint64_t)sp.n_leaves * sp.nseg_max;
+  w.mat = c.take<uint32_t>(mat_n + 1);
+  w.mat_smp = c.take<uint32_t>(mat_n + 1);
   w.sidx = c.take<uint32_t>(niv_plan);
-  w.sn = c.take<uint32_t>(niv_plan);
   w.ssb = c.take<uint32_t>(niv_plan + 1);
-  w.scan_tmp = c.take<uint32_t>(scan_tmp_words(std::max<uint64_t>({nr, niv_plan, (uint64_t)sp.n_leaves * sp.nseg_max})));
+  w.off_words = scan_state_words(nr);
+  w.chain_words = w.off_words + scan_state_words(mat_n);
+  w.chain = c.take<uint64_t>(w.chain_words);
   return c.off + 256;
 }
 
@@ -1039,9 +1059,13 @@ static int check_proposal(const amnerf_render_params* p) {
 // on demand.  Otherwise it is the static_bytes of static_ws (the allocation-free entry
 // point): the call must then fit one pass and that workspace, and runs no proposal or
 // empty-space selection (their buffers are sized on the host from a measured count).
+// keep_samples: a backward pass follows for certain, which reads the sample records, so the MLPs
+// may as well (a training step with its MLPs on the sorted intervals and the records written
+// afterwards took 1 % longer).
 static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_mlp* mlp,
                        const amnerf_rays* rays, const amnerf_render_params* p,
-                       amnerf_render_out* out, void* stream, char* static_ws, size_t static_bytes) {
+                       amnerf_render_out* out, void* stream, char* static_ws, size_t static_bytes,
+                       bool keep_samples) {
   if (!ctx || !tree || !mlp || !rays || !p || !out) return fail(AMNERF_EINVAL, "amnerf_render: null argument");
   MlpGeom g;
   int rc = check_geom(&mlp->shape, mlp->dtype, &g, "amnerf_render");
@@ -1091,12 +1115,26 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
   uint64_t chunk = std::max<uint64_t>(1, kChunkSamples / (uint64_t)p->s_max);
   if (R > 0 && (uint64_t)R < chunk) chunk = (uint64_t)R;
   const uint64_t niv_max = chunk * iv_per_ray, ns_max = chunk * (uint64_t)p->s_max;
-  SortPlan sp = make_sort_plan(niv_max, L);
   Work ws[kLanes];
   Work& w0 = ws[0];
   // early termination in rounds of 64-sample windows (a single window needs no rounds)
   const bool rounds = (p->flags & AMNERF_ERT_ROUNDS) && p->s_max > 64;
-  size_t need = carve(nullptr, chunk, niv_max, ns_max, sp, w0, rounds);
+  const int lanes_max = (uint64_t)R > chunk && !out->weights_dev && !static_ws ? ctx->render_lanes : 1;
+  // The MLPs read the sorted intervals, unless sample records are needed in any case (rounds
+  // compact them; jittered strata have no place in an interval's record) or the workspace is
+  // limited and only the layout with sample records fits it (the intervals' records may take
+  // 4 bytes per possible interval more).  Expanding first: 800x800 frame 2.60 against 2.35 ms,
+  // 64x64 87 against 54 us, 1920x1080 float8 7.95 against 7.21 ms (with the scans in one launch
+  // each).
+  bool fused = !rounds && !jitter && !keep_samples;
+  SortPlan sp = make_sort_plan(niv_max, L, fused);
+  size_t need = carve(nullptr, chunk, niv_max, ns_max, sp, w0, rounds, fused);
+  if (fused && ((static_ws && need > static_bytes) ||
+                (ctx->cap && need * (size_t)lanes_max + ctx->arena2_bytes + ctx->arena3_bytes > ctx->cap))) {
+    fused = false;
+    sp = make_sort_plan(niv_max, L, false);
+    need = carve(nullptr, chunk, niv_max, ns_max, sp, w0, rounds, false);
+  }
   if (static_ws) {
     if ((uint64_t)R > chunk)
       return fail(AMNERF_ECAPACITY, "amnerf_render_static: %lld rays exceed one pass (%llu at s_max %d)",
@@ -1104,11 +1142,11 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
     if (need > static_bytes)
       return fail(AMNERF_ECAPACITY, "amnerf_render_static: the call needs %zu bytes of workspace, the static "
                   "workspace holds %zu", need, static_bytes);
-    carve(static_ws, chunk, niv_max, ns_max, sp, w0, rounds);
+    carve(static_ws, chunk, niv_max, ns_max, sp, w0, rounds, fused);
   } else {
     rc = ensure_arena(ctx, need);
     if (rc) return rc;
-    carve((char*)ctx->arena, chunk, niv_max, ns_max, sp, w0, rounds);
+    carve((char*)ctx->arena, chunk, niv_max, ns_max, sp, w0, rounds, fused);
   }
   // More than one chunk (and no per-sample weights, whose offsets need the chunks in
   // order): chunk k runs on lane k mod n_lanes -- lanes beyond the caller's stream have their
@@ -1120,7 +1158,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
   for (int i = 1; i < n_lanes; ++i) {
     rc = lane_prepare(ctx, i, need);
     if (rc) return rc;
-    carve((char*)ctx->lanes[i - 1].arena, chunk, niv_max, ns_max, sp, ws[i], rounds);
+    carve((char*)ctx->lanes[i - 1].arena, chunk, niv_max, ns_max, sp, ws[i], rounds, fused);
   }
   if (R == 0) HIP_TRY(launch_pass_begin(ctx->counts, true, nullptr, 0, st));
   for (int i = 1; i < n_lanes; ++i) {
@@ -1132,7 +1170,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
   IvSet use = {};
   const uint64_t* sel_mask = nullptr;   // the last chunk's kept-slot mask, if it selected slots
   Work* wl = &w0;   // the last chunk's workspace
-  uint32_t *mat = w0.mat, *mat_scan = w0.mat_scan, *sidx = w0.sidx, *sn = w0.sn, *ssb = w0.ssb, *scan_tmp = w0.scan_tmp;
+  SortBufs sb = {};      // the last chunk's sort
   // A proposal or an occupancy grid sizes its buffers from the chunk's plain interval count,
   // which the host reads back.  The chunk loop is therefore split in two phases, and with
   // more than one lane chunk k's second phase is enqueued after chunk k + 1's first (which
@@ -1183,63 +1221,67 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
     const IvSet plain = {w.iv_off, w.smp_off, w.iv_t0, w.iv_dt, w.iv_key, w.iv_ray, w.iv_base, w.iv_off + nr};
     use = plain;
     SortPlan spu = sp;
-    mat = w.mat; mat_scan = w.mat_scan; sidx = w.sidx; sn = w.sn; ssb = w.ssb; scan_tmp = w.scan_tmp;
-    uint64_t niv_use_max = niv_max;
+    sb = {w.mat, w.mat_smp, w.sidx, w.ssb, w.rec, w.win, w.bucket_off, w.tile_off};
+    uint64_t* sort_chain = w.chain + w.trav_words;
     if (wait_count) HIP_TRY(hipStreamSynchronize(cs));   // the chunk's plain interval count has arrived
     if (p->proposal) {
       const uint32_t niv_plain = ctx->counts_host[li].n_iv;
       const amnerf_proposal* q = p->proposal;
       const uint64_t niv_plan = (uint64_t)niv_plain + (uint64_t)nr * (uint64_t)std::min(q->cap, p->s_max);
-      SortPlan spp = make_sort_plan(niv_plan, L);
+      SortPlan spp = make_sort_plan(niv_plan, L, fused);
       PropWork pw;
       rc = ensure_arena3_for(ctx, li, carve_prop(nullptr, nr, niv_plain, niv_plan, spp, pw));
       if (rc) return rc;
       carve_prop((char*)(li ? ctx->lanes[li - 1].arena3 : ctx->arena3), nr, niv_plain, niv_plan, spp, pw);
+      HIP_TRY(launch_pass_begin(nullptr, false, pw.chain, pw.chain_words, cs));
       HIP_TRY(launch_prop_fwd(q->dtype, q->packed_dev, plain, rays->o_dev, rays->d_dev, R, r0, tree->dev_leafbox,
                               p->s_max, niv_plain, true, pw.wts, pw.tot, cs));
       HIP_TRY(launch_prop_select(nr, plain, pw.wts, pw.tot, q->mass_thresh, q->cap, p->s_max, pw.runs, pw.nsel, pw.mask, nullptr,
                                  cc, cs));
-      HIP_TRY(launch_scan_u32_pair(pw.runs, pw.pv_off, pw.nsel, pw.ps_off, nr, pw.scan_tmp, cs));
+      HIP_TRY(launch_scan_u32_pair(pw.runs, pw.pv_off, pw.nsel, pw.ps_off, nr, pw.chain, cs));
       HIP_TRY(launch_prop_emit(nr, plain, pw.mask, pw.pv_off, pw.ps_off, pw.pt0, pw.pdt, pw.pkey, pw.pray, pw.pbase, cs));
       use = {pw.pv_off, pw.ps_off, pw.pt0, pw.pdt, pw.pkey, pw.pray, pw.pbase, pw.pv_off + nr};
       sel_mask = pw.mask;
       spu = spp;
-      mat = pw.mat; mat_scan = pw.mat_scan; sidx = pw.sidx; sn = pw.sn; ssb = pw.ssb; scan_tmp = pw.scan_tmp;
-      niv_use_max = niv_plan;
+      sb = {pw.mat, pw.mat_smp, pw.sidx, pw.ssb, niv_plan <= w.rec_cap ? w.rec : nullptr, w.win, w.bucket_off,
+            w.tile_off};
+      sort_chain = pw.chain + pw.off_words;
     } else if (occ) {
       // empty-space skipping: the kept samples of each ray as runs of consecutive slots
       // (within an interval of n slots at most ceil(n/2) runs, so a ray has at most
       // (s_max + m) / 2 of them); buffers sized from the plain interval count
       const uint64_t niv_plain = ctx->counts_host[li].n_iv;
       const uint64_t niv_plan = (niv_plain + (uint64_t)nr * (uint64_t)p->s_max) / 2 + nr;
-      SortPlan spp = make_sort_plan(niv_plan, L);
+      SortPlan spp = make_sort_plan(niv_plan, L, fused);
       PropWork pw;
       rc = ensure_arena3_for(ctx, li, carve_prop(nullptr, nr, 1, niv_plan, spp, pw));
       if (rc) return rc;
       carve_prop((char*)(li ? ctx->lanes[li - 1].arena3 : ctx->arena3), nr, 1, niv_plan, spp, pw);
+      HIP_TRY(launch_pass_begin(nullptr, false, pw.chain, pw.chain_words, cs));
       HIP_TRY(launch_occ_select(nr, plain, rays->o_dev, rays->d_dev, R, r0, occ->dev_bits, occ->g, pw.runs, pw.nsel,
                                 pw.mask, cs));
-      HIP_TRY(launch_scan_u32_pair(pw.runs, pw.pv_off, pw.nsel, pw.ps_off, nr, pw.scan_tmp, cs));
+      HIP_TRY(launch_scan_u32_pair(pw.runs, pw.pv_off, pw.nsel, pw.ps_off, nr, pw.chain, cs));
       HIP_TRY(launch_prop_emit(nr, plain, pw.mask, pw.pv_off, pw.ps_off, pw.pt0, pw.pdt, pw.pkey, pw.pray, pw.pbase, cs));
       use = {pw.pv_off, pw.ps_off, pw.pt0, pw.pdt, pw.pkey, pw.pray, pw.pbase, pw.pv_off + nr};
       sel_mask = pw.mask;
       spu = spp;
-      mat = pw.mat; mat_scan = pw.mat_scan; sidx = pw.sidx; sn = pw.sn; ssb = pw.ssb; scan_tmp = pw.scan_tmp;
-      niv_use_max = niv_plan;
+      sb = {pw.mat, pw.mat_smp, pw.sidx, pw.ssb, niv_plan <= w.rec_cap ? w.rec : nullptr, w.win, w.bucket_off,
+            w.tile_off};
+      sort_chain = pw.chain + pw.off_words;
     }
-    HIP_TRY(launch_chunk_begin(cc, use.n_iv_dev, spu.seg, L, cs));
     HIP_TRY(mark(2));
-    HIP_TRY(launch_sort_hist(spu, use.key, use.n_iv_dev, mat, cs));
-    HIP_TRY(launch_scan_u32(mat, mat_scan, (uint64_t)L * spu.nseg_max, &cc->mat_n, scan_tmp, cs));
-    HIP_TRY(launch_sort_scatter(spu, use.key, use.n_iv_dev, mat_scan, sidx, sn, cs));
-    HIP_TRY(launch_scan_u32(sn, ssb, niv_use_max, use.n_iv_dev, scan_tmp, cs));
-    HIP_TRY(launch_bucket_tiles(spu, mat_scan, ssb, w.bucket_off, w.tile_off, cc, cs));
+    HIP_TRY(launch_sort_hist(spu, use.key, use.n_iv_dev, sb.mat, cs));
+    HIP_TRY(launch_scan_packed(sb.mat, sb.mat_smp, (uint64_t)L * spu.nseg_max, use.n_iv_dev, L, spu.seg, sort_chain, cs));
+    HIP_TRY(launch_bucket_tiles(spu, sb, use.n_iv_dev, cc, cs));
+    HIP_TRY(launch_sort_scatter(spu, sb, use, cs));
     HIP_TRY(mark(3));
-    HIP_TRY(launch_expand(sidx, ssb, use, r0, jitter, p->jitter_seed, w.srec_ray, w.srec_t, w.perm, cs));
+    if (!sb.rec)
+      HIP_TRY(launch_expand(sb.sidx, sb.ssb, use, r0, jitter, p->jitter_seed, w.srec_ray, w.srec_t, w.perm, cs));
     HIP_TRY(mark(4));
     if (!rounds) {
-      HIP_TRY(launch_mlp(g, mlp->packed_dev, L, w.bucket_off, w.tile_off, cc, w.srec_ray, w.srec_t, w.perm,
-                         rays->o_dev, rays->d_dev, R, r0, w.smp_out, cs));
+      const RowSource rows = {sb.rec, sb.ssb, sb.win, w.srec_ray, w.srec_t, w.perm};
+      HIP_TRY(launch_mlp(g, mlp->packed_dev, L, w.bucket_off, w.tile_off, cc, rows, rays->o_dev, rays->d_dev, R, r0,
+                         w.smp_out, cs));
       HIP_TRY(mark(5));
       HIP_TRY(launch_composite(nr, use, !wait_count, w.smp_out, r0, jitter, p->jitter_seed, p->ert_eps, out->rgb_dev,
                                out->depth_dev, out->opacity_dev, out->weights_dev, w.ray_used, cc, cs));
@@ -1250,12 +1292,14 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
       const uint32_t n_rounds = (uint32_t)(p->s_max + 63) / 64;
       for (uint32_t k = 0; k < n_rounds; ++k) {
         HIP_TRY(launch_round_flags(w.perm, w.srec_ray, use.smp_off, w.carry, cc, k, (uint32_t)ns_max, w.r_flags, cs));
-        HIP_TRY(launch_scan_u32(w.r_flags, w.r_pos, ns_max, &cc->n_smp, w.r_tmp, cs));
+        HIP_TRY(launch_pass_begin(nullptr, false, w.r_chain, scan_state_words(ns_max), cs));
+        HIP_TRY(launch_scan_u32(w.r_flags, w.r_pos, ns_max, &cc->n_smp, w.r_chain, cs));
         HIP_TRY(launch_round_compact(w.r_flags, w.r_pos, w.srec_ray, w.srec_t, w.perm, cc, (uint32_t)ns_max, w.c_ray,
                                      w.c_t, w.c_perm, cs));
         HIP_TRY(launch_round_tiles(w.bucket_off, w.r_pos, L, w.c_boff, w.c_toff, cc, cs));
-        HIP_TRY(launch_mlp(g, mlp->packed_dev, L, w.c_boff, w.c_toff, cc, w.c_ray, w.c_t, w.c_perm, rays->o_dev,
-                           rays->d_dev, R, r0, w.smp_out, cs));
+        const RowSource rows = {nullptr, nullptr, nullptr, w.c_ray, w.c_t, w.c_perm};
+        HIP_TRY(launch_mlp(g, mlp->packed_dev, L, w.c_boff, w.c_toff, cc, rows, rays->o_dev, rays->d_dev, R, r0, w.smp_out,
+                           cs));
         if (k + 1 == n_rounds) HIP_TRY(mark(5));
         HIP_TRY(launch_composite_round(nr, use, !wait_count, w.smp_out, r0, jitter, p->jitter_seed, p->ert_eps, out->rgb_dev,
                                        out->depth_dev, out->opacity_dev, out->weights_dev, w.ray_used, cc, w.carry,
@@ -1311,6 +1355,9 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
   ctx->tile_off = wl->tile_off;
   ctx->srec_ray = wl->srec_ray;
   ctx->srec_t = wl->srec_t;
+  ctx->sidx = sb.sidx;
+  ctx->ssb = sb.ssb;
+  ctx->expanded = sb.rec == nullptr;
   ctx->ray_used = wl->ray_used;
   ctx->last_uses_arena3 = p->proposal != nullptr || occ != nullptr;
   ctx->last_tree = tree;
@@ -1329,7 +1376,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
 extern "C" int amnerf_render(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_mlp* mlp,
                              const amnerf_rays* rays, const amnerf_render_params* p,
                              amnerf_render_out* out, void* stream) {
-  return render_impl(ctx, tree, mlp, rays, p, out, stream, nullptr, 0);
+  return render_impl(ctx, tree, mlp, rays, p, out, stream, nullptr, 0, false);
 }
 
 extern "C" int amnerf_render_static(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_mlp* mlp,
@@ -1341,7 +1388,7 @@ extern "C" int amnerf_render_static(amnerf_ctx* ctx, const amnerf_tree* tree, co
                 "(use amnerf_render)");
   char* ws = (char*)static_workspace(ctx->device);
   if (!ws) return fail(AMNERF_ESTATE, "amnerf_render_static: no static workspace on device %d", ctx->device);
-  return render_impl(ctx, tree, mlp, rays, p, out, stream, ws, kStaticBytes);
+  return render_impl(ctx, tree, mlp, rays, p, out, stream, ws, kStaticBytes, false);
 }
 
 extern "C" size_t amnerf_render_static_capacity(void) { return kStaticBytes; }
@@ -1373,6 +1420,18 @@ extern "C" int amnerf_render_stats_get(amnerf_ctx* ctx, amnerf_render_stats* out
   return AMNERF_OK;
 }
 
+// The last render's sample records, for what reads them after it (the backward pass,
+// calibration, inspection): a render whose MLPs read the sorted intervals has not written them,
+// and their memory still holds the intervals' records, which nothing needs any more.
+static int ensure_expanded(amnerf_ctx* ctx, hipStream_t st) {
+  if (ctx->expanded) return AMNERF_OK;
+  const int jitter = (ctx->last_params.flags & AMNERF_JITTER) ? 1 : 0;
+  HIP_TRY(launch_expand(ctx->sidx, ctx->ssb, ctx->use, 0, jitter, ctx->last_params.jitter_seed, ctx->srec_ray,
+                        ctx->srec_t, ctx->perm, st));
+  ctx->expanded = true;
+  return AMNERF_OK;
+}
+
 extern "C" int amnerf_render_inspect(amnerf_ctx* ctx, const amnerf_inspect* o, void* stream) {
   if (!ctx || !o) return fail(AMNERF_EINVAL, "amnerf_render_inspect: null argument");
   if (!ctx->have_render) return fail(AMNERF_ESTATE, "amnerf_render_inspect: no render yet");
@@ -1389,6 +1448,10 @@ extern "C" int amnerf_render_inspect(amnerf_ctx* ctx, const amnerf_inspect* o, v
     return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, st);
   };
   const IvSet& u = ctx->use;
+  if (o->perm) {
+    rc = ensure_expanded(ctx, st);
+    if (rc) return rc;
+  }
   HIP_TRY(cp(o->ray_iv_off, u.iv_off, 4 * (nr + 1)));
   HIP_TRY(cp(o->ray_smp_off, u.smp_off, 4 * (nr + 1)));
   HIP_TRY(cp(o->iv_t0, u.t0, 4 * niv));
@@ -1491,6 +1554,8 @@ int backward_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_mlp* ml
   }
   auto mark = [&](int k) -> hipError_t { return ev ? hipEventRecord(ev->ev[k], st) : hipSuccess; };
   if (alone) HIP_TRY(mark(AMNERF_BWD_STAGE_COMPOSITE));
+  rc = ensure_expanded(ctx, st);   // (counted with the compositing stage)
+  if (rc) return rc;
   HIP_TRY(launch_comp_bwd(nr, ctx->use, ctx->smp_out, 0, jitter, p.jitter_seed, ctx->ray_used, g_rgb, g_depth,
                           g_opac, w.gpre, st));
   HIP_TRY(mark(AMNERF_BWD_STAGE_MLP));
@@ -1535,6 +1600,8 @@ extern "C" int amnerf_mlp_calibrate(amnerf_ctx* ctx, const amnerf_mlp_shape* s, 
     return fail(AMNERF_EINVAL, "amnerf_mlp_calibrate: %d parameter sets, the last render used %u", n_leaves,
                 ctx->last_leaves);
   HIP_TRY(hipSetDevice(ctx->device));
+  rc = ensure_expanded(ctx, (hipStream_t)stream);
+  if (rc) return rc;
   HIP_TRY(launch_act_max(s->n_hidden, master, (uint32_t)n_leaves, ctx->bucket_off, ctx->tile_off, ctx->counts,
                          ctx->srec_ray, ctx->srec_t, rays->o_dev, rays->d_dev, rays->n_rays, 0, act_max,
                          (hipStream_t)stream));
@@ -1611,7 +1678,7 @@ extern "C" int amnerf_train_step(amnerf_ctx* ctx, const amnerf_tree* tree, amner
     carve_bwd((char*)ctx->arena2, ns, L, nseg, P, R, w);
   }
   amnerf_render_out out = {w.rgb, nullptr, nullptr, nullptr};
-  int rc = amnerf_render(ctx, tree, &mlp, rays, &p->render, &out, stream);
+  int rc = render_impl(ctx, tree, &mlp, rays, &p->render, &out, stream, nullptr, 0, true);
   if (rc) return rc;
   BwdEvSet* ev = nullptr;
   if (ctx->timing) {

@@ -289,13 +289,6 @@ __global__ void k_chunk_finish(ChunkCounts* counts, const uint32_t* smp_total, c
   counts->plain_smp += *plain_total;
 }
 
-__global__ void k_chunk_begin(ChunkCounts* counts, const uint32_t* iv_total, uint32_t seg, uint32_t n_leaves) {
-  if (threadIdx.x != 0) return;
-  const uint32_t n = *iv_total;
-  counts->n_iv = n;
-  counts->mat_n = n_leaves * ((n + seg - 1) / seg);
-}
-
 // Adds the second lane's running totals into the first lane's counters.
 __global__ void k_counts_merge(ChunkCounts* a, const ChunkCounts* b) {
   if (threadIdx.x != 0) return;
@@ -368,12 +361,6 @@ hipError_t launch_counts_merge(ChunkCounts* a, const ChunkCounts* b, hipStream_t
 hipError_t launch_pass_begin(ChunkCounts* counts, bool reset, uint64_t* state, uint64_t words, hipStream_t st) {
   const uint64_t blocks = std::min<uint64_t>(256u, words / (4 * kThreads) + 1);
   hipLaunchKernelGGL(k_pass_begin, dim3((uint32_t)blocks), dim3(kThreads), 0, st, counts, reset ? 1 : 0, state, words);
-  return hipGetLastError();
-}
-
-hipError_t launch_chunk_begin(ChunkCounts* counts, const uint32_t* iv_total, uint32_t seg, uint32_t n_leaves,
-                              hipStream_t st) {
-  hipLaunchKernelGGL(k_chunk_begin, dim3(1), dim3(64), 0, st, counts, iv_total, seg, n_leaves);
   return hipGetLastError();
 }
 

@@ -28,7 +28,7 @@ struct ChunkCounts {
   uint32_t n_iv;        // intervals that carry samples (this chunk)
   uint32_t n_smp;       // samples (this chunk)
   uint32_t n_tiles;     // MLP work tiles (this chunk)
-  uint32_t mat_n;       // entries of the sort's slot x segment count matrix (this chunk)
+  uint32_t pad;
   uint64_t smp_global;  // ray-major sample index of this chunk's first sample
   uint64_t iv_global;   // intervals of the chunks before this one
   uint64_t nonfinite;   // rays with a non-finite output (accumulated over chunks)
@@ -89,40 +89,69 @@ __device__ __forceinline__ uint32_t find_interval(const uint32_t* __restrict__ b
 }
 
 // ---- scans -----------------------------------------------------------------------------
-// Exclusive prefix sum of n uint32 values (n given on the host, or read from n_dev when
-// n_dev != nullptr, capped at n_cap); out[n] receives the total.  tmp needs
-// scan_tmp_words(n_cap) words.
-size_t scan_tmp_words(uint64_t n_cap);
+// Exclusive prefix sums in one launch.  n uint32 values (n given on the host, or read from
+// n_dev when n_dev != nullptr, capped at n_cap); out[n] receives the total.  state:
+// scan_state_words(n_cap) zeroed words.  Totals stay below 2^31.
+uint64_t scan_state_words(uint64_t n_cap);
 hipError_t launch_scan_u32(const uint32_t* in, uint32_t* out, uint64_t n_cap,
-                           const uint32_t* n_dev, uint32_t* tmp, hipStream_t st);
-// Exclusive scans of two uint32 arrays of the same length n_cap at once (out_x[n_cap] = the
-// totals), each total below 2^32; tmp as above, 8-byte aligned.
+                           const uint32_t* n_dev, uint64_t* state, hipStream_t st);
+// Two uint32 arrays of the same length n_cap at once.
 hipError_t launch_scan_u32_pair(const uint32_t* in_a, uint32_t* out_a, const uint32_t* in_b, uint32_t* out_b,
-                                uint64_t n_cap, uint32_t* tmp, hipStream_t st);
+                                uint64_t n_cap, uint64_t* state, hipStream_t st);
+// n = mul * ceil(*n_dev / div) words of count << 20 | samples: the counts' prefix sums replace
+// them, the samples' go to out_smp (both arrays hold n + 1 words).
+hipError_t launch_scan_packed(uint32_t* mat, uint32_t* out_smp, uint64_t n_cap, const uint32_t* n_dev, uint32_t mul,
+                              uint32_t div, uint64_t* state, hipStream_t st);
 
 // ---- sort by leaf slot (Section 3.5: sort, then infer per node) ------------------------
 struct SortPlan {
-  uint32_t seg;         // intervals per segment (multiple of 64)
+  uint32_t seg;         // intervals per segment (multiple of 64, below 4096)
   uint32_t nseg_max;    // segments for the worst-case interval count (the kernels use the
                         // actual count, ceil(n_iv / seg), as the matrix's row length)
   uint32_t key_bits;    // bits of the leaf slot
   uint32_t n_leaves;
 };
-SortPlan make_sort_plan(uint64_t n_iv_max, uint32_t n_leaves);
+// One sorted interval: its start, its samples' step, its (chunk-local) ray and the ray-major
+// index of its first sample.
+struct SortRec {
+  float t0, delta;
+  uint32_t ray, base;
+};
+// The sort's arrays.  mat: n_leaves * nseg_max + 1 words, the packed counts and then their
+// prefix sums; mat_smp the samples' prefix sums.  Per sorted interval: sidx its index, ssb its
+// first sorted sample (ssb[n_iv] the total), rec its record (centred strata).  win[4 t + w]: the
+// sorted interval of the first row of window w (64 rows) of tile t.  rec null: only sidx and
+// ssb are made.
+struct SortBufs {
+  uint32_t *mat, *mat_smp, *sidx, *ssb;
+  SortRec* rec;
+  uint32_t* win;
+  uint32_t *bucket_off, *tile_off;
+};
+// small: shorter segments (a larger matrix) for few intervals.
+SortPlan make_sort_plan(uint64_t n_iv_max, uint32_t n_leaves, bool small);
 hipError_t launch_sort_hist(const SortPlan& p, const uint32_t* iv_key, const uint32_t* n_iv_dev,
                             uint32_t* mat, hipStream_t st);
-hipError_t launch_sort_scatter(const SortPlan& p, const uint32_t* iv_key, const uint32_t* n_iv_dev,
-                               const uint32_t* mat_scan, uint32_t* sidx, uint32_t* sn,
-                               hipStream_t st);
 // bucket_off[b] = first sorted sample of leaf b; tile_off[b] = first MLP tile of leaf b;
-// also fills counts->n_smp and counts->n_tiles.
-hipError_t launch_bucket_tiles(const SortPlan& p, const uint32_t* mat_scan, const uint32_t* ssb,
-                               uint32_t* bucket_off, uint32_t* tile_off, ChunkCounts* counts,
+// also fills ssb's total and counts->n_iv, n_smp and n_tiles.
+hipError_t launch_bucket_tiles(const SortPlan& p, const SortBufs& b, const uint32_t* n_iv_dev, ChunkCounts* counts,
                                hipStream_t st);
+hipError_t launch_sort_scatter(const SortPlan& p, const SortBufs& b, const IvSet& iv, hipStream_t st);
 // One record per sorted sample: ray (chunk-local), t, ray-major sample index.
 hipError_t launch_expand(const uint32_t* sidx, const uint32_t* ssb, const IvSet& iv,
                          int64_t r0, int jitter, uint64_t seed, uint32_t* srec_ray,
                          float* srec_t, uint32_t* perm, hipStream_t st);
+
+// Where the leaf MLPs read their rows from: the sorted intervals (rec not null), or sample
+// records.
+struct RowSource {
+  const SortRec* rec;
+  const uint32_t* ssb;
+  const uint32_t* win;
+  const uint32_t* ray;
+  const float* t;
+  const uint32_t* perm;
+};
 
 // ---- grouped per-leaf MLP ---------------------------------------------------------------
 struct MlpGeom {
@@ -150,17 +179,15 @@ hipError_t launch_mlp_pack(const MlpGeom& g, int n_leaves, const float* master, 
                            hipStream_t st);
 hipError_t launch_mlp(const MlpGeom& g, const void* packed, uint32_t n_leaves,
                       const uint32_t* bucket_off, const uint32_t* tile_off,
-                      const ChunkCounts* counts, const uint32_t* srec_ray, const float* srec_t,
-                      const uint32_t* perm, const float* o, const float* d, int64_t ray_stride,
-                      int64_t r0, float* out, hipStream_t st);
+                      const ChunkCounts* counts, const RowSource& rows, const float* o, const float* d,
+                      int64_t ray_stride, int64_t r0, float* out, hipStream_t st);
 
 // ---- float32 leaf MLPs on the bfloat16 matrix cores (values split in three) ----------------
 // Whether the split weights of a leaf fit a compute unit's LDS (n_hidden <= 7 at hidden 64).
 bool mlp32_fits(int n_hidden, int hidden);
 hipError_t launch_mlp32(int n_hidden, int hidden, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
-                        const uint32_t* tile_off, const ChunkCounts* counts, const uint32_t* srec_ray,
-                        const float* srec_t, const uint32_t* perm, const float* o, const float* d, int64_t stride,
-                        int64_t r0, float* out, hipStream_t st);
+                        const uint32_t* tile_off, const ChunkCounts* counts, const RowSource& rows, const float* o,
+                        const float* d, int64_t stride, int64_t r0, float* out, hipStream_t st);
 
 // ---- float8 weights and activations on the float8 matrix cores (hidden width 64,
 // n_hidden 1..4) ----------------------------------------------------------------------------
@@ -170,9 +197,8 @@ size_t mlp8_block_bytes(int n_hidden);
 hipError_t launch_mlp8_pack(int n_hidden, int n_leaves, const float* master, const float* act_max, void* packed,
                             hipStream_t st);
 hipError_t launch_mlp8(int n_hidden, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
-                       const uint32_t* tile_off, const ChunkCounts* counts, const uint32_t* srec_ray,
-                       const float* srec_t, const uint32_t* perm, const float* o, const float* d, int64_t stride,
-                       int64_t r0, float* out, hipStream_t st);
+                       const uint32_t* tile_off, const ChunkCounts* counts, const RowSource& rows, const float* o,
+                       const float* d, int64_t stride, int64_t r0, float* out, hipStream_t st);
 // Raises act_max[leaf][j] to the largest ReLU output of hidden layer j over the sorted
 // samples (float32 forward of the master parameters).
 hipError_t launch_act_max(int n_hidden, const float* master, uint32_t n_leaves, const uint32_t* bucket_off,
@@ -264,8 +290,6 @@ hipError_t launch_prop_train(const void* packed, const IvSet& iv, const float* o
 hipError_t launch_counts_merge(ChunkCounts* a, const ChunkCounts* b, hipStream_t st);
 // Start of a pass: zeroes the chained scans' state words, and the counters when `reset`.
 hipError_t launch_pass_begin(ChunkCounts* counts, bool reset, uint64_t* state, uint64_t words, hipStream_t st);
-hipError_t launch_chunk_begin(ChunkCounts* counts, const uint32_t* iv_total, uint32_t seg, uint32_t n_leaves,
-                              hipStream_t st);
 hipError_t launch_chunk_finish(ChunkCounts* counts, const uint32_t* smp_off_total,
                                const uint32_t* iv_off_total, const uint32_t* plain_smp_total, int rounds,
                                hipStream_t st);

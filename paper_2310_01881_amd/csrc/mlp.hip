@@ -25,6 +25,7 @@
 #include "internal.hpp"
 #include "devcommon.hpp"
 #include "mlp_layout.hpp"
+#include "rows.hpp"
 
 #include "../../include/amnerf.h"
 
@@ -262,19 +263,18 @@ __device__ __forceinline__ void stage_leaf(const Layout& L, const uint8_t* __res
   }
 }
 
-template <int H, bool BF16, bool FP8 = false>
+template <int H, bool BF16, bool FP8, bool FUSED>
 __global__ __launch_bounds__(kThreads, BF16 ? 4 : 2) void k_mlp(
     Layout L, const uint8_t* __restrict__ packed, uint32_t n_leaves,
     const uint32_t* __restrict__ bucket_off, const uint32_t* __restrict__ tile_off,
-    const ChunkCounts* __restrict__ counts, const uint32_t* __restrict__ srec_ray,
-    const float* __restrict__ srec_t, const uint32_t* __restrict__ perm,
+    const ChunkCounts* __restrict__ counts, RowSource rows,
     const float* __restrict__ o, const float* __restrict__ d, int64_t stride, int64_t r0,
     float* __restrict__ out) {
   extern __shared__ __align__(16) uint8_t lds[];
   constexpr int RB = H / 16;
   constexpr int NCB = 4;                       // column blocks per wave
   constexpr int KUh = BF16 ? H / 32 : H / 16;  // K units of a hidden-width input
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, m = lane & 15;
   const float* bias = reinterpret_cast<const float*>(lds);
   const uint8_t* units = lds + L.bias_bytes;
@@ -291,34 +291,15 @@ __global__ __launch_bounds__(kThreads, BF16 ? 4 : 2) void k_mlp(
   }
   uint32_t b = lo;
   int cur = -1;
-  // Inputs of the wave's 64 rows of the next tile, one row per lane: the sample record is
-  // loaded a tile ahead and the ray's origin and direction are gathered during the current
-  // tile's first layer, so neither load is waited for at the start of a tile.
-  uint32_t qb = lo, q_row0 = 0, q_end = 0;
-  uint32_t n_ray = 0, n_perm = 0;
-  float n_t = 0.f, n_o[3] = {0.f, 0.f, 0.f}, n_d[3] = {0.f, 0.f, 0.f};
-  auto next_rows = [&](uint32_t tt) {
-    while (tile_off[qb + 1] <= tt) ++qb;
-    q_row0 = bucket_off[qb] + (tt - tile_off[qb]) * kMlpTileRows + wave * 64;
-    q_end = bucket_off[qb + 1];
-    const uint32_t row = q_row0 + lane;
-    n_ray = 0u; n_perm = 0u; n_t = 0.f;
-    if (row < q_end) {
-      n_ray = srec_ray[row];
-      n_t = srec_t[row];
-      n_perm = perm[row];
-    }
-  };
-  auto gather = [&]() {
-    const int64_t ri = r0 + n_ray;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      n_o[a] = o[a * stride + ri];
-      n_d[a] = d[a * stride + ri];
-    }
-  };
-  next_rows(tb);
-  gather();
+  // The wave's 64 rows of the next tile, one per lane, are found and loaded during the current
+  // tile, so that no read is waited for at the start of a tile.
+  uint8_t* mark = lds + L.bytes + wave * 64;
+  const uint32_t n_iv = counts->n_iv;
+  RowFetch<FUSED, 64> q;
+  q.init(lo, wave);
+  q.locate(rows, bucket_off, tile_off, tb, wave, lane, n_iv);
+  q.fetch(rows, mark, o, d, stride, r0, lane);
+  q.gather(o, d, stride, r0);
   for (uint32_t t = tb; t < te; ++t) {
     while (tile_off[b + 1] <= t) ++b;
     if ((int)b != cur) {
@@ -327,19 +308,22 @@ __global__ __launch_bounds__(kThreads, BF16 ? 4 : 2) void k_mlp(
       __syncthreads();
       cur = (int)b;
     }
-    const uint32_t row0 = q_row0, row_end = q_end;
-    const uint32_t c_perm = n_perm;
+    const uint32_t row0 = q.row0, row_end = q.end;
+    const uint32_t c_perm = q.perm;
     // this lane's row: sample position mapped to [-1, 1]^3, and the direction
     float c_p[3], c_d[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      c_d[a] = n_d[a];
-      c_p[a] = 2.f * fmaf(n_t, n_d[a], n_o[a]) - 1.f;
+      c_d[a] = q.d[a];
+      c_p[a] = 2.f * fmaf(q.t, q.d[a], q.o[a]) - 1.f;
     }
     const bool more = t + 1 < te;
-    if (more) next_rows(t + 1);
+    if (more) q.locate(rows, bucket_off, tile_off, t + 1, wave, lane, n_iv);
     if (row0 >= row_end) {
-      if (more) gather();
+      if (more) {
+        q.fetch(rows, mark, o, d, stride, r0, lane);
+        q.gather(o, d, stride, r0);
+      }
       continue;
     }
 
@@ -406,13 +390,16 @@ __global__ __launch_bounds__(kThreads, BF16 ? 4 : 2) void k_mlp(
       uint32_t Ha[NCB][KUh][4], Hb[NCB][KUh][4];
       bf16_layer<H, NCB, 1>(L, units, bias, 0, lane, g, X0u, Ha);
       __builtin_amdgcn_sched_barrier(0);
-      if (more) gather();
+      if (more) q.fetch(rows, mark, o, d, stride, r0, lane);
       __builtin_amdgcn_sched_barrier(0);
       int layer = 1;
       for (; layer + 1 < L.nh; layer += 2) {
         bf16_layer<H, NCB, KUh>(L, units, bias, layer, lane, g, Ha, Hb);
         bf16_layer<H, NCB, KUh>(L, units, bias, layer + 1, lane, g, Hb, Ha);
       }
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) q.gather(o, d, stride, r0);
+      __builtin_amdgcn_sched_barrier(0);
       f32x4 res[NCB];
       if (layer < L.nh) {
         bf16_layer<H, NCB, KUh>(L, units, bias, layer, lane, g, Ha, Hb);
@@ -441,7 +428,10 @@ __global__ __launch_bounds__(kThreads, BF16 ? 4 : 2) void k_mlp(
     }
 
     __builtin_amdgcn_sched_barrier(0);
-    if (more) gather();
+    if (more) {
+      q.fetch(rows, mark, o, d, stride, r0, lane);
+      q.gather(o, d, stride, r0);
+    }
     __builtin_amdgcn_sched_barrier(0);
     // ---- hidden layers H -> H, then the output layer H -> 4 (padded to 16) ----
     for (int layer = 1; layer <= L.nh; ++layer) {
@@ -488,18 +478,28 @@ __global__ __launch_bounds__(kThreads, BF16 ? 4 : 2) void k_mlp(
   }
 }
 
+template <int H, bool BF16, bool FP8, bool FUSED>
+hipError_t launch_rows(const Layout& L, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
+                       const uint32_t* tile_off, const ChunkCounts* counts, const RowSource& rows, const float* o,
+                       const float* d, int64_t stride, int64_t r0, float* out, hipStream_t st) {
+  auto kern = k_mlp<H, BF16, FP8, FUSED>;
+  const uint32_t lds = L.bytes + (FUSED ? kThreads / 64 * 64u : 0u);   // + the waves' row marks
+  int grid = 0;
+  hipError_t e = persistent_grid((const void*)kern, kThreads, lds, &grid);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, L, (const uint8_t*)packed, n_leaves,
+                     bucket_off, tile_off, counts, rows, o, d, stride, r0, out);
+  return hipGetLastError();
+}
+
 template <int H, bool BF16, bool FP8 = false>
 hipError_t launch_typed(const Layout& L, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
-                        const uint32_t* tile_off, const ChunkCounts* counts, const uint32_t* srec_ray,
-                        const float* srec_t, const uint32_t* perm, const float* o, const float* d,
-                        int64_t stride, int64_t r0, float* out, hipStream_t st) {
-  auto kern = k_mlp<H, BF16, FP8>;
-  int grid = 0;
-  hipError_t e = persistent_grid((const void*)kern, kThreads, L.bytes, &grid);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), L.bytes, st, L, (const uint8_t*)packed, n_leaves,
-                     bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, stride, r0, out);
-  return hipGetLastError();
+                        const uint32_t* tile_off, const ChunkCounts* counts, const RowSource& rows, const float* o,
+                        const float* d, int64_t stride, int64_t r0, float* out, hipStream_t st) {
+  return rows.rec ? launch_rows<H, BF16, FP8, true>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, stride,
+                                                    r0, out, st)
+                  : launch_rows<H, BF16, FP8, false>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, stride,
+                                                     r0, out, st);
 }
 
 }  // namespace
@@ -586,27 +586,24 @@ hipError_t launch_mlp_pack(const MlpGeom& g, int n_leaves, const float* master, 
 }
 
 hipError_t launch_mlp(const MlpGeom& g, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
-                      const uint32_t* tile_off, const ChunkCounts* counts, const uint32_t* srec_ray,
-                      const float* srec_t, const uint32_t* perm, const float* o, const float* d,
-                      int64_t ray_stride, int64_t r0, float* out, hipStream_t st) {
+                      const uint32_t* tile_off, const ChunkCounts* counts, const RowSource& rows, const float* o,
+                      const float* d, int64_t ray_stride, int64_t r0, float* out, hipStream_t st) {
   if (g.dtype == AMNERF_FP8_ACT)
-    return launch_mlp8(g.n_hidden, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d,
-                       ray_stride, r0, out, st);
+    return launch_mlp8(g.n_hidden, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
   Layout L = make_layout(g.n_hidden, g.hidden, g.dtype);
   if (g.dtype == AMNERF_FP8) {
-    if (g.hidden == 64) return launch_typed<64, true, true>(L, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, ray_stride, r0, out, st);
-    return launch_typed<32, true, true>(L, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, ray_stride, r0, out, st);
+    if (g.hidden == 64) return launch_typed<64, true, true>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
+    return launch_typed<32, true, true>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
   }
   if (g.dtype == AMNERF_BF16) {
-    if (g.hidden == 64) return launch_typed<64, true>(L, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, ray_stride, r0, out, st);
-    return launch_typed<32, true>(L, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, ray_stride, r0, out, st);
+    if (g.hidden == 64) return launch_typed<64, true>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
+    return launch_typed<32, true>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
   }
   // float32: the split kernel (twice as fast) wherever its weights fit a compute unit's LDS,
   // which leaves 8 layers of 64 to the float32 matrix instructions
   if (mlp32_fits(g.n_hidden, g.hidden))
-    return launch_mlp32(g.n_hidden, g.hidden, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d,
-                        ray_stride, r0, out, st);
-  return launch_typed<64, false>(L, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, ray_stride, r0, out, st);
+    return launch_mlp32(g.n_hidden, g.hidden, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
+  return launch_typed<64, false>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
 }
 
 }  // namespace amn

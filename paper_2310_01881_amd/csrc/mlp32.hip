@@ -31,6 +31,7 @@
 #include "internal.hpp"
 #include "devcommon.hpp"
 #include "mlp_layout.hpp"
+#include "rows.hpp"
 
 namespace amn {
 namespace {
@@ -47,9 +48,10 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 __host__ __device__ constexpr int frag0(int H) { return H / 32 * 2; }
 __host__ __device__ constexpr int frags_hidden(int H) { return H / 32 * (H / 16); }
 __host__ __device__ constexpr int frags(int H, int nh) { return frag0(H) + (nh - 1) * frags_hidden(H); }
-// LDS: fragments, biases (n_hidden * H floats), output weights [H][4], output biases [4]
+// LDS: fragments, biases (n_hidden * H floats), output weights [H][4], output biases [4], the
+// waves' row marks
 __host__ __device__ constexpr uint32_t lds_bytes(int H, int nh) {
-  return (uint32_t)(frags(H, nh) * kFragBytes + nh * H * 4 + H * 16 + 16);
+  return (uint32_t)(frags(H, nh) * kFragBytes + nh * H * 4 + H * 16 + 16 + kWaves * 64);
 }
 
 __device__ __forceinline__ uint32_t high_halves(float a, float b) {   // low: a's, high: b's
@@ -199,15 +201,14 @@ __device__ __forceinline__ void layer32(const uint8_t* frag, const float* bias, 
   }
 }
 
-template <int H>
+template <int H, bool FUSED>
 __global__ __launch_bounds__(kThreads, H == 64 ? 2 : 4) void k_mlp32(
     Layout L, const uint8_t* __restrict__ packed, uint32_t n_leaves, const uint32_t* __restrict__ bucket_off,
-    const uint32_t* __restrict__ tile_off, const ChunkCounts* __restrict__ counts,
-    const uint32_t* __restrict__ srec_ray, const float* __restrict__ srec_t, const uint32_t* __restrict__ perm,
+    const uint32_t* __restrict__ tile_off, const ChunkCounts* __restrict__ counts, RowSource rows,
     const float* __restrict__ o, const float* __restrict__ d, int64_t stride, int64_t r0, float* __restrict__ out) {
   extern __shared__ __align__(16) uint8_t lds[];
   constexpr int KS = H / 16;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, c = lane & 31;
   const float* bias = reinterpret_cast<const float*>(lds + frags(H, L.nh) * kFragBytes);
   const float* wo = bias + L.nh * H;
@@ -222,32 +223,15 @@ __global__ __launch_bounds__(kThreads, H == 64 ? 2 : 4) void k_mlp32(
   }
   uint32_t b = lo;
   int cur = -1;
-  // the next tile's row of this lane (both halves of the wave hold row c): its record is
-  // loaded a tile ahead, its ray gathered during the current tile's first layer
-  uint32_t qb = lo, q_row0 = 0, q_end = 0, n_ray = 0, n_perm = 0;
-  float n_t = 0.f, n_o[3] = {0.f, 0.f, 0.f}, n_d[3] = {0.f, 0.f, 0.f};
-  auto next_rows = [&](uint32_t tt) {
-    while (tile_off[qb + 1] <= tt) ++qb;
-    q_row0 = bucket_off[qb] + (tt - tile_off[qb]) * kMlpTileRows + wave * 32;
-    q_end = bucket_off[qb + 1];
-    const uint32_t row = q_row0 + c;
-    n_ray = 0u; n_perm = 0u; n_t = 0.f;
-    if (row < q_end) {
-      n_ray = srec_ray[row];
-      n_t = srec_t[row];
-      n_perm = perm[row];
-    }
-  };
-  auto gather = [&]() {
-    const int64_t ri = r0 + n_ray;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      n_o[a] = o[a * stride + ri];
-      n_d[a] = d[a * stride + ri];
-    }
-  };
-  next_rows(tb);
-  gather();
+  // the next tile's row of this lane (both halves of the wave hold row c), found and loaded
+  // during the current tile
+  uint8_t* mark = lds + lds_bytes(H, L.nh) - (kWaves - wave) * 64;
+  const uint32_t n_iv = counts->n_iv;
+  RowFetch<FUSED, 32> q;
+  q.init(lo, wave);
+  q.locate(rows, bucket_off, tile_off, tb, wave, lane, n_iv);
+  q.fetch(rows, mark, o, d, stride, r0, lane);
+  q.gather(o, d, stride, r0);
   for (uint32_t t = tb; t < te; ++t) {
     while (tile_off[b + 1] <= t) ++b;
     if ((int)b != cur) {
@@ -256,19 +240,22 @@ __global__ __launch_bounds__(kThreads, H == 64 ? 2 : 4) void k_mlp32(
       __syncthreads();
       cur = (int)b;
     }
-    const bool valid = q_row0 + (uint32_t)c < q_end;
-    const bool any = q_row0 < q_end;
-    const uint32_t dst = n_perm;
+    const bool valid = q.row0 + (uint32_t)c < q.end;
+    const bool any = q.row0 < q.end;
+    const uint32_t dst = q.perm;
     float p[3], dd[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      dd[a] = n_d[a];
-      p[a] = 2.f * fmaf(n_t, n_d[a], n_o[a]) - 1.f;
+      dd[a] = q.d[a];
+      p[a] = 2.f * fmaf(q.t, q.d[a], q.o[a]) - 1.f;
     }
     const bool more = t + 1 < te;
-    if (more) next_rows(t + 1);
+    if (more) q.locate(rows, bucket_off, tile_off, t + 1, wave, lane, n_iv);
     if (!any) {
-      if (more) gather();
+      if (more) {
+        q.fetch(rows, mark, o, d, stride, r0, lane);
+        q.gather(o, d, stride, r0);
+      }
       continue;
     }
     // inputs: frequency groups g = h and h + 2 of mlp_layout.hpp's float32 order, slots 4 ks + e
@@ -297,11 +284,14 @@ __global__ __launch_bounds__(kThreads, H == 64 ? 2 : 4) void k_mlp32(
     f32x4 r = h == 0 ? *reinterpret_cast<const f32x4*>(wo + 4 * H) : f32x4{0.f, 0.f, 0.f, 0.f};
     if (L.nh == 1) {
       layer32<H, 2, true>(lds, bias, wo, lane, h, B, r);
-      if (more) gather();
+      if (more) {
+        q.fetch(rows, mark, o, d, stride, r0, lane);
+        q.gather(o, d, stride, r0);
+      }
     } else {
       layer32<H, 2, false>(lds, bias, wo, lane, h, B, r);
       __builtin_amdgcn_sched_barrier(0);
-      if (more) gather();
+      if (more) q.fetch(rows, mark, o, d, stride, r0, lane);
       __builtin_amdgcn_sched_barrier(0);
       const uint8_t* frag = lds + frag0(H) * kFragBytes;
       const float* lb = bias + H;
@@ -310,6 +300,9 @@ __global__ __launch_bounds__(kThreads, H == 64 ? 2 : 4) void k_mlp32(
         frag += frags_hidden(H) * kFragBytes;
         lb += H;
       }
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) q.gather(o, d, stride, r0);
+      __builtin_amdgcn_sched_barrier(0);
       layer32<H, KS, true>(frag, lb, wo, lane, h, B, r);
     }
 #pragma unroll
@@ -318,19 +311,26 @@ __global__ __launch_bounds__(kThreads, H == 64 ? 2 : 4) void k_mlp32(
   }
 }
 
-template <int H>
-hipError_t launch_typed32(const Layout& L, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
-                          const uint32_t* tile_off, const ChunkCounts* counts, const uint32_t* srec_ray,
-                          const float* srec_t, const uint32_t* perm, const float* o, const float* d, int64_t stride,
-                          int64_t r0, float* out, hipStream_t st) {
-  auto kern = k_mlp32<H>;
+template <int H, bool FUSED>
+hipError_t launch_rows32(const Layout& L, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
+                         const uint32_t* tile_off, const ChunkCounts* counts, const RowSource& rows, const float* o,
+                         const float* d, int64_t stride, int64_t r0, float* out, hipStream_t st) {
+  auto kern = k_mlp32<H, FUSED>;
   const uint32_t lds = lds_bytes(H, L.nh);
   int grid = 0;
   hipError_t e = persistent_grid((const void*)kern, kThreads, lds, &grid);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, L, (const uint8_t*)packed, n_leaves, bucket_off,
-                     tile_off, counts, srec_ray, srec_t, perm, o, d, stride, r0, out);
+                     tile_off, counts, rows, o, d, stride, r0, out);
   return hipGetLastError();
+}
+
+template <int H>
+hipError_t launch_typed32(const Layout& L, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
+                          const uint32_t* tile_off, const ChunkCounts* counts, const RowSource& rows, const float* o,
+                          const float* d, int64_t stride, int64_t r0, float* out, hipStream_t st) {
+  return rows.rec ? launch_rows32<H, true>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, stride, r0, out, st)
+                  : launch_rows32<H, false>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, stride, r0, out, st);
 }
 
 }  // namespace
@@ -338,14 +338,11 @@ hipError_t launch_typed32(const Layout& L, const void* packed, uint32_t n_leaves
 bool mlp32_fits(int n_hidden, int hidden) { return lds_bytes(hidden, n_hidden) <= 160u * 1024u; }
 
 hipError_t launch_mlp32(int n_hidden, int hidden, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
-                        const uint32_t* tile_off, const ChunkCounts* counts, const uint32_t* srec_ray,
-                        const float* srec_t, const uint32_t* perm, const float* o, const float* d, int64_t stride,
-                        int64_t r0, float* out, hipStream_t st) {
+                        const uint32_t* tile_off, const ChunkCounts* counts, const RowSource& rows, const float* o,
+                        const float* d, int64_t stride, int64_t r0, float* out, hipStream_t st) {
   const Layout L = make_layout(n_hidden, hidden, AMNERF_F32);
-  return hidden == 64 ? launch_typed32<64>(L, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o,
-                                           d, stride, r0, out, st)
-                      : launch_typed32<32>(L, packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o,
-                                           d, stride, r0, out, st);
+  return hidden == 64 ? launch_typed32<64>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, stride, r0, out, st)
+                      : launch_typed32<32>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, stride, r0, out, st);
 }
 
 }  // namespace amn

@@ -37,6 +37,7 @@
 #include "internal.hpp"
 #include "devcommon.hpp"
 #include "mlp_layout.hpp"
+#include "rows.hpp"
 
 #include "../../include/amnerf.h"
 
@@ -252,15 +253,15 @@ __device__ __forceinline__ void to_fp8(const f32x16 (&a)[2][2], const f32x4 (&b)
   }
 }
 
-template <int NH>
+template <int NH, bool FUSED>
 __global__ __launch_bounds__(kThreads8) void k_mlp8(
     const uint8_t* __restrict__ packed, uint32_t n_leaves, const uint32_t* __restrict__ bucket_off,
     const uint32_t* __restrict__ tile_off, const ChunkCounts* __restrict__ counts,
-    const uint32_t* __restrict__ srec_ray, const float* __restrict__ srec_t, const uint32_t* __restrict__ perm,
-    const float* __restrict__ o, const float* __restrict__ d, int64_t stride, int64_t r0, float* __restrict__ out) {
+    RowSource rows, const float* __restrict__ o, const float* __restrict__ d, int64_t stride, int64_t r0,
+    float* __restrict__ out) {
   extern __shared__ __align__(16) uint8_t lds[];
   const Layout8 L = make_layout8(NH);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, c = lane & 31;
 
   const uint32_t T = counts->n_tiles;
@@ -285,31 +286,13 @@ __global__ __launch_bounds__(kThreads8) void k_mlp8(
   const f32x16 zero16 = {};
 
   // the wave's 64 rows of the next tile, one row per lane (see k_mlp)
-  uint32_t qb = lo, q_row0 = 0, q_end = 0;
-  uint32_t n_ray = 0, n_perm = 0;
-  float n_t = 0.f, n_o[3] = {0.f, 0.f, 0.f}, n_d[3] = {0.f, 0.f, 0.f};
-  auto next_rows = [&](uint32_t tt) {
-    while (tile_off[qb + 1] <= tt) ++qb;
-    q_row0 = bucket_off[qb] + (tt - tile_off[qb]) * kMlpTileRows + wave * 64;
-    q_end = bucket_off[qb + 1];
-    const uint32_t row = q_row0 + lane;
-    n_ray = 0u; n_perm = 0u; n_t = 0.f;
-    if (row < q_end) {
-      n_ray = srec_ray[row];
-      n_t = srec_t[row];
-      n_perm = perm[row];
-    }
-  };
-  auto gather = [&]() {
-    const int64_t ri = r0 + n_ray;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      n_o[a] = o[a * stride + ri];
-      n_d[a] = d[a * stride + ri];
-    }
-  };
-  next_rows(tb);
-  gather();
+  uint8_t* mark = lds + L.bytes + wave * 64;
+  const uint32_t n_iv = counts->n_iv;
+  RowFetch<FUSED, 64> q;
+  q.init(lo, wave);
+  q.locate(rows, bucket_off, tile_off, tb, wave, lane, n_iv);
+  q.fetch(rows, mark, o, d, stride, r0, lane);
+  q.gather(o, d, stride, r0);
   for (uint32_t t = tb; t < te; ++t) {
     while (tile_off[b + 1] <= t) ++b;
     if ((int)b != cur) {
@@ -323,18 +306,21 @@ __global__ __launch_bounds__(kThreads8) void k_mlp8(
       bwo = *reinterpret_cast<const uint32_t*>(lds + L.off_obias + lane * 4);
       cur = (int)b;
     }
-    const uint32_t row0 = q_row0, row_end = q_end;
-    const uint32_t c_perm = n_perm;
+    const uint32_t row0 = q.row0, row_end = q.end;
+    const uint32_t c_perm = q.perm;
     float c_p[3], c_d[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-      c_d[a] = n_d[a];
-      c_p[a] = 2.f * fmaf(n_t, n_d[a], n_o[a]) - 1.f;
+      c_d[a] = q.d[a];
+      c_p[a] = 2.f * fmaf(q.t, q.d[a], q.o[a]) - 1.f;
     }
     const bool more = t + 1 < te;
-    if (more) next_rows(t + 1);
+    if (more) q.locate(rows, bucket_off, tile_off, t + 1, wave, lane, n_iv);
     if (row0 >= row_end) {
-      if (more) gather();
+      if (more) {
+        q.fetch(rows, mark, o, d, stride, r0, lane);
+        q.gather(o, d, stride, r0);
+      }
       continue;
     }
 
@@ -404,7 +390,7 @@ __global__ __launch_bounds__(kThreads8) void k_mlp8(
         acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, X[cb][1], acc[rb][cb], 0, 0, 0);
       }
     __builtin_amdgcn_sched_barrier(0);
-    if (more) gather();
+    if (more) q.fetch(rows, mark, o, d, stride, r0, lane);
     __builtin_amdgcn_sched_barrier(0);
     i32x8 act[2];
     to_fp8(acc, bias, act);
@@ -412,6 +398,11 @@ __global__ __launch_bounds__(kThreads8) void k_mlp8(
     // ---- hidden layers (float8) ----
 #pragma unroll
     for (int l = 0; l < NH - 1; ++l) {
+      if (l == (NH - 1) / 2) {   // (half way: the records have arrived, the rays will have)
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) q.gather(o, d, stride, r0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       asm volatile("" : "+v"(hb), "+v"(wl) : "v"(act[0]), "v"(act[1]));
       load_bias(l + 1);
 #pragma unroll
@@ -424,6 +415,7 @@ __global__ __launch_bounds__(kThreads8) void k_mlp8(
       to_fp8(acc, bias, act);
     }
 
+    if (NH == 1 && more) q.gather(o, d, stride, r0);
     // ---- output layer (float8; rows 0..3 are sigma^, r^, g^, b^): the bias, broadcast over
     // the columns by one bfloat16 MFMA (A = its high and low parts in two K slots, B = ones),
     // is the accumulator input ----
@@ -525,18 +517,26 @@ __global__ __launch_bounds__(kCalThreads) void k_act_max(int P, const float* __r
   }
 }
 
-template <int NH>
-hipError_t launch8(const void* packed, uint32_t n_leaves, const uint32_t* bucket_off, const uint32_t* tile_off,
-                   const ChunkCounts* counts, const uint32_t* srec_ray, const float* srec_t, const uint32_t* perm,
-                   const float* o, const float* d, int64_t stride, int64_t r0, float* out, hipStream_t st) {
-  auto kern = k_mlp8<NH>;
-  const uint32_t lds = make_layout8(NH).bytes;
+template <int NH, bool FUSED>
+hipError_t launch8_rows(const void* packed, uint32_t n_leaves, const uint32_t* bucket_off, const uint32_t* tile_off,
+                        const ChunkCounts* counts, const RowSource& rows, const float* o, const float* d,
+                        int64_t stride, int64_t r0, float* out, hipStream_t st) {
+  auto kern = k_mlp8<NH, FUSED>;
+  const uint32_t lds = make_layout8(NH).bytes + (FUSED ? kThreads8 / 64 * 64u : 0u);   // + the waves' row marks
   int grid = 0;
   hipError_t e = persistent_grid((const void*)kern, kThreads8, lds, &grid);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads8), lds, st, (const uint8_t*)packed, n_leaves, bucket_off, tile_off,
-                     counts, srec_ray, srec_t, perm, o, d, stride, r0, out);
+                     counts, rows, o, d, stride, r0, out);
   return hipGetLastError();
+}
+
+template <int NH>
+hipError_t launch8(const void* packed, uint32_t n_leaves, const uint32_t* bucket_off, const uint32_t* tile_off,
+                   const ChunkCounts* counts, const RowSource& rows, const float* o, const float* d, int64_t stride,
+                   int64_t r0, float* out, hipStream_t st) {
+  return rows.rec ? launch8_rows<NH, true>(packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, stride, r0, out, st)
+                  : launch8_rows<NH, false>(packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, stride, r0, out, st);
 }
 
 template <int NH>
@@ -567,14 +567,13 @@ hipError_t launch_mlp8_pack(int n_hidden, int n_leaves, const float* master, con
 }
 
 hipError_t launch_mlp8(int n_hidden, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
-                       const uint32_t* tile_off, const ChunkCounts* counts, const uint32_t* srec_ray,
-                       const float* srec_t, const uint32_t* perm, const float* o, const float* d, int64_t stride,
-                       int64_t r0, float* out, hipStream_t st) {
+                       const uint32_t* tile_off, const ChunkCounts* counts, const RowSource& rows, const float* o,
+                       const float* d, int64_t stride, int64_t r0, float* out, hipStream_t st) {
   switch (n_hidden) {
-    case 1: return launch8<1>(packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, stride, r0, out, st);
-    case 2: return launch8<2>(packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, stride, r0, out, st);
-    case 3: return launch8<3>(packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, stride, r0, out, st);
-    case 4: return launch8<4>(packed, n_leaves, bucket_off, tile_off, counts, srec_ray, srec_t, perm, o, d, stride, r0, out, st);
+    case 1: return launch8<1>(packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, stride, r0, out, st);
+    case 2: return launch8<2>(packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, stride, r0, out, st);
+    case 3: return launch8<3>(packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, stride, r0, out, st);
+    case 4: return launch8<4>(packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, stride, r0, out, st);
     default: return hipErrorInvalidValue;
   }
 }

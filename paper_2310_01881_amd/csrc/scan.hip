@@ -1,6 +1,12 @@
-// scan.hip -- exclusive prefix sums of uint32 arrays whose length may live on the device
-// (reduce, scan of block sums, rescan), used for ray offsets, bucket bases and tiles.
+// scan.hip -- exclusive prefix sums of uint32 arrays whose length may live on the device, in
+// one pass (chain.hpp): used for ray offsets, the sort's count matrix and the rounds' selection.
+//
+// A tile is 2048 elements (256 threads x 8, in registers between its sum and its output), so
+// every element is read and written once.  Reduce, scan of the block sums and rescan read
+// everything twice and took three launches: 24 + 10 + 44 us for the 4 million entries of an
+// 800x800 frame's matrix and intervals, and 12 us of launches for a 64x64 one.
 #include "internal.hpp"
+#include "chain.hpp"
 
 namespace amn {
 namespace {
@@ -9,168 +15,152 @@ constexpr int kThreads = 256;
 constexpr int kPer = kScanItems / kThreads;   // 8
 constexpr int kMaxGrid = 2048;
 
-__device__ __forceinline__ uint64_t scan_n(uint64_t n_cap, const uint32_t* n_dev) {
-  if (!n_dev) return n_cap;
-  uint64_t n = *n_dev;
-  return n < n_cap ? n : n_cap;
-}
-
-// Elements are uint32 (one array) or, for a pair of arrays scanned together, uint64 with
-// the first array in the high and the second in the low half: the sums of both stay below
-// 2^32 (a pass holds at most 2^28 samples), so the halves never carry into each other.
-template <bool PAIR>
-struct Elem {
-  typedef uint32_t T;
-  __device__ static T load(const uint32_t* a, const uint32_t*, uint64_t i) { return a[i]; }
-  __device__ static void store(uint32_t* a, uint32_t*, uint64_t i, T v) { a[i] = v; }
-};
-template <>
-struct Elem<true> {
-  typedef uint64_t T;
-  __device__ static T load(const uint32_t* a, const uint32_t* b, uint64_t i) {
-    return ((uint64_t)a[i] << 32) | b[i];
-  }
-  __device__ static void store(uint32_t* a, uint32_t* b, uint64_t i, T v) {
-    a[i] = (uint32_t)(v >> 32);
-    b[i] = (uint32_t)v;
-  }
+// What an element holds and where its prefix goes.
+enum ScanMode {
+  kSingle,   // one array to one
+  kPair,     // two arrays of the same length to two
+  kPacked    // count << 20 | samples in one word: the counts' prefix in place, the samples' to out2
 };
 
-// Inclusive scan of one value per thread across a 256-thread block; returns the block total.
-template <typename T>
-__device__ __forceinline__ T block_incl_scan(T v, T* sh_wave, T& incl) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    T y = __shfl_up(v, off, 64);
-    if (lane >= off) v += y;
-  }
-  if (lane == 63) sh_wave[wave] = v;
-  __syncthreads();
-  T pre = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < kThreads / 64; ++w) {
-    T s = sh_wave[w];
-    if (w < wave) pre += s;
-    tot += s;
-  }
-  __syncthreads();
-  incl = v + pre;
-  return tot;
+// Both halves of a sum stay below 2^31 (a pass holds at most 2^28 samples).
+__device__ __forceinline__ uint64_t pack2(uint32_t a, uint32_t b) { return ((uint64_t)a << 31) | b; }
+
+template <int MODE>
+__device__ __forceinline__ uint64_t element(uint32_t a, uint32_t b) {
+  if (MODE == kPair) return pack2(a, b);
+  if (MODE == kPacked) return pack2(a >> 20, a & 0xFFFFFu);
+  return a;
 }
 
-template <bool PAIR>
-__global__ __launch_bounds__(kThreads) void k_scan_reduce(const uint32_t* __restrict__ in,
-                                                          const uint32_t* __restrict__ in2,
-                                                          uint64_t n_cap, const uint32_t* n_dev,
-                                                          typename Elem<PAIR>::T* __restrict__ bsum) {
-  typedef typename Elem<PAIR>::T T;
-  __shared__ T sh[kThreads / 64];
-  const uint64_t n = scan_n(n_cap, n_dev);
-  const uint64_t nb = (n + kScanItems - 1) / kScanItems;
-  for (uint64_t b = blockIdx.x; b < nb; b += gridDim.x) {
-    uint64_t base = b * kScanItems + (uint64_t)threadIdx.x * kPer;
-    T s = 0;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i)
-      if (base + i < n) s += Elem<PAIR>::load(in, in2, base + i);
-    T incl;
-    T tot = block_incl_scan<T>(s, sh, incl);
-    if (threadIdx.x == 0) bsum[b] = tot;
-  }
+template <int MODE>
+__device__ __forceinline__ void split2(uint64_t v, uint32_t& a, uint32_t& b) {
+  a = MODE == kSingle ? (uint32_t)v : (uint32_t)(v >> 31);
+  b = (uint32_t)v & 0x7FFFFFFFu;
 }
 
-// Single block: exclusive scan of the block sums in place; writes the grand total to out[n].
-template <bool PAIR>
-__global__ __launch_bounds__(1024) void k_scan_blocks(typename Elem<PAIR>::T* __restrict__ bsum, uint64_t n_cap,
-                                                      const uint32_t* n_dev, uint32_t* __restrict__ out,
-                                                      uint32_t* __restrict__ out2) {
-  typedef typename Elem<PAIR>::T T;
-  __shared__ T sh[1024 / 64];
-  const uint64_t n = scan_n(n_cap, n_dev);
-  const uint64_t nb = (n + kScanItems - 1) / kScanItems;
+// n = n_cap, or mul * ceil(*n_dev / div) (at most n_cap) when n_dev is given.
+template <int MODE>
+__global__ __launch_bounds__(kThreads) void k_scan(const uint32_t* in, const uint32_t* __restrict__ in2, uint32_t* out,
+                                                   uint32_t* __restrict__ out2, uint64_t n_cap,
+                                                   const uint32_t* __restrict__ n_dev, uint32_t mul, uint32_t div,
+                                                   uint64_t* __restrict__ state) {
+  __shared__ uint32_t s_tile;
+  __shared__ uint64_t s_wave[kThreads / 64], s_before;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  T carry = 0;
-  for (uint64_t c = 0; c < nb; c += 1024) {
-    uint64_t i = c + threadIdx.x;
-    T v = i < nb ? bsum[i] : (T)0;
-    T x = v;
+  uint64_t n = n_cap;
+  if (n_dev) {
+    n = (uint64_t)mul * (((uint64_t)*n_dev + div - 1) / div);
+    if (n > n_cap) n = n_cap;
+  }
+  if (n == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
+    out[0] = 0u;
+    if (MODE != kSingle) out2[0] = 0u;
+  }
+  while (true) {
+    if (threadIdx.x == 0) s_tile = chain_ticket(state);
+    __syncthreads();
+    const uint32_t tile = __builtin_amdgcn_readfirstlane(s_tile);
+    const uint64_t first = (uint64_t)tile * kScanItems;
+    if (first >= n) break;   // (the same for the whole block)
+    const uint64_t base = first + (uint64_t)threadIdx.x * kPer;
+    uint32_t a[kPer], b[kPer];
+    if (base + kPer <= n) {
+#pragma unroll
+      for (int i = 0; i < kPer; i += 4) {
+        const uint4 v = *reinterpret_cast<const uint4*>(in + base + i);
+        a[i] = v.x; a[i + 1] = v.y; a[i + 2] = v.z; a[i + 3] = v.w;
+        if (MODE == kPair) {
+          const uint4 w = *reinterpret_cast<const uint4*>(in2 + base + i);
+          b[i] = w.x; b[i + 1] = w.y; b[i + 2] = w.z; b[i + 3] = w.w;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        a[i] = base + i < n ? in[base + i] : 0u;
+        b[i] = MODE == kPair && base + i < n ? in2[base + i] : 0u;
+      }
+    }
+    uint64_t own = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) own += element<MODE>(a[i], b[i]);
+    uint64_t incl = own;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-      T y = __shfl_up(x, off, 64);
-      if (lane >= off) x += y;
+      const uint64_t y = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += y;
     }
-    if (lane == 63) sh[wave] = x;
+    if (lane == 63) s_wave[wave] = incl;
     __syncthreads();
-    T pre = 0, tot = 0;
-    for (int w = 0; w < 16; ++w) {
-      T s = sh[w];
-      if (w < wave) pre += s;
-      tot += s;
+    uint64_t pre = 0, tot = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) {
+      if (w < wave) pre += s_wave[w];
+      tot += s_wave[w];
     }
-    if (i < nb) bsum[i] = carry + pre + x - v;
-    carry += tot;
+    if (wave == 0) {
+      const uint64_t before = chain_prefix(state + 1, tile, tot, lane);
+      if (lane == 0) s_before = before;
+    }
     __syncthreads();
+    uint64_t run = s_before + pre + (incl - own);
+    uint32_t x[kPer], y[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      split2<MODE>(run, x[i], y[i]);
+      run += element<MODE>(a[i], b[i]);
+    }
+    if (base + kPer <= n) {
+#pragma unroll
+      for (int i = 0; i < kPer; i += 4) {
+        *reinterpret_cast<uint4*>(out + base + i) = make_uint4(x[i], x[i + 1], x[i + 2], x[i + 3]);
+        if (MODE != kSingle) *reinterpret_cast<uint4*>(out2 + base + i) = make_uint4(y[i], y[i + 1], y[i + 2], y[i + 3]);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < kPer; ++i)
+        if (base + i < n) {
+          out[base + i] = x[i];
+          if (MODE != kSingle) out2[base + i] = y[i];
+        }
+    }
+    if (first + kScanItems >= n && threadIdx.x == 0) {   // the last tile: the totals
+      uint32_t ta, tb;
+      split2<MODE>(s_before + tot, ta, tb);
+      out[n] = ta;
+      if (MODE != kSingle) out2[n] = tb;
+    }
+    __syncthreads();   // (s_tile, s_before and s_wave are written again)
   }
-  if (threadIdx.x == 0) Elem<PAIR>::store(out, out2, n, carry);
 }
 
-template <bool PAIR>
-__global__ __launch_bounds__(kThreads) void k_scan_final(const uint32_t* __restrict__ in,
-                                                         const uint32_t* __restrict__ in2,
-                                                         uint32_t* __restrict__ out, uint32_t* __restrict__ out2,
-                                                         uint64_t n_cap, const uint32_t* n_dev,
-                                                         const typename Elem<PAIR>::T* __restrict__ bsum) {
-  typedef typename Elem<PAIR>::T T;
-  __shared__ T sh[kThreads / 64];
-  const uint64_t n = scan_n(n_cap, n_dev);
-  const uint64_t nb = (n + kScanItems - 1) / kScanItems;
-  for (uint64_t b = blockIdx.x; b < nb; b += gridDim.x) {
-    uint64_t base = b * kScanItems + (uint64_t)threadIdx.x * kPer;
-    T v[kPer];
-    T s = 0;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      v[i] = base + i < n ? Elem<PAIR>::load(in, in2, base + i) : (T)0;
-      s += v[i];
-    }
-    T incl;
-    block_incl_scan<T>(s, sh, incl);
-    T run = bsum[b] + incl - s;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      if (base + i < n) Elem<PAIR>::store(out, out2, base + i, run);
-      run += v[i];
-    }
-  }
+template <int MODE>
+hipError_t launch(const uint32_t* in, const uint32_t* in2, uint32_t* out, uint32_t* out2, uint64_t n_cap,
+                  const uint32_t* n_dev, uint32_t mul, uint32_t div, uint64_t* state, hipStream_t st) {
+  const uint64_t nb = (n_cap + kScanItems - 1) / kScanItems;
+  const uint32_t grid = (uint32_t)(nb < kMaxGrid ? (nb > 0 ? nb : 1) : kMaxGrid);
+  hipLaunchKernelGGL(k_scan<MODE>, dim3(grid), dim3(kThreads), 0, st, in, in2, out, out2, n_cap, n_dev, mul, div, state);
+  return hipGetLastError();
 }
 
 }  // namespace
 
-// Block sums of up to 64 bits each, plus the total.
-size_t scan_tmp_words(uint64_t n_cap) { return 2 * ((n_cap + kScanItems - 1) / kScanItems + 1); }
+// A ticket and a word per tile.
+uint64_t scan_state_words(uint64_t n_cap) { return 1 + (n_cap + kScanItems - 1) / kScanItems; }
 
 hipError_t launch_scan_u32(const uint32_t* in, uint32_t* out, uint64_t n_cap, const uint32_t* n_dev,
-                           uint32_t* tmp, hipStream_t st) {
-  uint64_t nb = (n_cap + kScanItems - 1) / kScanItems;
-  uint32_t grid = (uint32_t)(nb < kMaxGrid ? (nb > 0 ? nb : 1) : kMaxGrid);
-  hipLaunchKernelGGL(k_scan_reduce<false>, dim3(grid), dim3(kThreads), 0, st, in, nullptr, n_cap, n_dev, tmp);
-  hipLaunchKernelGGL(k_scan_blocks<false>, dim3(1), dim3(1024), 0, st, tmp, n_cap, n_dev, out, nullptr);
-  hipLaunchKernelGGL(k_scan_final<false>, dim3(grid), dim3(kThreads), 0, st, in, nullptr, out, nullptr, n_cap, n_dev,
-                     tmp);
-  return hipGetLastError();
+                           uint64_t* state, hipStream_t st) {
+  return launch<kSingle>(in, nullptr, out, nullptr, n_cap, n_dev, 1u, 1u, state, st);
 }
 
 hipError_t launch_scan_u32_pair(const uint32_t* in_a, uint32_t* out_a, const uint32_t* in_b, uint32_t* out_b,
-                                uint64_t n_cap, uint32_t* tmp, hipStream_t st) {
-  uint64_t nb = (n_cap + kScanItems - 1) / kScanItems;
-  uint32_t grid = (uint32_t)(nb < kMaxGrid ? (nb > 0 ? nb : 1) : kMaxGrid);
-  uint64_t* t64 = reinterpret_cast<uint64_t*>(tmp);
-  hipLaunchKernelGGL(k_scan_reduce<true>, dim3(grid), dim3(kThreads), 0, st, in_a, in_b, n_cap, nullptr, t64);
-  hipLaunchKernelGGL(k_scan_blocks<true>, dim3(1), dim3(1024), 0, st, t64, n_cap, nullptr, out_a, out_b);
-  hipLaunchKernelGGL(k_scan_final<true>, dim3(grid), dim3(kThreads), 0, st, in_a, in_b, out_a, out_b, n_cap, nullptr,
-                     t64);
-  return hipGetLastError();
+                                uint64_t n_cap, uint64_t* state, hipStream_t st) {
+  return launch<kPair>(in_a, in_b, out_a, out_b, n_cap, nullptr, 1u, 1u, state, st);
+}
+
+hipError_t launch_scan_packed(uint32_t* mat, uint32_t* out_smp, uint64_t n_cap, const uint32_t* n_dev, uint32_t mul,
+                              uint32_t div, uint64_t* state, hipStream_t st) {
+  return launch<kPacked>(mat, nullptr, mat, out_smp, n_cap, n_dev, mul, div, state, st);
 }
 
 }  // namespace amn

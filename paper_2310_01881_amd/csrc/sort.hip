@@ -5,16 +5,24 @@
 // so the stable sort of samples equals the stable sort of intervals, each expanded into
 // its samples in place.  The sort therefore runs on intervals (about S_max / n fewer keys
 // than samples):
-//   hist    one wave per segment of `seg` consecutive intervals: LDS histogram of slots,
-//           written column-wise into a [slot][segment] count matrix (row length = the
-//           chunk's actual segment count, so the matrix and its scan scale with the
-//           intervals present, and there is a segment per wave across the machine);
+//   hist    one wave per segment of `seg` consecutive intervals: LDS histogram of slots
+//           (intervals and samples in one word), written column-wise into a [slot][segment]
+//           matrix (row length = the chunk's actual segment count, so the matrix and its scan
+//           scale with the intervals present, and there is a segment per wave across the
+//           machine);
 //   scan    exclusive scan of that matrix in slot-major order = the first sorted position
-//           of (slot, segment);
+//           and the first sorted sample of (slot, segment), hence the leaves' buckets and tiles;
 //   scatter one wave per segment again, 64 intervals at a time: lanes holding the same
 //           slot find each other with one ballot per key bit; rank = earlier lanes of the
-//           same slot, base = a per-slot running counter in LDS -> stable positions;
-//   expand  each sorted interval writes its samples' records at its sorted sample base.
+//           same slot, on top of a per-slot running count in LDS -> stable positions; the
+//           samples before an interval likewise (one ballot per bit of the sample count), so
+//           its place among the sorted samples needs no scan of its own.  Each interval's
+//           16-byte record goes to its sorted position, and the 64-row windows of the MLP
+//           tiles that start inside it get its position;
+//   expand  (where one record per sample is needed: rounds, the backward pass, calibration,
+//           inspection) each sorted interval writes its samples' records.
+#include <algorithm>
+
 #include "internal.hpp"
 #include "devcommon.hpp"
 
@@ -23,26 +31,29 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-constexpr uint32_t kMaxGrid = 4096;
+constexpr uint32_t kMaxGrid = 16384;
 
-__device__ __forceinline__ uint64_t lanemask_lt(int lane) { return (1ull << lane) - 1ull; }
-
+// A word of the matrix and of the running counts: intervals << 20 | samples (a segment holds
+// less than 4096 intervals of at most 255 samples).
 __global__ __launch_bounds__(kThreads) void k_sort_hist(const uint32_t* __restrict__ iv_key,
                                                         const uint32_t* __restrict__ n_iv_dev,
                                                         uint32_t seg, uint32_t n_leaves,
                                                         uint32_t* __restrict__ mat) {
   extern __shared__ uint32_t sh[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
   uint32_t* hist = sh + wave * n_leaves;
   const uint32_t n_iv = *n_iv_dev;
   const uint32_t nseg = (n_iv + seg - 1) / seg;
-  for (uint32_t s = blockIdx.x * kWaves + wave; s < nseg; s += gridDim.x * kWaves) {
+  for (uint32_t s = blockIdx.x * waves + wave; s < nseg; s += gridDim.x * waves) {
     for (uint32_t b = lane; b < n_leaves; b += 64) hist[b] = 0u;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     uint64_t begin = (uint64_t)s * seg;
     uint64_t end = begin + seg < n_iv ? begin + seg : n_iv;
-    for (uint64_t i = begin + lane; i < end; i += 64) atomicAdd(&hist[key_slot(iv_key[i])], 1u);
+    for (uint64_t i = begin + lane; i < end; i += 64) {
+      const uint32_t key = iv_key[i];
+      atomicAdd(&hist[key_slot(key)], (1u << 20) | key_n(key));
+    }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     for (uint32_t b = lane; b < n_leaves; b += 64) mat[(uint64_t)b * nseg + s] = hist[b];
@@ -51,73 +62,86 @@ __global__ __launch_bounds__(kThreads) void k_sort_hist(const uint32_t* __restri
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_sort_scatter(const uint32_t* __restrict__ iv_key,
-                                                           const uint32_t* __restrict__ n_iv_dev,
-                                                           uint32_t seg, uint32_t n_leaves,
-                                                           uint32_t key_bits,
-                                                           const uint32_t* __restrict__ mat_scan,
-                                                           uint32_t* __restrict__ sidx,
-                                                           uint32_t* __restrict__ sn) {
+// Set bits of `mask` below this lane.
+__device__ __forceinline__ uint32_t count_below(uint64_t mask) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+__global__ __launch_bounds__(kThreads) void k_sort_scatter(IvSet iv, uint32_t seg, uint32_t n_leaves,
+                                                           uint32_t key_bits, SortBufs out) {
   extern __shared__ uint32_t sh[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t* base = sh + wave * n_leaves;
-  const uint32_t n_iv = *n_iv_dev;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
+  uint32_t* run = sh + wave * n_leaves;   // the segment's intervals and samples of each slot so far
+  const uint32_t n_iv = *iv.n_iv_dev;
   const uint32_t nseg = (n_iv + seg - 1) / seg;
-  for (uint32_t s = blockIdx.x * kWaves + wave; s < nseg; s += gridDim.x * kWaves) {
-    for (uint32_t b = lane; b < n_leaves; b += 64) base[b] = mat_scan[(uint64_t)b * nseg + s];
+  for (uint32_t s = blockIdx.x * waves + wave; s < nseg; s += gridDim.x * waves) {
+    for (uint32_t b = lane; b < n_leaves; b += 64) run[b] = 0u;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     uint64_t begin = (uint64_t)s * seg;
     uint64_t end = begin + seg < n_iv ? begin + seg : n_iv;
     for (uint64_t c = begin; c < end; c += 64) {
-      uint64_t i = c + lane;
-      bool valid = i < end;
-      uint32_t key = valid ? iv_key[i] : 0u;
-      uint32_t slot = key_slot(key);
+      const uint64_t i = c + lane;
+      const bool valid = i < end;
+      const uint32_t key = valid ? iv.key[i] : 0u;
+      const uint32_t slot = key_slot(key), n = key_n(key);
+      uint32_t pos = 0, smp = 0;
+      if (valid) {
+        pos = out.mat[(uint64_t)slot * nseg + s];
+        smp = out.mat_smp[(uint64_t)slot * nseg + s];
+      }
       // lanes with the same slot: intersect one ballot per key bit
       uint64_t peers = __ballot(valid);
       for (uint32_t bit = 0; bit < key_bits; ++bit) {
-        uint64_t ones = __ballot(valid && ((slot >> bit) & 1u));
+        const uint64_t ones = __ballot(valid && ((slot >> bit) & 1u));
         peers &= ((slot >> bit) & 1u) ? ones : ~ones;
       }
-      uint32_t rank = (uint32_t)__popcll(peers & lanemask_lt(lane));
-      uint32_t pos = 0;
-      if (valid) pos = base[slot] + rank;
+      const uint32_t rank = count_below(peers);
+      uint32_t before = 0;   // samples of the earlier lanes of this slot
+#pragma unroll
+      for (uint32_t bit = 0; bit < 8; ++bit) before += count_below(peers & __ballot((n >> bit) & 1u)) << bit;
+      const uint32_t had = valid ? run[slot] : 0u;
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      // the highest lane of each group advances that slot's counter
-      bool last = valid && (peers >> lane) == 1ull;
-      if (last) base[slot] = pos + 1;
+      // the highest lane of each group advances that slot's counts
+      if (valid && (peers >> lane) == 1ull) run[slot] = had + ((rank + 1) << 20) + before + n;
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
       if (valid) {
-        sidx[pos] = (uint32_t)i;
-        sn[pos] = key_n(key);
+        pos += (had >> 20) + rank;
+        smp += (had & 0xFFFFFu) + before;
+        out.sidx[pos] = (uint32_t)i;
+        out.ssb[pos] = smp;
+        if (out.rec) {
+          *reinterpret_cast<float4*>(out.rec + pos) = make_float4(
+              iv.t0[i], iv.dt[i] / (float)n, __uint_as_float(iv.ray[i]), __uint_as_float(iv.base[i]));
+          // the windows (64 rows of the leaf's bucket) whose first row is one of these samples
+          const uint32_t at = smp - out.bucket_off[slot], t0 = 4u * out.tile_off[slot];
+          for (uint32_t w = (at + 63u) / 64u; 64u * w < at + n; ++w) out.win[t0 + w] = pos;
+        }
       }
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
 // One block: leaf bucket offsets in sorted samples and MLP tile offsets.
-__global__ __launch_bounds__(1024) void k_bucket_tiles(const uint32_t* __restrict__ mat_scan,
-                                                       uint32_t seg, uint32_t n_leaves,
-                                                       const uint32_t* __restrict__ ssb,
-                                                       uint32_t* __restrict__ bucket_off,
-                                                       uint32_t* __restrict__ tile_off,
-                                                       ChunkCounts* counts) {
+__global__ __launch_bounds__(1024) void k_bucket_tiles(uint32_t seg, uint32_t n_leaves, SortBufs out,
+                                                       const uint32_t* __restrict__ n_iv_dev, ChunkCounts* counts) {
   __shared__ uint32_t sh[16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint32_t n_iv = counts->n_iv;
+  const uint32_t n_iv = *n_iv_dev;
   const uint32_t nseg = (n_iv + seg - 1) / seg;
-  const uint32_t n_smp = ssb[n_iv];
+  const uint32_t n_smp = out.mat_smp[(uint64_t)n_leaves * nseg];
   uint32_t carry = 0;
   for (uint32_t c = 0; c < n_leaves; c += 1024) {
     uint32_t b = c + threadIdx.x;
     uint32_t lo = 0, hi = 0;
     if (b < n_leaves) {
-      lo = ssb[mat_scan[(uint64_t)b * nseg]];
-      hi = b + 1 < n_leaves ? ssb[mat_scan[(uint64_t)(b + 1) * nseg]] : n_smp;
-      bucket_off[b] = lo;
+      lo = out.mat_smp[(uint64_t)b * nseg];
+      hi = out.mat_smp[(uint64_t)(b + 1) * nseg];
+      out.bucket_off[b] = lo;
     }
     uint32_t nt = (hi - lo + kMlpTileRows - 1) / kMlpTileRows;
     uint32_t x = nt;
@@ -134,13 +158,15 @@ __global__ __launch_bounds__(1024) void k_bucket_tiles(const uint32_t* __restric
       if (w < wave) pre += s;
       tot += s;
     }
-    if (b < n_leaves) tile_off[b] = carry + pre + x - nt;
+    if (b < n_leaves) out.tile_off[b] = carry + pre + x - nt;
     carry += tot;
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    bucket_off[n_leaves] = n_smp;
-    tile_off[n_leaves] = carry;
+    out.bucket_off[n_leaves] = n_smp;
+    out.tile_off[n_leaves] = carry;
+    out.ssb[n_iv] = n_smp;
+    counts->n_iv = n_iv;
     counts->n_smp = n_smp;
     counts->n_tiles = carry;
   }
@@ -223,48 +249,48 @@ __global__ __launch_bounds__(kThreads) void k_expand(
 
 }  // namespace
 
-SortPlan make_sort_plan(uint64_t n_iv_max, uint32_t n_leaves) {
+SortPlan make_sort_plan(uint64_t n_iv_max, uint32_t n_leaves, bool small) {
   SortPlan p;
   p.n_leaves = n_leaves;
   uint32_t bits = 0;
   while ((1u << bits) < n_leaves) ++bits;
   p.key_bits = bits;
-  // a segment per wave; at least as many intervals per segment as slots, so the count
-  // matrix (n_leaves x segments) has no more entries than there are intervals
-  uint64_t seg = ((uint64_t)n_leaves + 63) / 64 * 64;
-  if (seg < 512) seg = 512;
-  p.seg = (uint32_t)seg;
-  p.nseg_max = (uint32_t)((n_iv_max + seg - 1) / seg);
+  // a segment per wave, of 512 intervals, or 64 where few intervals would otherwise leave
+  // most of the chip without a segment (2^18 intervals make 512 segments of 512); at least as
+  // many intervals per segment as slots, so the count matrix (n_leaves x segments) has no more
+  // entries than there are intervals; below 4096, which the packed counts allow
+  uint64_t seg = small && n_iv_max <= (1u << 18) ? 64 : 512;
+  seg = std::max<uint64_t>(seg, ((uint64_t)n_leaves + 63) / 64 * 64);
+  p.seg = (uint32_t)std::min<uint64_t>(seg, 4032);
+  p.nseg_max = (uint32_t)((n_iv_max + p.seg - 1) / p.seg);
   if (p.nseg_max == 0) p.nseg_max = 1;
   return p;
 }
 
+// Waves per block: a wave's counts take 4 bytes per slot of LDS, so with many slots a block is
+// one wave (16 KiB at 4096: ten per compute unit against two blocks of four).
+static int sort_waves(const SortPlan& p) { return p.n_leaves > 1024 ? 1 : kWaves; }
+
 hipError_t launch_sort_hist(const SortPlan& p, const uint32_t* iv_key, const uint32_t* n_iv_dev,
                             uint32_t* mat, hipStream_t st) {
-  uint32_t grid = (p.nseg_max + kWaves - 1) / kWaves;
-  if (grid > kMaxGrid) grid = kMaxGrid;
-  size_t lds = sizeof(uint32_t) * kWaves * p.n_leaves;
-  hipLaunchKernelGGL(k_sort_hist, dim3(grid), dim3(kThreads), lds, st, iv_key, n_iv_dev, p.seg, p.n_leaves,
-                     mat);
+  const uint32_t w = (uint32_t)sort_waves(p);
+  const uint32_t grid = std::min<uint32_t>((p.nseg_max + w - 1) / w, kMaxGrid);
+  hipLaunchKernelGGL(k_sort_hist, dim3(grid), dim3(64 * w), sizeof(uint32_t) * w * p.n_leaves, st, iv_key, n_iv_dev,
+                     p.seg, p.n_leaves, mat);
   return hipGetLastError();
 }
 
-hipError_t launch_sort_scatter(const SortPlan& p, const uint32_t* iv_key, const uint32_t* n_iv_dev,
-                               const uint32_t* mat_scan, uint32_t* sidx, uint32_t* sn,
-                               hipStream_t st) {
-  uint32_t grid = (p.nseg_max + kWaves - 1) / kWaves;
-  if (grid > kMaxGrid) grid = kMaxGrid;
-  size_t lds = sizeof(uint32_t) * kWaves * p.n_leaves;
-  hipLaunchKernelGGL(k_sort_scatter, dim3(grid), dim3(kThreads), lds, st, iv_key, n_iv_dev, p.seg, p.n_leaves,
-                     p.key_bits, mat_scan, sidx, sn);
+hipError_t launch_sort_scatter(const SortPlan& p, const SortBufs& b, const IvSet& iv, hipStream_t st) {
+  const uint32_t w = (uint32_t)sort_waves(p);
+  const uint32_t grid = std::min<uint32_t>((p.nseg_max + w - 1) / w, kMaxGrid);
+  hipLaunchKernelGGL(k_sort_scatter, dim3(grid), dim3(64 * w), sizeof(uint32_t) * w * p.n_leaves, st, iv, p.seg,
+                     p.n_leaves, p.key_bits, b);
   return hipGetLastError();
 }
 
-hipError_t launch_bucket_tiles(const SortPlan& p, const uint32_t* mat_scan, const uint32_t* ssb,
-                               uint32_t* bucket_off, uint32_t* tile_off, ChunkCounts* counts,
+hipError_t launch_bucket_tiles(const SortPlan& p, const SortBufs& b, const uint32_t* n_iv_dev, ChunkCounts* counts,
                                hipStream_t st) {
-  hipLaunchKernelGGL(k_bucket_tiles, dim3(1), dim3(1024), 0, st, mat_scan, p.seg, p.n_leaves,
-                     ssb, bucket_off, tile_off, counts);
+  hipLaunchKernelGGL(k_bucket_tiles, dim3(1), dim3(1024), 0, st, p.seg, p.n_leaves, b, n_iv_dev, counts);
   return hipGetLastError();
 }
 
