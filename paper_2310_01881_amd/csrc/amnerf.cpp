@@ -1123,8 +1123,8 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
   // The MLPs read the sorted intervals, unless sample records are needed in any case (rounds
   // compact them; jittered strata have no place in an interval's record) or the workspace is
   // limited and only the layout with sample records fits it (the intervals' records may take
-  // 4 bytes per possible interval more).  Expanding first: 800x800 frame 2.60 against 2.35 ms,
-  // 64x64 87 against 54 us, 1920x1080 float8 7.95 against 7.21 ms (with the scans in one launch
+  // 4 bytes per possible interval more).  Expanding first: 800x800 frame 2.38 against 2.08 ms,
+  // 64x64 87 against 54 us, 1920x1080 float8 7.01 against 6.00 ms (with the scans in one launch
   // each).
   bool fused = !rounds && !jitter && !keep_samples;
   SortPlan sp = make_sort_plan(niv_max, L, fused);

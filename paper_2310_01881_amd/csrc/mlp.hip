@@ -267,7 +267,9 @@ template <int H, bool BF16, bool FP8, bool FUSED>
 __global__ __launch_bounds__(kThreads, BF16 ? 4 : 2) void k_mlp(
     Layout L, const uint8_t* __restrict__ packed, uint32_t n_leaves,
     const uint32_t* __restrict__ bucket_off, const uint32_t* __restrict__ tile_off,
-    const ChunkCounts* __restrict__ counts, RowSource rows,
+    const ChunkCounts* __restrict__ counts, const SortRec* __restrict__ sv_rec, const uint32_t* __restrict__ sv_ssb,
+    const uint32_t* __restrict__ sv_win, const uint32_t* __restrict__ sm_ray, const float* __restrict__ sm_t,
+    const uint32_t* __restrict__ sm_perm,
     const float* __restrict__ o, const float* __restrict__ d, int64_t stride, int64_t r0,
     float* __restrict__ out) {
   extern __shared__ __align__(16) uint8_t lds[];
@@ -295,9 +297,10 @@ __global__ __launch_bounds__(kThreads, BF16 ? 4 : 2) void k_mlp(
   // tile, so that no read is waited for at the start of a tile.
   uint8_t* mark = lds + L.bytes + wave * 64;
   const uint32_t n_iv = counts->n_iv;
+  const RowSource rows = {sv_rec, sv_ssb, sv_win, sm_ray, sm_t, sm_perm};
   RowFetch<FUSED, 64> q;
-  q.init(lo, wave);
-  q.locate(rows, bucket_off, tile_off, tb, wave, lane, n_iv);
+  q.init(rows, lo, tb, wave);
+  q.locate(rows, bucket_off, tile_off, tb, te - 1, wave, lane, n_iv);
   q.fetch(rows, mark, o, d, stride, r0, lane);
   q.gather(o, d, stride, r0);
   for (uint32_t t = tb; t < te; ++t) {
@@ -317,13 +320,11 @@ __global__ __launch_bounds__(kThreads, BF16 ? 4 : 2) void k_mlp(
       c_d[a] = q.d[a];
       c_p[a] = 2.f * fmaf(q.t, q.d[a], q.o[a]) - 1.f;
     }
-    const bool more = t + 1 < te;
-    if (more) q.locate(rows, bucket_off, tile_off, t + 1, wave, lane, n_iv);
+    q.locate(rows, bucket_off, tile_off, min(t + 1, te - 1), te - 1, wave, lane, n_iv);
     if (row0 >= row_end) {
-      if (more) {
-        q.fetch(rows, mark, o, d, stride, r0, lane);
-        q.gather(o, d, stride, r0);
-      }
+      q.fetch(rows, mark, o, d, stride, r0, lane);
+      q.gather(o, d, stride, r0);
+      q.settle();
       continue;
     }
 
@@ -390,7 +391,7 @@ __global__ __launch_bounds__(kThreads, BF16 ? 4 : 2) void k_mlp(
       uint32_t Ha[NCB][KUh][4], Hb[NCB][KUh][4];
       bf16_layer<H, NCB, 1>(L, units, bias, 0, lane, g, X0u, Ha);
       __builtin_amdgcn_sched_barrier(0);
-      if (more) q.fetch(rows, mark, o, d, stride, r0, lane);
+      q.fetch(rows, mark, o, d, stride, r0, lane);
       __builtin_amdgcn_sched_barrier(0);
       int layer = 1;
       for (; layer + 1 < L.nh; layer += 2) {
@@ -398,7 +399,7 @@ __global__ __launch_bounds__(kThreads, BF16 ? 4 : 2) void k_mlp(
         bf16_layer<H, NCB, KUh>(L, units, bias, layer + 1, lane, g, Hb, Ha);
       }
       __builtin_amdgcn_sched_barrier(0);
-      if (more) q.gather(o, d, stride, r0);
+      q.gather(o, d, stride, r0);
       __builtin_amdgcn_sched_barrier(0);
       f32x4 res[NCB];
       if (layer < L.nh) {
@@ -428,10 +429,8 @@ __global__ __launch_bounds__(kThreads, BF16 ? 4 : 2) void k_mlp(
     }
 
     __builtin_amdgcn_sched_barrier(0);
-    if (more) {
-      q.fetch(rows, mark, o, d, stride, r0, lane);
-      q.gather(o, d, stride, r0);
-    }
+    q.fetch(rows, mark, o, d, stride, r0, lane);
+    q.gather(o, d, stride, r0);
     __builtin_amdgcn_sched_barrier(0);
     // ---- hidden layers H -> H, then the output layer H -> 4 (padded to 16) ----
     for (int layer = 1; layer <= L.nh; ++layer) {
@@ -488,7 +487,8 @@ hipError_t launch_rows(const Layout& L, const void* packed, uint32_t n_leaves, c
   hipError_t e = persistent_grid((const void*)kern, kThreads, lds, &grid);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, L, (const uint8_t*)packed, n_leaves,
-                     bucket_off, tile_off, counts, rows, o, d, stride, r0, out);
+                     bucket_off, tile_off, counts, rows.rec, rows.ssb, rows.win, rows.ray, rows.t,
+                     rows.perm, o, d, stride, r0, out);
   return hipGetLastError();
 }
 

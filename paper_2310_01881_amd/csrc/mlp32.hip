@@ -204,7 +204,9 @@ __device__ __forceinline__ void layer32(const uint8_t* frag, const float* bias, 
 template <int H, bool FUSED>
 __global__ __launch_bounds__(kThreads, H == 64 ? 2 : 4) void k_mlp32(
     Layout L, const uint8_t* __restrict__ packed, uint32_t n_leaves, const uint32_t* __restrict__ bucket_off,
-    const uint32_t* __restrict__ tile_off, const ChunkCounts* __restrict__ counts, RowSource rows,
+    const uint32_t* __restrict__ tile_off, const ChunkCounts* __restrict__ counts, const SortRec* __restrict__ sv_rec, const uint32_t* __restrict__ sv_ssb,
+    const uint32_t* __restrict__ sv_win, const uint32_t* __restrict__ sm_ray, const float* __restrict__ sm_t,
+    const uint32_t* __restrict__ sm_perm,
     const float* __restrict__ o, const float* __restrict__ d, int64_t stride, int64_t r0, float* __restrict__ out) {
   extern __shared__ __align__(16) uint8_t lds[];
   constexpr int KS = H / 16;
@@ -227,9 +229,10 @@ __global__ __launch_bounds__(kThreads, H == 64 ? 2 : 4) void k_mlp32(
   // during the current tile
   uint8_t* mark = lds + lds_bytes(H, L.nh) - (kWaves - wave) * 64;
   const uint32_t n_iv = counts->n_iv;
+  const RowSource rows = {sv_rec, sv_ssb, sv_win, sm_ray, sm_t, sm_perm};
   RowFetch<FUSED, 32> q;
-  q.init(lo, wave);
-  q.locate(rows, bucket_off, tile_off, tb, wave, lane, n_iv);
+  q.init(rows, lo, tb, wave);
+  q.locate(rows, bucket_off, tile_off, tb, te - 1, wave, lane, n_iv);
   q.fetch(rows, mark, o, d, stride, r0, lane);
   q.gather(o, d, stride, r0);
   for (uint32_t t = tb; t < te; ++t) {
@@ -249,13 +252,11 @@ __global__ __launch_bounds__(kThreads, H == 64 ? 2 : 4) void k_mlp32(
       dd[a] = q.d[a];
       p[a] = 2.f * fmaf(q.t, q.d[a], q.o[a]) - 1.f;
     }
-    const bool more = t + 1 < te;
-    if (more) q.locate(rows, bucket_off, tile_off, t + 1, wave, lane, n_iv);
+    q.locate(rows, bucket_off, tile_off, min(t + 1, te - 1), te - 1, wave, lane, n_iv);
     if (!any) {
-      if (more) {
-        q.fetch(rows, mark, o, d, stride, r0, lane);
-        q.gather(o, d, stride, r0);
-      }
+      q.fetch(rows, mark, o, d, stride, r0, lane);
+      q.gather(o, d, stride, r0);
+      q.settle();
       continue;
     }
     // inputs: frequency groups g = h and h + 2 of mlp_layout.hpp's float32 order, slots 4 ks + e
@@ -284,14 +285,12 @@ __global__ __launch_bounds__(kThreads, H == 64 ? 2 : 4) void k_mlp32(
     f32x4 r = h == 0 ? *reinterpret_cast<const f32x4*>(wo + 4 * H) : f32x4{0.f, 0.f, 0.f, 0.f};
     if (L.nh == 1) {
       layer32<H, 2, true>(lds, bias, wo, lane, h, B, r);
-      if (more) {
-        q.fetch(rows, mark, o, d, stride, r0, lane);
-        q.gather(o, d, stride, r0);
-      }
+      q.fetch(rows, mark, o, d, stride, r0, lane);
+      q.gather(o, d, stride, r0);
     } else {
       layer32<H, 2, false>(lds, bias, wo, lane, h, B, r);
       __builtin_amdgcn_sched_barrier(0);
-      if (more) q.fetch(rows, mark, o, d, stride, r0, lane);
+      q.fetch(rows, mark, o, d, stride, r0, lane);
       __builtin_amdgcn_sched_barrier(0);
       const uint8_t* frag = lds + frag0(H) * kFragBytes;
       const float* lb = bias + H;
@@ -301,7 +300,7 @@ __global__ __launch_bounds__(kThreads, H == 64 ? 2 : 4) void k_mlp32(
         lb += H;
       }
       __builtin_amdgcn_sched_barrier(0);
-      if (more) q.gather(o, d, stride, r0);
+      q.gather(o, d, stride, r0);
       __builtin_amdgcn_sched_barrier(0);
       layer32<H, KS, true>(frag, lb, wo, lane, h, B, r);
     }
@@ -321,7 +320,8 @@ hipError_t launch_rows32(const Layout& L, const void* packed, uint32_t n_leaves,
   hipError_t e = persistent_grid((const void*)kern, kThreads, lds, &grid);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, L, (const uint8_t*)packed, n_leaves, bucket_off,
-                     tile_off, counts, rows, o, d, stride, r0, out);
+                     tile_off, counts, rows.rec, rows.ssb, rows.win, rows.ray, rows.t,
+                     rows.perm, o, d, stride, r0, out);
   return hipGetLastError();
 }
 

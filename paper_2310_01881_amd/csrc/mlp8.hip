@@ -257,7 +257,9 @@ template <int NH, bool FUSED>
 __global__ __launch_bounds__(kThreads8) void k_mlp8(
     const uint8_t* __restrict__ packed, uint32_t n_leaves, const uint32_t* __restrict__ bucket_off,
     const uint32_t* __restrict__ tile_off, const ChunkCounts* __restrict__ counts,
-    RowSource rows, const float* __restrict__ o, const float* __restrict__ d, int64_t stride, int64_t r0,
+    const SortRec* __restrict__ sv_rec, const uint32_t* __restrict__ sv_ssb,
+    const uint32_t* __restrict__ sv_win, const uint32_t* __restrict__ sm_ray, const float* __restrict__ sm_t,
+    const uint32_t* __restrict__ sm_perm, const float* __restrict__ o, const float* __restrict__ d, int64_t stride, int64_t r0,
     float* __restrict__ out) {
   extern __shared__ __align__(16) uint8_t lds[];
   const Layout8 L = make_layout8(NH);
@@ -288,9 +290,10 @@ __global__ __launch_bounds__(kThreads8) void k_mlp8(
   // the wave's 64 rows of the next tile, one row per lane (see k_mlp)
   uint8_t* mark = lds + L.bytes + wave * 64;
   const uint32_t n_iv = counts->n_iv;
+  const RowSource rows = {sv_rec, sv_ssb, sv_win, sm_ray, sm_t, sm_perm};
   RowFetch<FUSED, 64> q;
-  q.init(lo, wave);
-  q.locate(rows, bucket_off, tile_off, tb, wave, lane, n_iv);
+  q.init(rows, lo, tb, wave);
+  q.locate(rows, bucket_off, tile_off, tb, te - 1, wave, lane, n_iv);
   q.fetch(rows, mark, o, d, stride, r0, lane);
   q.gather(o, d, stride, r0);
   for (uint32_t t = tb; t < te; ++t) {
@@ -314,13 +317,11 @@ __global__ __launch_bounds__(kThreads8) void k_mlp8(
       c_d[a] = q.d[a];
       c_p[a] = 2.f * fmaf(q.t, q.d[a], q.o[a]) - 1.f;
     }
-    const bool more = t + 1 < te;
-    if (more) q.locate(rows, bucket_off, tile_off, t + 1, wave, lane, n_iv);
+    q.locate(rows, bucket_off, tile_off, min(t + 1, te - 1), te - 1, wave, lane, n_iv);
     if (row0 >= row_end) {
-      if (more) {
-        q.fetch(rows, mark, o, d, stride, r0, lane);
-        q.gather(o, d, stride, r0);
-      }
+      q.fetch(rows, mark, o, d, stride, r0, lane);
+      q.gather(o, d, stride, r0);
+      q.settle();
       continue;
     }
 
@@ -390,7 +391,7 @@ __global__ __launch_bounds__(kThreads8) void k_mlp8(
         acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w1, X[cb][1], acc[rb][cb], 0, 0, 0);
       }
     __builtin_amdgcn_sched_barrier(0);
-    if (more) q.fetch(rows, mark, o, d, stride, r0, lane);
+    q.fetch(rows, mark, o, d, stride, r0, lane);
     __builtin_amdgcn_sched_barrier(0);
     i32x8 act[2];
     to_fp8(acc, bias, act);
@@ -400,7 +401,7 @@ __global__ __launch_bounds__(kThreads8) void k_mlp8(
     for (int l = 0; l < NH - 1; ++l) {
       if (l == (NH - 1) / 2) {   // (half way: the records have arrived, the rays will have)
         __builtin_amdgcn_sched_barrier(0);
-        if (more) q.gather(o, d, stride, r0);
+        q.gather(o, d, stride, r0);
         __builtin_amdgcn_sched_barrier(0);
       }
       asm volatile("" : "+v"(hb), "+v"(wl) : "v"(act[0]), "v"(act[1]));
@@ -415,7 +416,7 @@ __global__ __launch_bounds__(kThreads8) void k_mlp8(
       to_fp8(acc, bias, act);
     }
 
-    if (NH == 1 && more) q.gather(o, d, stride, r0);
+    if (NH == 1) q.gather(o, d, stride, r0);
     // ---- output layer (float8; rows 0..3 are sigma^, r^, g^, b^): the bias, broadcast over
     // the columns by one bfloat16 MFMA (A = its high and low parts in two K slots, B = ones),
     // is the accumulator input ----
@@ -527,7 +528,8 @@ hipError_t launch8_rows(const void* packed, uint32_t n_leaves, const uint32_t* b
   hipError_t e = persistent_grid((const void*)kern, kThreads8, lds, &grid);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads8), lds, st, (const uint8_t*)packed, n_leaves, bucket_off, tile_off,
-                     counts, rows, o, d, stride, r0, out);
+                     counts, rows.rec, rows.ssb, rows.win, rows.ray, rows.t,
+                     rows.perm, o, d, stride, r0, out);
   return hipGetLastError();
 }
 
