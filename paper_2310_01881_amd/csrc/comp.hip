@@ -50,28 +50,30 @@ __device__ __forceinline__ DF df_add(DF a, DF b) {
 // exp(-(hi + lo)) for |lo| << 1: exp(-hi) * (1 - lo).
 __device__ __forceinline__ float df_exp_neg(DF a) { return exp_neg(a.hi) * (1.f - a.lo); }
 
-// Inclusive compensated prefix sum over the 16 lanes of a row (shifts by 1, 2, 4, 8; lanes
-// whose source is outside the row add 0).  The high parts are added with an exact TwoSum; the
-// low parts, and each TwoSum's rounding error, go into a plain running sum of low parts,
-// normalised once at the end.
-template <int CTRL>
-__device__ __forceinline__ void df_scan_step(float& hi, float& lo) {
-  const float b = dpp_or_zero<CTRL, 0xF>(hi);
-  const float s = hi + b;
-  const float bb = s - hi;
-  const float e = (hi - (s - bb)) + (b - bb);
-  lo = lo + dpp_or_zero<CTRL, 0xF>(lo) + e;
-  hi = s;
+// Compensated sums of a window of 64 samples, 16 lanes at a time.  High parts are added with an
+// exact TwoSum; low parts, and each TwoSum's rounding error, go into a plain running sum of low
+// parts (the pair is normalised once, at the end).
+__device__ __forceinline__ void df_accumulate(DF& v, float hi, float lo) {
+  const float s = v.hi + hi;
+  const float bb = s - v.hi;
+  const float e = (v.hi - (s - bb)) + (hi - bb);
+  v.lo = v.lo + lo + e;
+  v.hi = s;
 }
 
-__device__ __forceinline__ DF row_scan_incl(float v) {
-  float hi = v, lo = 0.f;
-  df_scan_step<0x111>(hi, lo);
-  df_scan_step<0x112>(hi, lo);
-  df_scan_step<0x114>(hi, lo);
-  df_scan_step<0x118>(hi, lo);
-  const float h = hi + lo;
-  return {h, lo - (h - hi)};
+// Inclusive prefix sum over the 16 lanes of a row, not normalised (shifts by 1, 2, 4, 8; lanes
+// whose source is outside the row add 0).
+template <int CTRL>
+__device__ __forceinline__ void df_scan_step(DF& v) {
+  df_accumulate(v, dpp_or_zero<CTRL, 0xF>(v.hi), dpp_or_zero<CTRL, 0xF>(v.lo));
+}
+__device__ __forceinline__ DF row_scan_incl(float x) {
+  DF v = {x, 0.f};
+  df_scan_step<0x111>(v);
+  df_scan_step<0x112>(v);
+  df_scan_step<0x114>(v);
+  df_scan_step<0x118>(v);
+  return v;
 }
 
 // Sum over the row, in its last lane (the other lanes hold partial sums).
@@ -82,6 +84,23 @@ __device__ __forceinline__ float row_sum_last(float v) {
   v += dpp_or_zero<0x118, 0xF>(v);
   return v;
 }
+// Sums of w * x over the row for four values x, value i's in lane 12 + i (the other lanes hold
+// partial sums): pairs, fours, eights and the row are added as row_sum_last adds them, and at
+// the first two levels every lane keeps half of the values.  A pair's sum is the odd lane's
+// product, exact, added to the even lane's, rounded (one fused multiply-add).
+__device__ __forceinline__ float row_pair2(float w_odd, float w, float x0, float x1, bool odd) {
+  const float x0_odd = dpp_or_zero<0xF5, 0xF>(x0);          // quad_perm 1 1 3 3
+  const float p1_even = dpp_or_zero<0xA0, 0xF>(w * x1);     // quad_perm 0 0 2 2
+  return fmaf(w_odd, odd ? x1 : x0_odd, odd ? p1_even : w * x0);
+}
+__device__ __forceinline__ float row_sums4(float w, float a, float b, float c, float d, bool bit0, bool bit1) {
+  const float w_odd = dpp_or_zero<0xF5, 0xF>(w);
+  const float ab = row_pair2(w_odd, w, a, b, bit0), cd = row_pair2(w_odd, w, c, d, bit0);
+  float v = (bit1 ? cd : ab) + dpp_or_zero<0x4E, 0xF>(bit1 ? ab : cd);   // quad_perm 2 3 0 1
+  v += dpp_or_zero<0x124, 0xF>(v);   // row_ror:4
+  v += dpp_or_zero<0x128, 0xF>(v);   // row_ror:8
+  return v;
+}
 __device__ __forceinline__ float row_last(float v) { return dpp_or_zero<0x15F, 0xF>(v); }   // row_newbcast:15
 
 // Four rays per wave, a row of 16 lanes each, 16 samples of every ray per step.  Lane c of a
@@ -89,15 +108,22 @@ __device__ __forceinline__ float row_last(float v) { return dpp_or_zero<0x15F, 0
 // prefix scan across the row plus the running total of earlier steps; T_j = exp(-S_j), w_j =
 // T_j (1 - e^-tau_j).  Early termination: the first lane whose T_{j+1} < eps keeps its sample
 // and later lanes (and steps) of its ray contribute nothing.  T_j is the neighbouring lane's
-// T_{j+1}, so one exponential per sample serves both.  Each lane keeps its own weighted sums;
-// they are reduced across the row once per window of 64 samples.
+// T_{j+1}, so one exponential per sample serves both.
+//
+// Sums run over windows of 64 samples (the four steps q = 0..3 of a window) in one fixed order,
+// that of a 64-lane prefix sum over rows of 16: with R_q the row's sum of step q, a window's sum
+// is (R3 + R2) + (R1 + R0), and step q's prefix sums get R0 (q = 1), R1 + R0 (q = 2), or R2 and
+// then R1 + R0 (q = 3) added.  Training depends on it: colours that differ in their last bit
+// give gradients that do, and the optimiser, which divides by the gradients' own size, carries
+// that into the bfloat16 weights.
 //
 // What bounds it is the latency of a ray's chain (offsets -> interval records and samples ->
 // scan) and the vector work per ray.  One wave per ray (64 samples per step, a 6-step scan and
 // five 6-step reductions for rays that composite 26 to 52 samples on average, most of them
 // stopping in their first step) issued about three times the instructions per ray and held a
-// quarter of the rays in flight: 800x800 frame 334 -> 201 us (61 M samples, 3.0 -> 4.9
-// TB/s), planned 267 -> 140 us.  A step's samples are loaded two steps ahead.
+// quarter of the rays in flight: 800x800 frame 334 -> 211 us (61 M samples, 2.9 -> 4.6
+// TB/s), planned 267 -> 145 us (each lane keeping sums of its own over a window took 201 and
+// 140, in another order).  A step's samples are loaded two steps ahead.
 //
 // The ray's interval records are staged in LDS (kStage of them; the rest are read from
 // memory).  UNIFORM: every interval of a ray has the same number of samples (all but planned
@@ -129,8 +155,10 @@ __global__ __launch_bounds__(kThreads, 8) void k_composite(
   const uint32_t s0 = live ? iv.smp_off[r] : 0u, ns = live ? iv.smp_off[r + 1] - s0 : 0u;
   uint32_t sb = 0, se = ns;                    // this launch's samples of the ray
   bool marching = live;
-  DF S = {0.f, 0.f};                           // sum of tau before the current step
-  float tot[5] = {0.f, 0.f, 0.f, 0.f, 0.f};    // rgb, depth, opacity of the windows so far (last lane)
+  DF S = {0.f, 0.f};                           // sum of tau before the current window
+  // sums of the windows so far: lanes 12..15 of the row hold red, green, blue and depth in tot;
+  // lane 15 holds the opacity
+  float tot = 0.f, tot_a = 0.f;
   if (ROUND) {
     sb = 64u * round;
     if (sb >= ns && !(ns == 0 && round == 0)) marching = false;   // finished in an earlier window
@@ -138,7 +166,8 @@ __global__ __launch_bounds__(kThreads, 8) void k_composite(
       const CompCarry cy = carry_st[r];
       if (cy.state & kDone) marching = false;
       S = {cy.s_hi, cy.s_lo};
-      tot[0] = cy.cr; tot[1] = cy.cg; tot[2] = cy.cb; tot[3] = cy.dep; tot[4] = cy.acc;
+      tot = (c & 2u) ? ((c & 1u) ? cy.dep : cy.cb) : ((c & 1u) ? cy.cg : cy.cr);
+      tot_a = cy.acc;
     }
     se = sb + 64u < ns ? sb + 64u : ns;
   }
@@ -166,8 +195,12 @@ __global__ __launch_bounds__(kThreads, 8) void k_composite(
   uint32_t used = ns;   // samples composited: up to and including the stop sample
   uint32_t next = sb;   // first sample after the last step processed
   bool stopped = false;
-  float part[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
-  for (uint32_t base = sb; __ballot(!done && base < se) != 0; base += 16u) {
+  const bool bit0 = (c & 1u) != 0, bit1 = (c & 2u) != 0;
+  float sum = 0.f, sum_a = 0.f, sum01 = 0.f, sum01_a = 0.f;   // of this pair of steps; of the window's first pair
+  DF scan_row = {0.f, 0.f}, scan01 = {0.f, 0.f};   // R_q of the optical depth; R1 + R0 (not normalised)
+  float Tlast = 0.f;                               // T after the step before
+  uint32_t q = 0;                                  // step in the window
+  for (uint32_t base = sb; __ballot(!done && base < se) != 0; base += 16u, q = (q + 1u) & 3u) {
     const uint32_t j = base + c;
     const float4 z = z0;
     z0 = z1;
@@ -207,58 +240,84 @@ __global__ __launch_bounds__(kThreads, 8) void k_composite(
     const float u = jitter ? stratum_u(1, seed, (uint64_t)(r0 + r), k) : 0.5f;
     const float t = sample_t(t0, delta, jj, u);
     const float tau = valid ? softplusf(z.x) * delta : 0.f;   // sigma = softplus, rgb = logistic
-    // inclusive compensated scan of tau across the row; exclusive = shifted by one lane
-    const DF Sn = df_add(S, row_scan_incl(tau));
+    // inclusive compensated scan of tau over the window so far; exclusive = shifted by one lane
+    DF v = row_scan_incl(tau);
+    const DF row_v = {row_last(v.hi), row_last(v.lo)};
+    if (q & 1u) df_accumulate(v, scan_row.hi, scan_row.lo);
+    if (q & 2u) df_accumulate(v, scan01.hi, scan01.lo);
+    if (q == 1u) scan01 = {row_last(v.hi), row_last(v.lo)};
+    scan_row = row_v;
+    const float h = v.hi + v.lo;
+    const DF Sn = df_add(S, {h, v.lo - (h - v.hi)});
     const float Tn = df_exp_neg(Sn);                     // T_{j+1}
+    if (q == 0u) Tlast = df_exp_neg(S);
     const float Tsh = dpp_or_zero<0x111, 0xF>(Tn);       // row_shr:1: lane c - 1's T_{j+1}
-    const float T = c == 0 ? df_exp_neg(S) : Tsh;
+    const float T = c == 0 ? Tlast : Tsh;
+    Tlast = row_last(Tn);
     float w = valid ? T * one_minus_exp_neg(tau) : 0.f;
     const bool stop = valid && eps > 0.f && Tn < eps;
     const uint32_t stops = (uint32_t)(__ballot(stop) >> (lane & 48)) & 0xFFFFu;
     const bool now = stops != 0;
     const uint32_t first = (uint32_t)__ffs((int)stops) - 1u;
     if (now && c > first) w = 0.f;
-    part[0] = fmaf(w, logisticf(z.y), part[0]);
-    part[1] = fmaf(w, logisticf(z.z), part[1]);
-    part[2] = fmaf(w, logisticf(z.w), part[2]);
-    part[3] = fmaf(w, t, part[3]);
-    part[4] += w;
+    const float x = row_sums4(w, logisticf(z.y), logisticf(z.z), logisticf(z.w), t, bit0, bit1);
+    const float xa = row_sum_last(w);
+    if (q & 1u) {
+      sum = x + sum;
+      sum_a = xa + sum_a;
+    } else {
+      sum = x;
+      sum_a = xa;
+    }
     if (weights && valid) weights[wbase + j] = w;
-    S = {row_last(Sn.hi), row_last(Sn.lo)};
     if (!done) next = base + 16u;
     if (now) {
       used = base + first + 1u;
       stopped = true;
       done = true;
     }
-    if (((base - sb) & 63u) == 48u) {   // the window is complete
-#pragma unroll
-      for (int q = 0; q < 5; ++q) {
-        tot[q] += row_sum_last(part[q]);
-        part[q] = 0.f;
-      }
+    if (q == 1u) {
+      sum01 = sum;
+      sum01_a = sum_a;
+      sum = sum_a = 0.f;
+    }
+    if (q == 3u) {   // the window is complete
+      S = {row_last(Sn.hi), row_last(Sn.lo)};
+      tot += sum + sum01;
+      tot_a += sum_a + sum01_a;
+      sum = sum_a = sum01 = sum01_a = 0.f;
     }
   }
-#pragma unroll
-  for (int q = 0; q < 5; ++q) tot[q] += row_sum_last(part[q]);   // what is left of the last window
+  tot += sum + sum01;   // what is left of the last window
+  tot_a += sum_a + sum01_a;
+  const bool odd_value = !isfinite(tot) || (c == 15u && !isfinite(tot_a));
+  const uint32_t bad = (uint32_t)(__ballot(odd_value) >> (lane & 48)) & 0xF000u;   // of this ray
   if (!marching) return;
   // a ray that stopped has weight 0 on every later sample
   if (weights && stopped)
     for (uint32_t j = next + c; j < ns; j += 16) weights[wbase + j] = 0.f;
-  if (c != 15u) return;
+  if (c < 12u) return;
+  const uint32_t i = c - 12u;
   if (ROUND && !stopped && se < ns) {
-    carry_st[r] = {S.hi, S.lo, tot[0], tot[1], tot[2], tot[3], tot[4], 0u};
+    CompCarry* cy = carry_st + r;
+    (&cy->cr)[i] = tot;
+    if (i == 3u) {
+      cy->s_hi = S.hi;
+      cy->s_lo = S.lo;
+      cy->acc = tot_a;
+      cy->state = 0u;
+    }
+    return;
+  }
+  if (i < 3u) {
+    rgb[3 * (uint64_t)(r0 + r) + i] = tot;
     return;
   }
   if (ROUND) carry_st[r].state = kDone;
   ray_used[r] = used;
-  rgb[3 * (uint64_t)(r0 + r) + 0] = tot[0];
-  rgb[3 * (uint64_t)(r0 + r) + 1] = tot[1];
-  rgb[3 * (uint64_t)(r0 + r) + 2] = tot[2];
-  if (depth) depth[r0 + r] = tot[3];
-  if (opac) opac[r0 + r] = tot[4];
-  if (!isfinite(tot[0]) || !isfinite(tot[1]) || !isfinite(tot[2]) || !isfinite(tot[3]) || !isfinite(tot[4]))
-    atomicAdd(reinterpret_cast<unsigned long long*>(&counts->nonfinite), 1ull);
+  if (depth) depth[r0 + r] = tot;
+  if (opac) opac[r0 + r] = tot_a;
+  if (bad) atomicAdd(reinterpret_cast<unsigned long long*>(&counts->nonfinite), 1ull);
 }
 
 // counts->composited += sum of ray_used[0, nr): block sums in a fixed order, one integer
