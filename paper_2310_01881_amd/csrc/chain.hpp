@@ -40,13 +40,15 @@ __device__ __forceinline__ uint64_t chain_prefix(uint64_t* state, uint32_t blk, 
   int64_t at = (int64_t)blk - 1;
   while (true) {
     const int64_t i = at - lane;
-    const uint64_t s = i >= 0 ? __hip_atomic_load(&state[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : kChainPrefix;
-    const uint64_t full = __ballot((s >> 62) == 2u), none = __ballot((s >> 62) == 0u);
-    // lanes up to the nearest block whose prefix is known (all 64 if there is none)
-    const uint64_t need = full ? (((full & (~full + 1ull)) << 1) - 1ull) : ~0ull;
-    if (none & need) {
-      __builtin_amdgcn_s_sleep(1);
-      continue;
+    uint64_t s = i >= 0 ? 0ull : kChainPrefix;
+    uint64_t full, need;
+    while (true) {
+      if ((s >> 62) == 0u) s = __hip_atomic_load(&state[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      full = __ballot((s >> 62) == 2u);
+      // lanes up to the nearest block whose prefix is known (all 64 if there is none)
+      need = full ? (((full & (~full + 1ull)) << 1) - 1ull) : ~0ull;
+      if ((__ballot((s >> 62) == 0u) & need) == 0) break;
+      __builtin_amdgcn_s_sleep(2);
     }
     before += wave_sum_u64((need >> lane) & 1ull ? s & kChainValue : 0ull);
     if (full) break;
