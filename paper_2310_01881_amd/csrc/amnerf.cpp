@@ -1059,13 +1059,13 @@ static int check_proposal(const amnerf_render_params* p) {
 // on demand.  Otherwise it is the static_bytes of static_ws (the allocation-free entry
 // point): the call must then fit one pass and that workspace, and runs no proposal or
 // empty-space selection (their buffers are sized on the host from a measured count).
-// keep_samples: a backward pass follows for certain, which reads the sample records, so the MLPs
+// in_step: a backward pass follows for certain, which reads the sample records, so the MLPs
 // may as well (a training step with its MLPs on the sorted intervals and the records written
 // afterwards took 1 % longer).
 static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_mlp* mlp,
                        const amnerf_rays* rays, const amnerf_render_params* p,
                        amnerf_render_out* out, void* stream, char* static_ws, size_t static_bytes,
-                       bool keep_samples) {
+                       bool in_step) {
   if (!ctx || !tree || !mlp || !rays || !p || !out) return fail(AMNERF_EINVAL, "amnerf_render: null argument");
   MlpGeom g;
   int rc = check_geom(&mlp->shape, mlp->dtype, &g, "amnerf_render");
@@ -1126,7 +1126,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
   // 4 bytes per possible interval more).  Expanding first: 800x800 frame 2.38 against 2.08 ms,
   // 64x64 87 against 54 us, 1920x1080 float8 7.01 against 6.00 ms (with the scans in one launch
   // each).
-  bool fused = !rounds && !jitter && !keep_samples;
+  bool fused = !rounds && !jitter && !in_step;
   SortPlan sp = make_sort_plan(niv_max, L, fused);
   size_t need = carve(nullptr, chunk, niv_max, ns_max, sp, w0, rounds, fused);
   if (fused && ((static_ws && need > static_bytes) ||
@@ -1281,7 +1281,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
     if (!rounds) {
       const RowSource rows = {sb.rec, sb.ssb, sb.win, w.srec_ray, w.srec_t, w.perm};
       HIP_TRY(launch_mlp(g, mlp->packed_dev, L, w.bucket_off, w.tile_off, cc, rows, rays->o_dev, rays->d_dev, R, r0,
-                         w.smp_out, cs));
+                         w.smp_out, in_step, cs));
       HIP_TRY(mark(5));
       HIP_TRY(launch_composite(nr, use, !wait_count, w.smp_out, r0, jitter, p->jitter_seed, p->ert_eps, out->rgb_dev,
                                out->depth_dev, out->opacity_dev, out->weights_dev, w.ray_used, cc, cs));
@@ -1299,7 +1299,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
         HIP_TRY(launch_round_tiles(w.bucket_off, w.r_pos, L, w.c_boff, w.c_toff, cc, cs));
         const RowSource rows = {nullptr, nullptr, nullptr, w.c_ray, w.c_t, w.c_perm};
         HIP_TRY(launch_mlp(g, mlp->packed_dev, L, w.c_boff, w.c_toff, cc, rows, rays->o_dev, rays->d_dev, R, r0, w.smp_out,
-                           cs));
+                           in_step, cs));
         if (k + 1 == n_rounds) HIP_TRY(mark(5));
         HIP_TRY(launch_composite_round(nr, use, !wait_count, w.smp_out, r0, jitter, p->jitter_seed, p->ert_eps, out->rgb_dev,
                                        out->depth_dev, out->opacity_dev, out->weights_dev, w.ray_used, cc, w.carry,

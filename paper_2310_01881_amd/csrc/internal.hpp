@@ -177,10 +177,11 @@ hipError_t persistent_grid(const void* kern, int threads, uint32_t lds, int* gri
 
 hipError_t launch_mlp_pack(const MlpGeom& g, int n_leaves, const float* master, void* packed,
                            hipStream_t st);
+// in_step: the forward pass of a training step.
 hipError_t launch_mlp(const MlpGeom& g, const void* packed, uint32_t n_leaves,
                       const uint32_t* bucket_off, const uint32_t* tile_off,
                       const ChunkCounts* counts, const RowSource& rows, const float* o, const float* d,
-                      int64_t ray_stride, int64_t r0, float* out, hipStream_t st);
+                      int64_t ray_stride, int64_t r0, float* out, bool in_step, hipStream_t st);
 
 // ---- float32 leaf MLPs on the bfloat16 matrix cores (values split in three) ----------------
 // Whether the split weights of a leaf fit a compute unit's LDS (n_hidden <= 7 at hidden 64).

@@ -587,7 +587,7 @@ hipError_t launch_mlp_pack(const MlpGeom& g, int n_leaves, const float* master, 
 
 hipError_t launch_mlp(const MlpGeom& g, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
                       const uint32_t* tile_off, const ChunkCounts* counts, const RowSource& rows, const float* o,
-                      const float* d, int64_t ray_stride, int64_t r0, float* out, hipStream_t st) {
+                      const float* d, int64_t ray_stride, int64_t r0, float* out, bool in_step, hipStream_t st) {
   if (g.dtype == AMNERF_FP8_ACT)
     return launch_mlp8(g.n_hidden, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
   Layout L = make_layout(g.n_hidden, g.hidden, g.dtype);
@@ -600,10 +600,14 @@ hipError_t launch_mlp(const MlpGeom& g, const void* packed, uint32_t n_leaves, c
     return launch_typed<32, true>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
   }
   // float32: the split kernel (twice as fast) wherever its weights fit a compute unit's LDS,
-  // which leaves 8 layers of 64 to the float32 matrix instructions
-  if (mlp32_fits(g.n_hidden, g.hidden))
+  // which leaves 8 layers of 64 to the float32 matrix instructions.  A training step keeps
+  // those too: its backward pass recomputes the activations with them, and what differs in the
+  // last bit between the two (1e-7) an optimiser that divides by the gradients' size carries
+  // into the weights (after two steps some gradients differed by 2e-2 of their size).
+  if (!in_step && mlp32_fits(g.n_hidden, g.hidden))
     return launch_mlp32(g.n_hidden, g.hidden, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
-  return launch_typed<64, false>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
+  if (g.hidden == 64) return launch_typed<64, false>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
+  return launch_typed<32, false>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
 }
 
 }  // namespace amn
