@@ -1506,6 +1506,20 @@ size_t carve_bwd(char* base, uint64_t ns, uint64_t L, uint64_t nseg, uint64_t P,
   return c.off + 256;
 }
 
+// Tiles per backward segment: 16; fewer in float32 where the batch (ns possible samples) would
+// give the chip's 1024 block slots fewer than two segments each: 16 384 rays' backward (0.8 M
+// samples, 2x32 wide: 230 segments) took 556 us, 296 with 4 tiles.  Every segment writes its own
+// partial gradient, so shorter ones cost memory and a longer reduction (4 -> 9 us there); a
+// context with a memory cap keeps the longest, so that what fits its cap does not depend on
+// this.  bfloat16 passes and training steps keep 16 always: their sums stay in one order, whose
+// last bits an optimiser carries into the weights.
+uint32_t seg_tiles_for(const amnerf_ctx* ctx, uint64_t ns, int32_t dtype, bool in_step) {
+  uint32_t t = kSegTiles;
+  while (dtype == AMNERF_F32 && !in_step && !ctx->cap && t > 1 && ns / kMlpTileRows < 2048ull * t) t /= 2;
+  return t;
+}
+uint64_t seg_count_max(uint64_t ns, uint64_t L, uint32_t seg_tiles) { return (ns / kMlpTileRows + L) / seg_tiles + L; }
+
 // in_step: called by a training step, whose backward stage events (stage 0 already marked)
 // are ev, null when timing is off; a backward pass alone takes an event set of its own when
 // timing is on.
@@ -1536,10 +1550,10 @@ int backward_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_mlp* ml
   const uint64_t L = (uint64_t)ctx->last_leaves;   // parameter sets of that render
   const uint64_t P = (uint64_t)amnerf_mlp_param_count(&mlp->shape);
   const uint64_t ns = ctx->last_ns_max, R = (uint64_t)rays->n_rays;
-  const uint64_t tiles = ns / kMlpTileRows + L;
-  const uint64_t nseg = tiles / kSegTiles + L;
+  const uint32_t seg_tiles = seg_tiles_for(ctx, ns, mlp->dtype, in_step);
+  const uint64_t nseg = seg_count_max(ns, L, seg_tiles);
   BwdWork w;
-  size_t need = carve_bwd(nullptr, ns, L, nseg, P, R, w);
+  const size_t need = carve_bwd(nullptr, ns, L, nseg, P, R, w);
   rc = ensure_arena2(ctx, need);
   if (rc) return rc;
   carve_bwd((char*)ctx->arena2, ns, L, nseg, P, R, w);
@@ -1559,9 +1573,10 @@ int backward_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_mlp* ml
   HIP_TRY(launch_comp_bwd(nr, ctx->use, ctx->smp_out, 0, jitter, p.jitter_seed, ctx->ray_used, g_rgb, g_depth,
                           g_opac, w.gpre, st));
   HIP_TRY(mark(AMNERF_BWD_STAGE_MLP));
-  HIP_TRY(launch_seg_offsets(ctx->tile_off, (uint32_t)L, w.seg_off, st));
+  HIP_TRY(launch_seg_offsets(ctx->tile_off, (uint32_t)L, seg_tiles, w.seg_off, st));
   HIP_TRY(launch_mlp_bwd(g, mlp->packed_dev, (uint32_t)L, ctx->bucket_off, ctx->tile_off, w.seg_off, ctx->srec_ray,
-                         ctx->srec_t, ctx->perm, rays->o_dev, rays->d_dev, rays->n_rays, 0, w.gpre, w.part, st));
+                         ctx->srec_t, ctx->perm, rays->o_dev, rays->d_dev, rays->n_rays, 0, w.gpre, w.part, seg_tiles,
+                         st));
   HIP_TRY(mark(AMNERF_BWD_STAGE_REDUCE));
   HIP_TRY(launch_grad_reduce(w.part, w.seg_off, (uint32_t)L, (uint32_t)P, grad, st));
   HIP_TRY(mark(AMNERF_BWD_STAGE_ADAM));
@@ -1672,7 +1687,7 @@ extern "C" int amnerf_train_step(amnerf_ctx* ctx, const amnerf_tree* tree, amner
     if (R > chunk) return fail(AMNERF_ECAPACITY, "amnerf_train_step: %llu rays exceed one pass (%llu)",
                                (unsigned long long)R, (unsigned long long)chunk);
     const uint64_t ns = std::max<uint64_t>(R, 1) * (uint64_t)std::max(1, p->render.s_max);
-    const uint64_t nseg = (ns / kMlpTileRows + L) / kSegTiles + L;
+    const uint64_t nseg = seg_count_max(ns, L, seg_tiles_for(ctx, ns, dtype, true));
     int rc = ensure_arena2(ctx, carve_bwd(nullptr, ns, L, nseg, P, R, w));
     if (rc) return rc;
     carve_bwd((char*)ctx->arena2, ns, L, nseg, P, R, w);

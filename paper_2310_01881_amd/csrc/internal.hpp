@@ -47,7 +47,7 @@ struct CompCarry {
 };
 
 constexpr int kMlpTileRows = 256;       // rows of one MLP work tile (4 waves x 64)
-constexpr int kSegTiles = 16;           // tiles per backward work segment (one leaf)
+constexpr uint32_t kSegTiles = 16;      // tiles per backward work segment (one leaf), at most
 constexpr int kScanItems = 2048;        // elements per scan block (256 threads x 8)
 
 // ---- traversal (Algorithm 1: Traverse) -------------------------------------------------
@@ -248,11 +248,13 @@ hipError_t launch_comp_bwd(uint32_t nr, const IvSet& iv, const float* smp_out, i
                            const float* g_opac, float* gpre, hipStream_t st);
 // seg_off: n_leaves + 2 words; the last is the bfloat16 backward's segment queue, which
 // launch_seg_offsets resets to 0 and launch_mlp_bwd advances.
-hipError_t launch_seg_offsets(const uint32_t* tile_off, uint32_t n_leaves, uint32_t* seg_off, hipStream_t st);
+hipError_t launch_seg_offsets(const uint32_t* tile_off, uint32_t n_leaves, uint32_t seg_tiles, uint32_t* seg_off,
+                              hipStream_t st);
 hipError_t launch_mlp_bwd(const MlpGeom& g, const void* packed, uint32_t n_leaves, const uint32_t* bucket_off,
                           const uint32_t* tile_off, uint32_t* seg_off, const uint32_t* srec_ray,
                           const float* srec_t, const uint32_t* perm, const float* o, const float* d,
-                          int64_t ray_stride, int64_t r0, const float* gpre, float* part, hipStream_t st);
+                          int64_t ray_stride, int64_t r0, const float* gpre, float* part, uint32_t seg_tiles,
+                          hipStream_t st);
 hipError_t launch_grad_reduce(const float* part, const uint32_t* seg_off, uint32_t n_leaves, uint32_t P,
                               float* grad, hipStream_t st);
 size_t loss_partial_words(uint64_t R);

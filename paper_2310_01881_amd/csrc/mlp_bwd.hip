@@ -1,7 +1,7 @@
 // mlp_bwd.hip -- backward pass of the grouped per-leaf MLP (bfloat16 operands, float32
 // accumulation), the differentiable counterpart of the grouped forward in mlp.hip.
 //
-// Work item: a segment of at most kSegTiles consecutive 256-row tiles of one leaf, each
+// Work item: a segment of at most seg_tiles consecutive 256-row tiles of one leaf, each
 // processed by a block of 16 waves (4 per SIMD: one block fills a compute unit), 16 rows per
 // wave.  Every wave recomputes its forward activations (none are stored between the forward
 // and backward passes) and keeps each layer's bfloat16 input in registers in B-operand
@@ -60,7 +60,7 @@ __global__ __launch_bounds__(kThreadsB) void k_mlp_bwd(
     const uint32_t* __restrict__ srec_ray, const float* __restrict__ srec_t,
     const uint32_t* __restrict__ perm, const float* __restrict__ o, const float* __restrict__ d,
     int64_t stride, int64_t r0, const float* __restrict__ gpre, float* __restrict__ part, int P,
-    uint32_t* __restrict__ seg_queue) {
+    uint32_t* __restrict__ seg_queue, uint32_t seg_tiles) {
   extern __shared__ __align__(16) uint8_t lds[];
   constexpr int RB = H / 16;
   constexpr int KUh = H / 32;
@@ -109,8 +109,8 @@ __global__ __launch_bounds__(kThreadsB) void k_mlp_bwd(
       if (seg_off[mid] <= seg) lo = mid; else hi = mid;
     }
     const uint32_t b = lo;
-    const uint32_t t_first = tile_off[b] + (seg - seg_off[b]) * kSegTiles;
-    const uint32_t t_last = t_first + kSegTiles < tile_off[b + 1] ? t_first + kSegTiles : tile_off[b + 1];
+    const uint32_t t_first = tile_off[b] + (seg - seg_off[b]) * seg_tiles;
+    const uint32_t t_last = t_first + seg_tiles < tile_off[b + 1] ? t_first + seg_tiles : tile_off[b + 1];
     if ((int)b != cur) {
       __syncthreads();
       const f32x4* s1 = reinterpret_cast<const f32x4*>(packed_fwd + (uint64_t)b * L.bytes);
@@ -371,7 +371,7 @@ __global__ __launch_bounds__(kThreads) void k_mlp_bwd_f32(
     const uint32_t* __restrict__ tile_off, const uint32_t* __restrict__ seg_off,
     const uint32_t* __restrict__ srec_ray, const float* __restrict__ srec_t, const uint32_t* __restrict__ perm,
     const float* __restrict__ o, const float* __restrict__ d, int64_t stride, int64_t r0,
-    const float* __restrict__ gpre, float* __restrict__ part, int P) {
+    const float* __restrict__ gpre, float* __restrict__ part, int P, uint32_t seg_tiles) {
   extern __shared__ __align__(16) uint8_t lds[];
   constexpr int RB = H / 16;
   const float* bias = reinterpret_cast<const float*>(lds);
@@ -389,8 +389,8 @@ __global__ __launch_bounds__(kThreads) void k_mlp_bwd_f32(
       if (seg_off[mid] <= seg) lo = mid; else hi = mid;
     }
     const uint32_t b = lo;
-    const uint32_t t_first = tile_off[b] + (seg - seg_off[b]) * kSegTiles;
-    const uint32_t t_last = t_first + kSegTiles < tile_off[b + 1] ? t_first + kSegTiles : tile_off[b + 1];
+    const uint32_t t_first = tile_off[b] + (seg - seg_off[b]) * seg_tiles;
+    const uint32_t t_last = t_first + seg_tiles < tile_off[b + 1] ? t_first + seg_tiles : tile_off[b + 1];
     if ((int)b != cur) {
       __syncthreads();
       const f32x4* src = reinterpret_cast<const f32x4*>(packed + (uint64_t)b * L.bytes);
@@ -561,7 +561,7 @@ hipError_t launch_bwd_f32_typed(const Layout& L, const void* packed, uint32_t n_
                                 const uint32_t* bucket_off, const uint32_t* tile_off,
                                 const uint32_t* seg_off, const uint32_t* srec_ray, const float* srec_t,
                                 const uint32_t* perm, const float* o, const float* d, int64_t stride,
-                                int64_t r0, const float* gpre, float* part, hipStream_t st) {
+                                int64_t r0, const float* gpre, float* part, uint32_t seg_tiles, hipStream_t st) {
   auto kern = k_mlp_bwd_f32<H, NH>;
   const uint32_t lds = L.bytes + 2u * H * kRowF * 4u;
   int grid = 0;
@@ -569,7 +569,7 @@ hipError_t launch_bwd_f32_typed(const Layout& L, const void* packed, uint32_t n_
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), lds, st, L, (const uint8_t*)packed, n_leaves,
                      bucket_off, tile_off, seg_off, srec_ray, srec_t, perm, o, d, stride, r0, gpre, part,
-                     master_param_count(NH, H));
+                     master_param_count(NH, H), seg_tiles);
   return hipGetLastError();
 }
 
@@ -578,7 +578,7 @@ hipError_t launch_bwd_typed(const Layout& L, const void* packed, uint32_t n_leav
                             const uint32_t* bucket_off, const uint32_t* tile_off,
                             uint32_t* seg_off, const uint32_t* srec_ray, const float* srec_t,
                             const uint32_t* perm, const float* o, const float* d, int64_t stride,
-                            int64_t r0, const float* gpre, float* part, hipStream_t st) {
+                            int64_t r0, const float* gpre, float* part, uint32_t seg_tiles, hipStream_t st) {
   auto kern = k_mlp_bwd<H, NH>;
   const uint32_t lds = L.bytes + L.bwd_bytes + 2u * H * kRowBytes + 16u;   // + the queue word
   int grid = 0;
@@ -588,7 +588,7 @@ hipError_t launch_bwd_typed(const Layout& L, const void* packed, uint32_t n_leav
   const uint8_t* pb = pf + (uint64_t)n_leaves * L.bytes;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreadsB), lds, st, L, pf, pb, n_leaves, bucket_off, tile_off,
                      seg_off, srec_ray, srec_t, perm, o, d, stride, r0, gpre, part,
-                     master_param_count(NH, H), seg_off + n_leaves + 1);
+                     master_param_count(NH, H), seg_off + n_leaves + 1, seg_tiles);
   return hipGetLastError();
 }
 
@@ -602,15 +602,15 @@ hipError_t launch_mlp_bwd(const MlpGeom& g, const void* packed, uint32_t n_leave
                           const uint32_t* bucket_off, const uint32_t* tile_off, uint32_t* seg_off,
                           const uint32_t* srec_ray, const float* srec_t, const uint32_t* perm,
                           const float* o, const float* d, int64_t ray_stride, int64_t r0,
-                          const float* gpre, float* part, hipStream_t st) {
+                          const float* gpre, float* part, uint32_t seg_tiles, hipStream_t st) {
   Layout L = make_layout(g.n_hidden, g.hidden, g.dtype);
 #define AMN_BWD(HH, NN)                                                                                \
   if (g.hidden == HH && g.n_hidden == NN) {                                                            \
     if (g.dtype == AMNERF_F32)                                                                         \
       return launch_bwd_f32_typed<HH, NN>(L, packed, n_leaves, bucket_off, tile_off, seg_off, srec_ray, \
-                                          srec_t, perm, o, d, ray_stride, r0, gpre, part, st);        \
+                                          srec_t, perm, o, d, ray_stride, r0, gpre, part, seg_tiles, st); \
     return launch_bwd_typed<HH, NN>(L, packed, n_leaves, bucket_off, tile_off, seg_off, srec_ray,       \
-                                    srec_t, perm, o, d, ray_stride, r0, gpre, part, st);              \
+                                    srec_t, perm, o, d, ray_stride, r0, gpre, part, seg_tiles, st);   \
   }
   AMN_BWD(64, 4)
   AMN_BWD(64, 3)

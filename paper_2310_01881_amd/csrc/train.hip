@@ -150,16 +150,17 @@ __global__ __launch_bounds__(kThreads) void k_comp_bwd(
     *reinterpret_cast<float4*>(gpre + 4 * (uint64_t)(s0 + j)) = float4{0.f, 0.f, 0.f, 0.f};
 }
 
-// Segments of at most kSegTiles tiles per leaf: seg_off[b] (exclusive scan) and the total.
+// Segments of at most seg_tiles tiles per leaf: seg_off[b] (exclusive scan) and the total.
 __global__ __launch_bounds__(1024) void k_seg_offsets(const uint32_t* __restrict__ tile_off,
-                                                      uint32_t n_leaves, uint32_t* __restrict__ seg_off) {
+                                                      uint32_t n_leaves, uint32_t seg_tiles,
+                                                      uint32_t* __restrict__ seg_off) {
   __shared__ uint32_t sh[16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t carry = 0;
   for (uint32_t c = 0; c < n_leaves; c += 1024) {
     const uint32_t b = c + threadIdx.x;
     const uint32_t nt = b < n_leaves ? tile_off[b + 1] - tile_off[b] : 0u;
-    const uint32_t ns = (nt + kSegTiles - 1) / kSegTiles;
+    const uint32_t ns = (nt + seg_tiles - 1) / seg_tiles;
     uint32_t x = ns;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -273,8 +274,9 @@ hipError_t launch_comp_bwd(uint32_t nr, const IvSet& iv, const float* smp_out, i
   return hipGetLastError();
 }
 
-hipError_t launch_seg_offsets(const uint32_t* tile_off, uint32_t n_leaves, uint32_t* seg_off, hipStream_t st) {
-  hipLaunchKernelGGL(k_seg_offsets, dim3(1), dim3(1024), 0, st, tile_off, n_leaves, seg_off);
+hipError_t launch_seg_offsets(const uint32_t* tile_off, uint32_t n_leaves, uint32_t seg_tiles, uint32_t* seg_off,
+                              hipStream_t st) {
+  hipLaunchKernelGGL(k_seg_offsets, dim3(1), dim3(1024), 0, st, tile_off, n_leaves, seg_tiles, seg_off);
   return hipGetLastError();
 }
 
