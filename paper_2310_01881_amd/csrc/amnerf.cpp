@@ -1508,7 +1508,7 @@ size_t carve_bwd(char* base, uint64_t ns, uint64_t L, uint64_t nseg, uint64_t P,
 
 // Tiles per backward segment: 16; fewer in float32 where the batch (ns possible samples) would
 // give the chip's 1024 block slots fewer than two segments each: 16 384 rays' backward (0.8 M
-// samples, 2x32 wide: 230 segments) took 556 us, 296 with 4 tiles.  Every segment writes its own
+// samples, 4 layers of 32: 230 segments) took 556 us, 296 with 4 tiles.  Every segment writes its own
 // partial gradient, so shorter ones cost memory and a longer reduction (4 -> 9 us there); a
 // context with a memory cap keeps the longest, so that what fits its cap does not depend on
 // this.  bfloat16 passes and training steps keep 16 always: their sums stay in one order, whose

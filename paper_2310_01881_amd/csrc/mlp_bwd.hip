@@ -2,19 +2,24 @@
 // accumulation), the differentiable counterpart of the grouped forward in mlp.hip.
 //
 // Work item: a segment of at most seg_tiles consecutive 256-row tiles of one leaf, each
-// processed by a block of 16 waves (4 per SIMD: one block fills a compute unit), 16 rows per
-// wave.  Every wave recomputes its forward activations (none are stored between the forward
-// and backward passes) and keeps each layer's bfloat16 input in registers in B-operand
-// order.  Then, from the output layer down:
+// processed by a block of 8 waves (2 per SIMD: one block fills a compute unit), 32 rows per
+// wave in two column blocks that share every weight read.  Every wave recomputes its forward
+// activations (none are stored between the forward and backward passes) and keeps each layer's
+// bfloat16 input in registers in B-operand order.  Then, from the output layer down:
 //   * dZ_l (gradient at layer l's pre-activation) and the layer's input H_{l-1} are staged
-//     feature-major in LDS ([feature][256 samples], rows padded by 16 bytes), and the
-//     waves accumulate dW_l = sum_samples dZ_l H_{l-1}^T on MFMA with K = samples (and
-//     db_l = sum_samples dZ_l against a ones operand);
+//     in LDS, a row per sample, and the waves accumulate dW_l = sum_samples dZ_l H_{l-1}^T on
+//     MFMA with K = samples (and db_l = sum_samples dZ_l against a ones operand), their
+//     operands coming from transposed LDS reads;
 //   * dH_{l-1} = W_l^T dZ_l runs on MFMA in registers (transposed weights packed in the
 //     same register-chained order as the forward), then dZ_{l-1} = dH_{l-1} where the
 //     forward activation was positive.
 // Each segment writes its partial dW, db (master layout) to its own slot; a separate
 // kernel sums the slots of each leaf in order, so the gradient is deterministic.
+//
+// What bounds it is LDS traffic and the waits between the phases of a layer.  With 16 waves of
+// 16 rows that staged feature-major, every value was a 2-byte write and every weight fragment
+// was read twice as often: 4.70 ms for a 262 144-ray training batch (23 M samples, 4 layers of
+// 64), 3.67 now, every sum in the same order.
 #include "internal.hpp"
 #include "devcommon.hpp"
 #include "mlp_layout.hpp"
@@ -23,37 +28,57 @@ namespace amn {
 namespace {
 
 constexpr int kThreads = 256;                    // the float32 kernel's block
-constexpr int kWavesB = 16;                      // waves of a bfloat16 block (4 per SIMD)
+constexpr int kWavesB = 8;                       // waves of a bfloat16 block (2 per SIMD)
 constexpr int kThreadsB = 64 * kWavesB;
-constexpr int kNCB = 1;                          // 16-sample column blocks per wave
-constexpr int kTileRows = kMlpTileRows;          // 256-row tiles of the forward pass, each
-constexpr int kSubRows = kWavesB * 16 * kNCB;    // processed as one sub-tile of 16 rows per wave
-constexpr int kSubPerTile = kTileRows / kSubRows;
-static_assert(kTileRows % kSubRows == 0, "sub-tiles must divide a tile");
-constexpr int kRowBytes = kSubRows * 2 + 16;     // staged feature row (bf16) + padding
-static_assert(kWavesB == 16, "the weight-gradient ownership below assumes 16 waves");
+constexpr int kNCB = 2;                          // 16-sample column blocks per wave
+constexpr int kTileRows = kMlpTileRows;          // 256-row tiles of the forward pass, one
+static_assert(kWavesB * 16 * kNCB == kTileRows, "a tile is one step of the block");   // step each
+constexpr int kRowBytes = 128;                   // staged sample (bf16 features)
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // Weight-gradient ownership, fixed so that every sum is taken in one order.  Below the
-// output layer, dW_l is cut into 32x32 blocks (rows: outputs; columns: staged inputs), one
-// wave each, accumulated with 32x32x16 MFMAs over the sub-tile's samples: the layers take
-// waves in the order 1, 2, .., NH - 1, 0 (slot li), (H/32)^2 waves apiece.  db_l's 16-row
-// blocks go to 16x16x32 MFMAs against a ones operand on waves 8 + li H/16 + j (mod 16),
-// which never hold a dW block of the same layer, and each hold one layer's.  The output
-// layer (its outputs padded to 16 rows) keeps 16x16 blocks: column block ci on wave ci,
-// its db on wave 0.
+// output layer, dW_l is cut into 32x32 blocks (rows: outputs; columns: staged inputs),
+// accumulated with 32x32x16 MFMAs over the tile's samples.  The blocks of the layers in the
+// order 1, 2, .., NH - 1, 0 are dealt to the waves in turn, (H/32)^2 a layer, so a wave holds
+// at most two and never two of one layer.  db_l's 16-row blocks go to 16x16x32 MFMAs against
+// a ones operand, dealt in turn too, to waves that hold no dW block of the layer and at most
+// two a wave.  The output layer (its outputs padded to 16 rows) keeps 16x16 blocks: column
+// block ci on wave ci, its db on the last wave.
 __device__ __forceinline__ constexpr int bwd_slot(int NH, int l) { return l >= 1 ? l - 1 : NH - 1; }
-
-__device__ __forceinline__ void stage(uint8_t* base, int row, int col, __bf16 v) {
-  *reinterpret_cast<__bf16*>(base + row * kRowBytes + col * 2) = v;
+__device__ __forceinline__ constexpr int bwd_first_block(int H, int NH, int l) {
+  return bwd_slot(NH, l) * (H / 32) * (H / 32);
 }
+
+// Staged samples are rows of kRowBytes whose sixteen 8-byte pieces are permuted by an exclusive
+// or with the low bits of the sample's number, reordered to s1 s3 s2 s0.  A wave's 8-byte write
+// takes 16 lanes at a time (32 banks): 16 samples, the same piece, which all four bits spread.  A
+// transposed read takes 32 lanes (64 banks): eight pieces of four samples in a row, which s0
+// (a row is half the banks) and s1 spread, or four pieces of samples 0..3 and 8..11, which s0,
+// s1 and s3 spread.  Neither has a bank conflict; with 32-byte pieces permuted the writes took
+// 16 cycles instead of 4.
+__device__ __forceinline__ uint32_t stage_swz(uint32_t s) {
+  return (s & 2u) << 5 ^ (s & 8u) << 2 ^ (s & 4u) << 2 ^ (s & 1u) << 3;
+}
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+// Eight samples of one feature from two transposed reads: each lane group of 16 reads a
+// 4-sample x 16-feature block, lane i receiving feature i of the four samples.
+__device__ __forceinline__ bf16x8 read_tr(const uint8_t* p0, const uint8_t* p1) {
+  typedef __attribute__((address_space(3))) s16x4* lds_ptr;
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)p0);
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)p1);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
 __device__ __forceinline__ bool pos_bf16(__bf16 v) {
   return __builtin_bit_cast(short, v) > 0;
 }
 
 template <int H, int NH>
-__global__ __launch_bounds__(kThreadsB) void k_mlp_bwd(
+__global__ __launch_bounds__(kThreadsB, 2) void k_mlp_bwd(
     Layout L, const uint8_t* __restrict__ packed_fwd, const uint8_t* __restrict__ packed_bwd,
     uint32_t n_leaves, const uint32_t* __restrict__ bucket_off,
     const uint32_t* __restrict__ tile_off, const uint32_t* __restrict__ seg_off,
@@ -64,36 +89,58 @@ __global__ __launch_bounds__(kThreadsB) void k_mlp_bwd(
   extern __shared__ __align__(16) uint8_t lds[];
   constexpr int RB = H / 16;
   constexpr int KUh = H / 32;
+  constexpr int kBig = 2, kBias = 2;                         // blocks a wave holds at most
   uint8_t* w_fwd = lds;
   uint8_t* w_bwd = lds + L.bytes;
-  uint8_t* s_dz = w_bwd + L.bwd_bytes;
-  uint8_t* s_h = s_dz + H * kRowBytes;
-  uint32_t& s_seg = *reinterpret_cast<uint32_t*>(s_h + H * kRowBytes);   // the segment taken
+  uint8_t* s_dz = w_bwd + L.bwd_bytes;                       // H = 32: gradients and inputs share rows
+  uint32_t& s_seg = *reinterpret_cast<uint32_t*>(s_dz + (H == 64 ? 2 : 1) * kTileRows * kRowBytes);   // the segment taken
   const float* bias = reinterpret_cast<const float*>(w_fwd);
   const uint8_t* units = w_fwd + L.bias_bytes;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, m = lane & 15;
   bf16x8 ones;
 #pragma unroll
   for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.f;
-  // this wave's blocks (see above) and the byte offsets of its operand fragments in the
-  // staged rows, which are the same for every layer
+  // this wave's blocks (see above)
   const int h32 = lane >> 5, c32 = lane & 31;
-  int big_l = -1, big_ri = 0, big_cj = 0, bias_l = -1, bias_j = 0;
+  int big_l[kBig], big_ri[kBig], big_cj[kBig], bias_l[kBias], bias_j[kBias];
+#pragma unroll
+  for (int q = 0; q < kBig; ++q) big_l[q] = -1, big_ri[q] = 0, big_cj[q] = 0;
+#pragma unroll
+  for (int q = 0; q < kBias; ++q) bias_l[q] = -1, bias_j[q] = 0;
 #pragma unroll
   for (int l = 0; l < NH; ++l) {
-    const int li = bwd_slot(NH, l);
     const int ncol = l == 0 ? 1 : H / 32;
-    const int bi = wave - li * (H / 32) * (H / 32);
-    if (bi >= 0 && bi < (H / 32) * ncol) { big_l = l; big_ri = bi / ncol; big_cj = bi % ncol; }
-    const int bj = (wave - 8 - li * (H / 16)) & 15;
-    if (bj < H / 16) { bias_l = l; bias_j = bj; }
+    const int first = bwd_first_block(H, NH, l);
+    const int n_big = (H / 32) * ncol;
+#pragma unroll
+    for (int q = 0; q < kBig; ++q) {
+      const int bi = wave + q * kWavesB - first;
+      if (bi >= 0 && bi < n_big) { big_l[q] = l; big_ri[q] = bi / ncol; big_cj[q] = bi % ncol; }
+    }
+    const int bj = (wave - (H / 16) * (bwd_slot(NH, l) + 1)) & (kWavesB - 1);
+    if (bj < H / 16) {
+      bias_l[bwd_slot(NH, l) >> 1] = l;
+      bias_j[bwd_slot(NH, l) >> 1] = bj;
+    }
   }
-  const uint32_t big_a = (uint32_t)(32 * big_ri + c32) * kRowBytes + 16u * h32;   // + 32 bytes per K step
-  const uint32_t big_b = (uint32_t)(32 * big_cj + c32) * kRowBytes + 16u * h32;
-  const uint32_t bias_a = (uint32_t)(16 * bias_j + m) * kRowBytes + 16u * g;      // + 64 bytes per K step
-  const uint32_t out_b = (uint32_t)(16 * (wave & (RB - 1)) + m) * kRowBytes + 16u * g;
-  const uint32_t out_a = (uint32_t)m * kRowBytes + 16u * g;
+  // byte offsets, the same for every layer: this wave's writes (sample row, 16-feature block rb)
+  uint32_t wr[4];
+#pragma unroll
+  for (int rb = 0; rb < 4; ++rb)
+    wr[rb] = (uint32_t)(wave * 16 * kNCB + m) * kRowBytes + ((32u * rb + 8u * g) ^ stage_swz(m));
+  // and the transposed reads: 32-wide operands (+ 2048 bytes per 16 samples; feature block j of
+  // the gradients, of the inputs) and 16-wide ones (+ 4096 bytes per 32 samples)
+  auto rd32 = [&](int j, uint32_t area, int t) {
+    const uint32_t smp = 8u * h32 + 4u * t + (m >> 2);
+    return smp * kRowBytes + ((area + 64u * j + 32u * (g & 1) + 8u * (m & 3)) ^ stage_swz(smp));
+  };
+  auto rd16 = [&](int j, uint32_t area, int t) {
+    const uint32_t smp = 8u * g + 4u * t + (m >> 2);
+    return smp * kRowBytes + ((area + 32u * j + 8u * (m & 3)) ^ stage_swz(smp));
+  };
+  constexpr uint32_t kHIn = H == 64 ? 0u : 64u;              // the inputs' place in a row
+  uint8_t* s_in = H == 64 ? s_dz + kTileRows * kRowBytes : s_dz;
 
   const uint32_t n_seg = seg_off[n_leaves];
   int cur = -1;
@@ -120,38 +167,63 @@ __global__ __launch_bounds__(kThreadsB) void k_mlp_bwd(
       __syncthreads();
       cur = (int)b;
     }
-    f32x16 accW32;             // this wave's 32x32 block of some dW_l (l < NH)
+    f32x16 accW32[kBig];       // this wave's 32x32 blocks of dW_l (l < NH)
+    f32x4 accB16[kBias];       // its 16-row blocks of db_l (l < NH)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) accW32[i] = 0.f;
-    f32x4 accB16 = {0.f, 0.f, 0.f, 0.f};   // its 16-row block of some db_l (l < NH)
+    for (int q = 0; q < kBig; ++q)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) accW32[q][i] = 0.f;
+#pragma unroll
+    for (int q = 0; q < kBias; ++q) accB16[q] = f32x4{0.f, 0.f, 0.f, 0.f};
     f32x4 accWo = {0.f, 0.f, 0.f, 0.f};    // its 16x16 block of the output layer's dW
-    f32x4 accBo = {0.f, 0.f, 0.f, 0.f};    // the output layer's db (wave 0)
+    f32x4 accBo = {0.f, 0.f, 0.f, 0.f};    // the output layer's db (last wave)
 
-    for (uint32_t sub = kSubPerTile * t_first; sub < kSubPerTile * t_last; ++sub) {
-      const uint32_t row0 = bucket_off[b] + (sub - kSubPerTile * tile_off[b]) * kSubRows + wave * (16 * kNCB);
-      const uint32_t row_end = bucket_off[b + 1];
+    // Rows are read a tile ahead, in two steps (the record, then what it points at), each
+    // issued well before its use; past the leaf's last row the last one is read again.
+    const uint32_t row_first = bucket_off[b] + (t_first - tile_off[b]) * kTileRows;
+    const uint32_t row_end = bucket_off[b + 1];
+    const uint32_t row_lane = wave * (16 * kNCB) + m;
+    uint32_t n_ray[kNCB], n_dst[kNCB];
+    float n_ts[kNCB], n_ray6[kNCB][6];
+    f32x4 n_gz[kNCB];
+    auto read_rec = [&](uint32_t row0) {
+#pragma unroll
+      for (int cb = 0; cb < kNCB; ++cb) {
+        const uint32_t row = min(row0 + row_lane + 16u * cb, row_end - 1u);
+        n_ray[cb] = srec_ray[row];
+        n_ts[cb] = srec_t[row];
+        n_dst[cb] = perm[row];
+      }
+    };
+    auto read_row = [&]() {
+#pragma unroll
+      for (int cb = 0; cb < kNCB; ++cb) {
+        const int64_t ri = r0 + n_ray[cb];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          n_ray6[cb][a] = o[a * stride + ri];
+          n_ray6[cb][3 + a] = d[a * stride + ri];
+        }
+        n_gz[cb] = *reinterpret_cast<const f32x4*>(gpre + 4 * (uint64_t)n_dst[cb]);
+      }
+    };
+    read_rec(row_first);
+    read_row();
+
+    for (uint32_t tile = t_first; tile < t_last; ++tile) {
+      const uint32_t row0 = row_first + (tile - t_first) * kTileRows;
       // ---- forward recompute: layer inputs in B-operand order ----
       bf16x8 X0[kNCB];
       bf16x8 Hs[NH + 1][kNCB][KUh];    // Hs[l] = input of layer l (l >= 1), after ReLU
       f32x4 dz[kNCB][RB];
 #pragma unroll
       for (int cb = 0; cb < kNCB; ++cb) {
-        const uint32_t row = row0 + cb * 16 + m;
-        const bool valid = row < row_end;
-        uint32_t ray = 0;
-        float ts = 0.f;
-        uint32_t dst = 0;
-        if (valid) {
-          ray = srec_ray[row];
-          ts = srec_t[row];
-          dst = perm[row];
-        }
-        const int64_t ri = r0 + ray;
-        const float ox = o[ri], oy = o[stride + ri], oz = o[2 * stride + ri];
-        const float dx = d[ri], dy = d[stride + ri], dzz = d[2 * stride + ri];
-        const float px = 2.f * fmaf(ts, dx, ox) - 1.f;
-        const float py = 2.f * fmaf(ts, dy, oy) - 1.f;
-        const float pz = 2.f * fmaf(ts, dzz, oz) - 1.f;
+        const bool valid = row0 + row_lane + 16u * cb < row_end;
+        const float ts = n_ts[cb];
+        const float dx = n_ray6[cb][3], dy = n_ray6[cb][4], dzz = n_ray6[cb][5];
+        const float px = 2.f * fmaf(ts, dx, n_ray6[cb][0]) - 1.f;
+        const float py = 2.f * fmaf(ts, dy, n_ray6[cb][1]) - 1.f;
+        const float pz = 2.f * fmaf(ts, dzz, n_ray6[cb][2]) - 1.f;
         float feat[8];
         const float v = g == 1 ? py : (g == 2 ? pz : px);
         float sn = __builtin_amdgcn_sinf(0.5f * v);
@@ -174,11 +246,12 @@ __global__ __launch_bounds__(kThreadsB) void k_mlp_bwd(
         for (int e = 0; e < 8; ++e) X0[cb][e] = (__bf16)feat[e];
         // output-layer gradient: lanes of group 0 hold (dsigma^, dr^, dg^, db^)
         f32x4 gz = {0.f, 0.f, 0.f, 0.f};
-        if (g == 0 && valid) gz = *reinterpret_cast<const f32x4*>(gpre + 4 * (uint64_t)dst);
+        if (g == 0 && valid) gz = n_gz[cb];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) dz[cb][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
         dz[cb][0] = gz;
       }
+      read_rec(row0 + kTileRows);
 #pragma unroll
       for (int l = 0; l < NH; ++l) {
         f32x4 acc[kNCB][RB];
@@ -210,64 +283,13 @@ __global__ __launch_bounds__(kThreadsB) void k_mlp_bwd(
           }
       }
 
+      read_row();
+
       // ---- backward, output layer first ----
 #pragma unroll
       for (int l = NH; l >= 0; --l) {
         const int rbo = l == NH ? 1 : RB;          // row blocks of this layer's outputs
-        // stage dZ_l and the layer input, feature-major
-        __syncthreads();
-#pragma unroll
-        for (int cb = 0; cb < kNCB; ++cb) {
-          const int col = wave * (16 * kNCB) + cb * 16 + m;
-#pragma unroll
-          for (int rb = 0; rb < RB; ++rb) {
-            if (rb >= rbo) break;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) stage(s_dz, 16 * rb + 4 * g + i, col, (__bf16)dz[cb][rb][i]);
-          }
-          if (l == 0) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) stage(s_h, 8 * g + e, col, X0[cb][e]);
-          } else {
-#pragma unroll
-            for (int ku = 0; ku < KUh; ++ku)
-#pragma unroll
-              for (int e = 0; e < 8; ++e) stage(s_h, hidden_col_bf16(ku, g, e), col, Hs[l][cb][ku][e]);
-          }
-        }
-        __syncthreads();
-        // dW_l += dZ_l H^T, db_l += dZ_l 1 over the sub-tile's samples
-        if (l == NH) {
-          if (wave < RB) {
-#pragma unroll
-            for (int kb = 0; kb < kSubRows / 32; ++kb) {
-              const bf16x8 A = *reinterpret_cast<const bf16x8*>(s_dz + out_a + 64 * kb);
-              const bf16x8 Bm = *reinterpret_cast<const bf16x8*>(s_h + out_b + 64 * kb);
-              accWo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, Bm, accWo, 0, 0, 0);
-              if (wave == 0) accBo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, ones, accBo, 0, 0, 0);
-            }
-          }
-        } else {
-          // A: lane (h, c) holds dZ row 32 ri + c at samples 16 ks + 8 h ..; B: the input
-          // feature 32 cj + c at the same samples
-          if (big_l == l) {
-#pragma unroll 4
-            for (int ks = 0; ks < kSubRows / 16; ++ks) {
-              const bf16x8 A = *reinterpret_cast<const bf16x8*>(s_dz + big_a + 32 * ks);
-              const bf16x8 Bm = *reinterpret_cast<const bf16x8*>(s_h + big_b + 32 * ks);
-              accW32 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, Bm, accW32, 0, 0, 0);
-            }
-          }
-          if (bias_l == l) {
-#pragma unroll
-            for (int kb = 0; kb < kSubRows / 32; ++kb) {
-              const bf16x8 A = *reinterpret_cast<const bf16x8*>(s_dz + bias_a + 64 * kb);
-              accB16 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, ones, accB16, 0, 0, 0);
-            }
-          }
-        }
-        if (l == 0) break;
-        // dH = W_l^T dZ_l, then the ReLU mask of the forward activation
+        // dZ_l in bfloat16: the operand of dH below, and what is staged
         const int ku_n = l == NH ? 1 : KUh;
         bf16x8 Bz[kNCB][KUh];
 #pragma unroll
@@ -275,13 +297,86 @@ __global__ __launch_bounds__(kThreadsB) void k_mlp_bwd(
 #pragma unroll
           for (int ku = 0; ku < KUh; ++ku) {
             if (ku >= ku_n) break;
+            float vv[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
               const int rbs = 2 * ku + e / 4;
-              const float v = (rbs < rbo) ? dz[cb][rbs][e % 4] : 0.f;
-              Bz[cb][ku][e] = (__bf16)v;
+              vv[e] = rbs < rbo ? dz[cb][rbs][e % 4] : 0.f;
+            }
+            Bz[cb][ku] = cvt_bf16x8(vv);
+          }
+        // stage dZ_l and the layer input, a row per sample
+        __syncthreads();
+#pragma unroll
+        for (int cb = 0; cb < kNCB; ++cb) {
+          auto put = [&](uint8_t* base, int rb, bf16x8 v, int half) {
+            *reinterpret_cast<bf16x4*>(base + wr[rb] + cb * 16 * kRowBytes) =
+                half ? __builtin_shufflevector(v, v, 4, 5, 6, 7) : __builtin_shufflevector(v, v, 0, 1, 2, 3);
+          };
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb) {
+            if (rb >= rbo) break;
+            put(s_dz, rb, Bz[cb][rb / 2], rb & 1);
+          }
+          if (l == 0) {
+#pragma unroll
+            for (int half = 0; half < 2; ++half)
+              *reinterpret_cast<bf16x4*>(s_in + (wave * 16 * kNCB + cb * 16 + m) * kRowBytes +
+                                         ((kHIn + 16u * g + 8u * half) ^ stage_swz(m))) =
+                  half ? __builtin_shufflevector(X0[cb], X0[cb], 4, 5, 6, 7) : __builtin_shufflevector(X0[cb], X0[cb], 0, 1, 2, 3);
+          } else {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+              put(s_in, (int)(kHIn / 32u) + rb, Hs[l][cb][rb / 2], rb & 1);
+          }
+        }
+        __syncthreads();
+        // dW_l += dZ_l H^T, db_l += dZ_l 1 over the tile's samples
+        if (l == NH) {
+          if (wave < RB || wave == kWavesB - 1) {
+            const int cj = wave & (RB - 1);
+            const uint8_t *a0 = s_dz + rd16(0, 0u, 0), *a1 = s_dz + rd16(0, 0u, 1);
+            const uint8_t *b0 = s_in + rd16(cj, kHIn, 0), *b1 = s_in + rd16(cj, kHIn, 1);
+#pragma unroll
+            for (int kb = 0; kb < kTileRows / 32; ++kb) {
+              const bf16x8 A = read_tr(a0 + 4096 * kb, a1 + 4096 * kb);
+              if (wave < RB) {
+                const bf16x8 Bm = read_tr(b0 + 4096 * kb, b1 + 4096 * kb);
+                accWo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, Bm, accWo, 0, 0, 0);
+              } else {
+                accBo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, ones, accBo, 0, 0, 0);
+              }
             }
           }
+        } else {
+          // A: lane (h, c) holds dZ feature 32 ri + c of samples 16 ks + 8 h ..; B: the input
+          // feature 32 cj + c of the same samples
+#pragma unroll
+          for (int q = 0; q < kBig; ++q) {
+            if (bwd_first_block(H, NH, l) + (H / 32) * (l == 0 ? 1 : H / 32) <= q * kWavesB ||
+                bwd_first_block(H, NH, l) >= (q + 1) * kWavesB)
+              continue;
+            if (big_l[q] != l) continue;
+            const uint8_t *a0 = s_dz + rd32(big_ri[q], 0u, 0), *a1 = s_dz + rd32(big_ri[q], 0u, 1);
+            const uint8_t *b0 = s_in + rd32(big_cj[q], kHIn, 0), *b1 = s_in + rd32(big_cj[q], kHIn, 1);
+#pragma unroll
+            for (int ks = 0; ks < kTileRows / 16; ++ks) {
+              const bf16x8 A = read_tr(a0 + 2048 * ks, a1 + 2048 * ks);
+              const bf16x8 Bm = read_tr(b0 + 2048 * ks, b1 + 2048 * ks);
+              accW32[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, Bm, accW32[q], 0, 0, 0);
+            }
+          }
+          const int q = bwd_slot(NH, l) >> 1;
+          if (bias_l[q] == l) {
+            const uint8_t *a0 = s_dz + rd16(bias_j[q], 0u, 0), *a1 = s_dz + rd16(bias_j[q], 0u, 1);
+#pragma unroll
+            for (int kb = 0; kb < kTileRows / 32; ++kb)
+              accB16[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(read_tr(a0 + 4096 * kb, a1 + 4096 * kb), ones,
+                                                                 accB16[q], 0, 0, 0);
+          }
+        }
+        if (l == 0) break;
+        // dH = W_l^T dZ_l, then the ReLU mask of the forward activation
         f32x4 dh[kNCB][RB];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
@@ -311,34 +406,36 @@ __global__ __launch_bounds__(kThreadsB) void k_mlp_bwd(
     {
       int din, dout, off_w, off_b;
       master_offsets(NH, H, NH, din, dout, off_w, off_b);
-      if (wave < RB) {
-        const int c = 16 * wave + m;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int out = 4 * g + i;
-          if (out < dout) dst[off_w + out * din + c] = accWo[i];
-          if (wave == 0 && m == 0 && out < dout) dst[off_b + out] = accBo[i];
-        }
-      }
-    }
-    if (big_l >= 0) {
-      int din, dout, off_w, off_b;
-      master_offsets(NH, H, big_l, din, dout, off_w, off_b);
-      const int cc = 32 * big_cj + c32;
-      const int col = big_l == 0 ? first_layer_col_bf16(cc / 8, cc % 8) : cc;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int out = 32 * big_ri + 8 * (r / 4) + 4 * h32 + (r % 4);   // accumulator row of register r
-        if (out < dout && col >= 0) dst[off_w + out * din + col] = accW32[r];
-      }
-    }
-    if (bias_l >= 0 && m == 0) {
-      int din, dout, off_w, off_b;
-      master_offsets(NH, H, bias_l, din, dout, off_w, off_b);
+      const int c = 16 * wave + m;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int out = 16 * bias_j + 4 * g + i;
-        if (out < dout) dst[off_b + out] = accB16[i];
+        const int out = 4 * g + i;
+        if (wave < RB && out < dout) dst[off_w + out * din + c] = accWo[i];
+        if (wave == kWavesB - 1 && m == 0 && out < dout) dst[off_b + out] = accBo[i];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kBig; ++q) {
+      if (big_l[q] < 0) continue;
+      int din, dout, off_w, off_b;
+      master_offsets(NH, H, big_l[q], din, dout, off_w, off_b);
+      const int cc = 32 * big_cj[q] + c32;
+      const int col = big_l[q] == 0 ? first_layer_col_bf16(cc / 8, cc % 8) : cc;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int out = 32 * big_ri[q] + 8 * (r / 4) + 4 * h32 + (r % 4);   // accumulator row of register r
+        if (out < dout && col >= 0) dst[off_w + out * din + col] = accW32[q][r];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kBias; ++q) {
+      if (bias_l[q] < 0 || m != 0) continue;
+      int din, dout, off_w, off_b;
+      master_offsets(NH, H, bias_l[q], din, dout, off_w, off_b);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int out = 16 * bias_j[q] + 4 * g + i;
+        if (out < dout) dst[off_b + out] = accB16[q][i];
       }
     }
     __syncthreads();   // every wave has read s_seg
@@ -580,7 +677,7 @@ hipError_t launch_bwd_typed(const Layout& L, const void* packed, uint32_t n_leav
                             const uint32_t* perm, const float* o, const float* d, int64_t stride,
                             int64_t r0, const float* gpre, float* part, uint32_t seg_tiles, hipStream_t st) {
   auto kern = k_mlp_bwd<H, NH>;
-  const uint32_t lds = L.bytes + L.bwd_bytes + 2u * H * kRowBytes + 16u;   // + the queue word
+  const uint32_t lds = L.bytes + L.bwd_bytes + (H == 64 ? 2u : 1u) * kTileRows * kRowBytes + 16u;   // + the queue word
   int grid = 0;
   hipError_t e = persistent_grid((const void*)kern, kThreadsB, lds, &grid);
   if (e != hipSuccess) return e;
