@@ -16,10 +16,13 @@
 // Each segment writes its partial dW, db (master layout) to its own slot; a separate
 // kernel sums the slots of each leaf in order, so the gradient is deterministic.
 //
-// What bounds it is LDS traffic and the waits between the phases of a layer.  With 16 waves of
-// 16 rows that staged feature-major, every value was a 2-byte write and every weight fragment
-// was read twice as often: 4.70 ms for a 262 144-ray training batch (23 M samples, 4 layers of
-// 64), 3.67 now, every sum in the same order.
+// What bounds it is the chain of a tile's phases (the matrix cores are busy a third of the
+// time): a layer's staging, its dW blocks on half of the waves, and dH wait for each other, two
+// waves per SIMD being what the registers allow.  262 144-ray training batch (23 M samples, 4
+// layers of 64), every sum in the same order throughout: 16 waves of 16 rows that staged
+// feature-major (2-byte writes, every weight fragment read twice as often) 4.70 ms; rows staged
+// as they are 3.67; LDS reads issued ahead of the matrix instructions 3.15.  16 waves of 16 rows
+// on this staging spill (3.8 ms or more).
 #include "internal.hpp"
 #include "devcommon.hpp"
 #include "mlp_layout.hpp"
@@ -34,6 +37,7 @@ constexpr int kNCB = 2;                          // 16-sample column blocks per 
 constexpr int kTileRows = kMlpTileRows;          // 256-row tiles of the forward pass, one
 static_assert(kWavesB * 16 * kNCB == kTileRows, "a tile is one step of the block");   // step each
 constexpr int kRowBytes = 128;                   // staged sample (bf16 features)
+constexpr int kWeightsAhead = 6;                 // weight fragments read ahead of their use
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -77,6 +81,22 @@ __device__ __forceinline__ bool pos_bf16(__bf16 v) {
   return __builtin_bit_cast(short, v) > 0;
 }
 
+// N steps, each reading LDS operands (read(i)) and using them (use(i)), in order, with the reads
+// AHEAD steps in front and kept there: left to itself the compiler issues a step's reads right
+// before it needs them and waits for the round trip.
+template <int N, int AHEAD, typename READ, typename USE>
+__device__ __forceinline__ void read_ahead(READ read, USE use) {
+#pragma unroll
+  for (int i = 0; i < AHEAD && i < N; ++i) read(i);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (i + AHEAD < N) read(i + AHEAD);
+    __builtin_amdgcn_sched_barrier(0);
+    use(i);
+  }
+}
+
 template <int H, int NH>
 __global__ __launch_bounds__(kThreadsB, 2) void k_mlp_bwd(
     Layout L, const uint8_t* __restrict__ packed_fwd, const uint8_t* __restrict__ packed_bwd,
@@ -89,7 +109,8 @@ __global__ __launch_bounds__(kThreadsB, 2) void k_mlp_bwd(
   extern __shared__ __align__(16) uint8_t lds[];
   constexpr int RB = H / 16;
   constexpr int KUh = H / 32;
-  constexpr int kBig = 2, kBias = 2;                         // blocks a wave holds at most
+  constexpr int kBig = (4 * (H / 32) * (H / 32) + kWavesB - 1) / kWavesB;   // blocks a wave holds at most
+  constexpr int kBias = (4 * (H / 16) + kWavesB - 1) / kWavesB;
   uint8_t* w_fwd = lds;
   uint8_t* w_bwd = lds + L.bytes;
   uint8_t* s_dz = w_bwd + L.bwd_bytes;                       // H = 32: gradients and inputs share rows
@@ -120,8 +141,8 @@ __global__ __launch_bounds__(kThreadsB, 2) void k_mlp_bwd(
     }
     const int bj = (wave - (H / 16) * (bwd_slot(NH, l) + 1)) & (kWavesB - 1);
     if (bj < H / 16) {
-      bias_l[bwd_slot(NH, l) >> 1] = l;
-      bias_j[bwd_slot(NH, l) >> 1] = bj;
+      bias_l[bwd_slot(NH, l) * (H / 16) / kWavesB] = l;
+      bias_j[bwd_slot(NH, l) * (H / 16) / kWavesB] = bj;
     }
   }
   // byte offsets, the same for every layer: this wave's writes (sample row, 16-feature block rb)
@@ -255,23 +276,24 @@ __global__ __launch_bounds__(kThreadsB, 2) void k_mlp_bwd(
 #pragma unroll
       for (int l = 0; l < NH; ++l) {
         f32x4 acc[kNCB][RB];
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          const f32x4 bv = *reinterpret_cast<const f32x4*>(bias + l * H + 16 * rb + 4 * g);
-          if (l == 0) {
-            const bf16x8 A = *reinterpret_cast<const bf16x8*>(units + L.unit_index(0, rb, 0) * kUnitBytes + lane * 16);
-#pragma unroll
-            for (int cb = 0; cb < kNCB; ++cb) acc[cb][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, X0[cb], bv, 0, 0, 0);
-          } else {
-#pragma unroll
-            for (int ku = 0; ku < KUh; ++ku) {
-              const bf16x8 A = *reinterpret_cast<const bf16x8*>(units + L.unit_index(l, rb, ku) * kUnitBytes + lane * 16);
+        const int n_ku = l == 0 ? 1 : KUh;
+        bf16x8 A[RB * KUh];
+        f32x4 bv[RB];
+        read_ahead<RB * KUh, kWeightsAhead>(
+            [&](int i) {
+              const int rb = i / KUh, ku = i % KUh;
+              if (ku >= n_ku) return;
+              if (ku == 0) bv[rb] = *reinterpret_cast<const f32x4*>(bias + l * H + 16 * rb + 4 * g);
+              A[i] = *reinterpret_cast<const bf16x8*>(units + L.unit_index(l, rb, ku) * kUnitBytes + lane * 16);
+            },
+            [&](int i) {
+              const int rb = i / KUh, ku = i % KUh;
+              if (ku >= n_ku) return;
 #pragma unroll
               for (int cb = 0; cb < kNCB; ++cb)
-                acc[cb][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, Hs[l][cb][ku], ku == 0 ? bv : acc[cb][rb], 0, 0, 0);
-            }
-          }
-        }
+                acc[cb][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i], l == 0 ? X0[cb] : Hs[l][cb][ku],
+                                                                      ku == 0 ? bv[rb] : acc[cb][rb], 0, 0, 0);
+            });
 #pragma unroll
         for (int cb = 0; cb < kNCB; ++cb)
 #pragma unroll
@@ -333,20 +355,20 @@ __global__ __launch_bounds__(kThreadsB, 2) void k_mlp_bwd(
         __syncthreads();
         // dW_l += dZ_l H^T, db_l += dZ_l 1 over the tile's samples
         if (l == NH) {
-          if (wave < RB || wave == kWavesB - 1) {
-            const int cj = wave & (RB - 1);
-            const uint8_t *a0 = s_dz + rd16(0, 0u, 0), *a1 = s_dz + rd16(0, 0u, 1);
-            const uint8_t *b0 = s_in + rd16(cj, kHIn, 0), *b1 = s_in + rd16(cj, kHIn, 1);
-#pragma unroll
-            for (int kb = 0; kb < kTileRows / 32; ++kb) {
-              const bf16x8 A = read_tr(a0 + 4096 * kb, a1 + 4096 * kb);
-              if (wave < RB) {
-                const bf16x8 Bm = read_tr(b0 + 4096 * kb, b1 + 4096 * kb);
-                accWo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, Bm, accWo, 0, 0, 0);
-              } else {
-                accBo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, ones, accBo, 0, 0, 0);
-              }
-            }
+          const uint8_t *a0 = s_dz + rd16(0, 0u, 0), *a1 = s_dz + rd16(0, 0u, 1);
+          bf16x8 A[kTileRows / 32], Bm[kTileRows / 32];
+          if (wave < RB) {
+            const uint8_t *b0 = s_in + rd16(wave, kHIn, 0), *b1 = s_in + rd16(wave, kHIn, 1);
+            read_ahead<kTileRows / 32, 3>(
+                [&](int kb) {
+                  A[kb] = read_tr(a0 + 4096 * kb, a1 + 4096 * kb);
+                  Bm[kb] = read_tr(b0 + 4096 * kb, b1 + 4096 * kb);
+                },
+                [&](int kb) { accWo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[kb], Bm[kb], accWo, 0, 0, 0); });
+          } else if (wave == kWavesB - 1) {
+            read_ahead<kTileRows / 32, 5>(
+                [&](int kb) { A[kb] = read_tr(a0 + 4096 * kb, a1 + 4096 * kb); },
+                [&](int kb) { accBo = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[kb], ones, accBo, 0, 0, 0); });
           }
         } else {
           // A: lane (h, c) holds dZ feature 32 ri + c of samples 16 ks + 8 h ..; B: the input
@@ -359,37 +381,41 @@ __global__ __launch_bounds__(kThreadsB, 2) void k_mlp_bwd(
             if (big_l[q] != l) continue;
             const uint8_t *a0 = s_dz + rd32(big_ri[q], 0u, 0), *a1 = s_dz + rd32(big_ri[q], 0u, 1);
             const uint8_t *b0 = s_in + rd32(big_cj[q], kHIn, 0), *b1 = s_in + rd32(big_cj[q], kHIn, 1);
-#pragma unroll
-            for (int ks = 0; ks < kTileRows / 16; ++ks) {
-              const bf16x8 A = read_tr(a0 + 2048 * ks, a1 + 2048 * ks);
-              const bf16x8 Bm = read_tr(b0 + 2048 * ks, b1 + 2048 * ks);
-              accW32[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A, Bm, accW32[q], 0, 0, 0);
-            }
+            bf16x8 A[kTileRows / 16], Bm[kTileRows / 16];
+            read_ahead<kTileRows / 16, 3>(
+                [&](int ks) {
+                  A[ks] = read_tr(a0 + 2048 * ks, a1 + 2048 * ks);
+                  Bm[ks] = read_tr(b0 + 2048 * ks, b1 + 2048 * ks);
+                },
+                [&](int ks) { accW32[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[ks], Bm[ks], accW32[q], 0, 0, 0); });
           }
-          const int q = bwd_slot(NH, l) >> 1;
+          const int q = bwd_slot(NH, l) * (H / 16) / kWavesB;
           if (bias_l[q] == l) {
             const uint8_t *a0 = s_dz + rd16(bias_j[q], 0u, 0), *a1 = s_dz + rd16(bias_j[q], 0u, 1);
-#pragma unroll
-            for (int kb = 0; kb < kTileRows / 32; ++kb)
-              accB16[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(read_tr(a0 + 4096 * kb, a1 + 4096 * kb), ones,
-                                                                 accB16[q], 0, 0, 0);
+            bf16x8 A[kTileRows / 32];
+            read_ahead<kTileRows / 32, 5>(
+                [&](int kb) { A[kb] = read_tr(a0 + 4096 * kb, a1 + 4096 * kb); },
+                [&](int kb) { accB16[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[kb], ones, accB16[q], 0, 0, 0); });
           }
         }
         if (l == 0) break;
         // dH = W_l^T dZ_l, then the ReLU mask of the forward activation
         f32x4 dh[kNCB][RB];
+        bf16x8 A[RB * KUh];
+        read_ahead<RB * KUh, kWeightsAhead>(
+            [&](int i) {
+              const int rb = i / KUh, ku = i % KUh;
+              if (ku >= ku_n) return;
+              A[i] = *reinterpret_cast<const bf16x8*>(w_bwd + L.bwd_unit_index(l, rb, ku) * kUnitBytes + lane * 16);
+            },
+            [&](int i) {
+              const int rb = i / KUh, ku = i % KUh;
+              if (ku >= ku_n) return;
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-#pragma unroll
-          for (int ku = 0; ku < KUh; ++ku) {
-            if (ku >= ku_n) break;
-            const bf16x8 A = *reinterpret_cast<const bf16x8*>(w_bwd + L.bwd_unit_index(l, rb, ku) * kUnitBytes + lane * 16);
-#pragma unroll
-            for (int cb = 0; cb < kNCB; ++cb)
-              dh[cb][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                  A, Bz[cb][ku], ku == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : dh[cb][rb], 0, 0, 0);
-          }
-        }
+              for (int cb = 0; cb < kNCB; ++cb)
+                dh[cb][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    A[i], Bz[cb][ku], ku == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : dh[cb][rb], 0, 0, 0);
+            });
 #pragma unroll
         for (int cb = 0; cb < kNCB; ++cb)
 #pragma unroll
