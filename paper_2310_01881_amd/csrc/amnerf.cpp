@@ -1305,11 +1305,10 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
                                        out->depth_dev, out->opacity_dev, out->weights_dev, w.ray_used, cc, w.carry,
                                        k, cs));
       }
-      HIP_TRY(launch_sum_used(nr, w.ray_used, cc, cs));
     }
     HIP_TRY(mark(6));
     if (ev) ev->pending = true;
-    HIP_TRY(launch_chunk_finish(cc, use.smp_off + nr, use.n_iv_dev, w.smp_off + nr, rounds ? 1 : 0, cs));
+    HIP_TRY(launch_chunk_finish(nr, w.ray_used, cc, use.smp_off + nr, use.n_iv_dev, w.smp_off + nr, rounds ? 1 : 0, cs));
     return rc;
   };
   Pending prev = {};

@@ -320,10 +320,13 @@ __global__ __launch_bounds__(kThreads, 8) void k_composite(
   if (bad) atomicAdd(reinterpret_cast<unsigned long long*>(&counts->nonfinite), 1ull);
 }
 
-// counts->composited += sum of ray_used[0, nr): block sums in a fixed order, one integer
-// atomic per block.
-__global__ __launch_bounds__(kThreads) void k_sum_used(uint32_t nr, const uint32_t* __restrict__ ray_used,
-                                                       ChunkCounts* __restrict__ counts) {
+// End of a chunk: counts->composited += sum of ray_used[0, nr) (block sums in a fixed order, one
+// integer atomic per block), and the chunk's totals are recorded for the host and the global
+// sample base advanced.  (As two launches 1.4 us more a pass: a 32x32 thumbnail 49.3 -> 47.8 us.)
+__global__ __launch_bounds__(kThreads) void k_chunk_finish(uint32_t nr, const uint32_t* __restrict__ ray_used,
+                                                           ChunkCounts* __restrict__ counts, const uint32_t* smp_total,
+                                                           const uint32_t* iv_total, const uint32_t* plain_total,
+                                                           int rounds) {
   __shared__ uint32_t sh[kThreads / 64];
   uint32_t s = 0;
   for (uint32_t i = blockIdx.x * kThreads + threadIdx.x; i < nr; i += gridDim.x * kThreads) s += ray_used[i];
@@ -331,17 +334,11 @@ __global__ __launch_bounds__(kThreads) void k_sum_used(uint32_t nr, const uint32
   for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t t = 0;
-    for (int w = 0; w < kThreads / 64; ++w) t += sh[w];
-    if (t) atomicAdd(reinterpret_cast<unsigned long long*>(&counts->composited), (unsigned long long)t);
-  }
-}
-
-// Records the chunk's totals for the host and advances the global sample base.
-__global__ void k_chunk_finish(ChunkCounts* counts, const uint32_t* smp_total, const uint32_t* iv_total,
-                               const uint32_t* plain_total, int rounds) {
   if (threadIdx.x != 0) return;
+  uint64_t t = 0;
+  for (int w = 0; w < kThreads / 64; ++w) t += sh[w];
+  if (t) atomicAdd(reinterpret_cast<unsigned long long*>(&counts->composited), (unsigned long long)t);
+  if (blockIdx.x != 0) return;
   if (!rounds) counts->evaluated += *smp_total;   // (in rounds: added by each round's selection)
   counts->smp_global += *smp_total;
   counts->iv_global += *iv_total;
@@ -382,7 +379,7 @@ hipError_t launch_composite(uint32_t nr, const IvSet& iv, bool uniform, const fl
   hipLaunchKernelGGL((uniform ? k_composite<false, true> : k_composite<false, false>), dim3((nr + rays - 1) / rays),
                      dim3(kThreads), 0, st, nr, iv, smp_out, r0, jitter, seed, ert_eps, rgb, depth, opac, weights,
                      ray_used, counts, nullptr, 0u);
-  return launch_sum_used(nr, ray_used, counts, st);
+  return hipGetLastError();
 }
 
 hipError_t launch_composite_round(uint32_t nr, const IvSet& iv, bool uniform, const float* smp_out, int64_t r0,
@@ -397,18 +394,12 @@ hipError_t launch_composite_round(uint32_t nr, const IvSet& iv, bool uniform, co
   return hipGetLastError();
 }
 
-hipError_t launch_sum_used(uint32_t nr, const uint32_t* ray_used, ChunkCounts* counts, hipStream_t st) {
-  if (nr == 0) return hipSuccess;
-  const uint32_t sgrid = std::min<uint32_t>(256u, (nr + 4 * kThreads - 1) / (4 * kThreads));
-  hipLaunchKernelGGL(k_sum_used, dim3(sgrid), dim3(kThreads), 0, st, nr, ray_used, counts);
-  return hipGetLastError();
-}
-
-hipError_t launch_chunk_finish(ChunkCounts* counts, const uint32_t* smp_off_total,
+hipError_t launch_chunk_finish(uint32_t nr, const uint32_t* ray_used, ChunkCounts* counts, const uint32_t* smp_off_total,
                                const uint32_t* iv_off_total, const uint32_t* plain_smp_total, int rounds,
                                hipStream_t st) {
-  hipLaunchKernelGGL(k_chunk_finish, dim3(1), dim3(64), 0, st, counts, smp_off_total, iv_off_total,
-                     plain_smp_total, rounds);
+  const uint32_t grid = std::max(1u, std::min<uint32_t>(256u, (nr + 4 * kThreads - 1) / (4 * kThreads)));
+  hipLaunchKernelGGL(k_chunk_finish, dim3(grid), dim3(kThreads), 0, st, nr, ray_used, counts, smp_off_total,
+                     iv_off_total, plain_smp_total, rounds);
   return hipGetLastError();
 }
 

@@ -217,12 +217,11 @@ hipError_t launch_composite(uint32_t nr, const IvSet& iv, bool uniform, const fl
                             hipStream_t st);
 // One 64-sample window (`round`) of every ray still marching, continuing from `carry`;
 // ray_used and the outputs are written as rays finish.  counts->composited is added by
-// launch_sum_used once every round has run.
+// launch_chunk_finish once every round has run.
 hipError_t launch_composite_round(uint32_t nr, const IvSet& iv, bool uniform, const float* smp_out, int64_t r0, int jitter,
                                   uint64_t seed, float ert_eps, float* rgb, float* depth, float* opac,
                                   float* weights, uint32_t* ray_used, ChunkCounts* counts, CompCarry* carry,
                                   uint32_t round, hipStream_t st);
-hipError_t launch_sum_used(uint32_t nr, const uint32_t* ray_used, ChunkCounts* counts, hipStream_t st);
 
 // ---- early termination in rounds (Section 4.1) -------------------------------------------
 // Round k selects, in sorted order, the samples of window k (sample index 64k .. 64k + 63 of
@@ -293,7 +292,7 @@ hipError_t launch_prop_train(const void* packed, const IvSet& iv, const float* o
 hipError_t launch_counts_merge(ChunkCounts* a, const ChunkCounts* b, hipStream_t st);
 // Start of a pass: zeroes the chained scans' state words, and the counters when `reset`.
 hipError_t launch_pass_begin(ChunkCounts* counts, bool reset, uint64_t* state, uint64_t words, hipStream_t st);
-hipError_t launch_chunk_finish(ChunkCounts* counts, const uint32_t* smp_off_total,
+hipError_t launch_chunk_finish(uint32_t nr, const uint32_t* ray_used, ChunkCounts* counts, const uint32_t* smp_off_total,
                                const uint32_t* iv_off_total, const uint32_t* plain_smp_total, int rounds,
                                hipStream_t st);
 
