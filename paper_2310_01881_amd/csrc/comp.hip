@@ -394,9 +394,9 @@ hipError_t launch_composite_round(uint32_t nr, const IvSet& iv, bool uniform, co
   return hipGetLastError();
 }
 
-hipError_t launch_chunk_finish(uint32_t nr, const uint32_t* ray_used, ChunkCounts* counts, const uint32_t* smp_off_total,
-                               const uint32_t* iv_off_total, const uint32_t* plain_smp_total, int rounds,
-                               hipStream_t st) {
+hipError_t launch_chunk_finish(uint32_t nr, const uint32_t* ray_used, ChunkCounts* counts,
+                               const uint32_t* smp_off_total, const uint32_t* iv_off_total,
+                               const uint32_t* plain_smp_total, int rounds, hipStream_t st) {
   const uint32_t grid = std::max(1u, std::min<uint32_t>(256u, (nr + 4 * kThreads - 1) / (4 * kThreads)));
   hipLaunchKernelGGL(k_chunk_finish, dim3(grid), dim3(kThreads), 0, st, nr, ray_used, counts, smp_off_total,
                      iv_off_total, plain_smp_total, rounds);
