@@ -357,7 +357,7 @@ int amnerf_render(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_mlp* ml
  * amnerf_render_static_capacity() bytes (64 MiB) on each GPU, set up when the first context
  * on that GPU is created and held until the process ends; the call itself allocates nothing
  * and never waits on the host.  The whole call must fit one pass and that workspace: about
- * 20 + 40 * min(s_max, n_leaves) + 28 * s_max bytes per ray (7 500 rays at s_max 128 with
+ * 16 + 36 * min(s_max, n_leaves) + 28 * s_max bytes per ray (8 100 rays at s_max 128 with
  * 512 leaves); larger calls fail with AMNERF_ECAPACITY and the bytes they need, before any
  * work is enqueued.  No proposal or occupancy grid (AMNERF_EINVAL: their buffers are sized
  * from a count measured on the host).  Every call on a GPU shares that GPU's array and
