@@ -1273,10 +1273,18 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
     HIP_TRY(launch_sort_hist(spu, use.key, use.n_iv_dev, sb.mat, cs));
     HIP_TRY(launch_scan_packed(sb.mat, sb.mat_smp, (uint64_t)L * spu.nseg_max, use.n_iv_dev, L, spu.seg, sort_chain, cs));
     HIP_TRY(launch_bucket_tiles(spu, sb, use.n_iv_dev, cc, cs));
-    HIP_TRY(launch_sort_scatter(spu, sb, use, cs));
+    // a pass that expands its intervals does so from their sorted records, which lie where the
+    // MLPs will write (an interval has a sample at least); jittered strata need the intervals
+    SortBufs placed = sb;
+    if (!sb.rec) {
+      placed.rec = jitter ? nullptr : reinterpret_cast<SortRec*>(w.smp_out);
+      placed.win = nullptr;
+    }
+    HIP_TRY(launch_sort_scatter(spu, placed, use, cs));
     HIP_TRY(mark(3));
     if (!sb.rec)
-      HIP_TRY(launch_expand(sb.sidx, sb.ssb, use, r0, jitter, p->jitter_seed, w.srec_ray, w.srec_t, w.perm, cs));
+      HIP_TRY(launch_expand(sb.sidx, placed.rec, sb.ssb, use, r0, jitter, p->jitter_seed, w.srec_ray, w.srec_t, w.perm,
+                            cs));
     HIP_TRY(mark(4));
     if (!rounds) {
       const RowSource rows = {sb.rec, sb.ssb, sb.win, w.srec_ray, w.srec_t, w.perm};
@@ -1425,7 +1433,7 @@ extern "C" int amnerf_render_stats_get(amnerf_ctx* ctx, amnerf_render_stats* out
 static int ensure_expanded(amnerf_ctx* ctx, hipStream_t st) {
   if (ctx->expanded) return AMNERF_OK;
   const int jitter = (ctx->last_params.flags & AMNERF_JITTER) ? 1 : 0;
-  HIP_TRY(launch_expand(ctx->sidx, ctx->ssb, ctx->use, 0, jitter, ctx->last_params.jitter_seed, ctx->srec_ray,
+  HIP_TRY(launch_expand(ctx->sidx, nullptr, ctx->ssb, ctx->use, 0, jitter, ctx->last_params.jitter_seed, ctx->srec_ray,
                         ctx->srec_t, ctx->perm, st));
   ctx->expanded = true;
   return AMNERF_OK;

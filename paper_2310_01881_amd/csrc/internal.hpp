@@ -137,8 +137,9 @@ hipError_t launch_sort_hist(const SortPlan& p, const uint32_t* iv_key, const uin
 hipError_t launch_bucket_tiles(const SortPlan& p, const SortBufs& b, const uint32_t* n_iv_dev, ChunkCounts* counts,
                                hipStream_t st);
 hipError_t launch_sort_scatter(const SortPlan& p, const SortBufs& b, const IvSet& iv, hipStream_t st);
-// One record per sorted sample: ray (chunk-local), t, ray-major sample index.
-hipError_t launch_expand(const uint32_t* sidx, const uint32_t* ssb, const IvSet& iv,
+// One record per sorted sample: ray (chunk-local), t, ray-major sample index; from the sorted
+// interval records where rec is given (centred strata only).
+hipError_t launch_expand(const uint32_t* sidx, const SortRec* rec, const uint32_t* ssb, const IvSet& iv,
                          int64_t r0, int jitter, uint64_t seed, uint32_t* srec_ray,
                          float* srec_t, uint32_t* perm, hipStream_t st);
 

@@ -79,7 +79,8 @@ __device__ __forceinline__ uint32_t count_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-template <bool REC>
+// REC: the interval records are written too; WIN: and the MLP's windows.
+template <bool REC, bool WIN>
 __global__ __launch_bounds__(kThreads) void k_sort_scatter(IvSet iv, uint32_t seg, uint32_t n_leaves,
                                                            uint32_t key_bits, SortBufs out) {
   extern __shared__ uint32_t sh[];
@@ -120,7 +121,7 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(IvSet iv, uint32_t se
       const uint32_t slot = key_slot(key), n = valid ? key_n(key) : 0u;
       uint32_t pos = out.mat[(uint64_t)slot * nseg + s], smp = out.mat_smp[(uint64_t)slot * nseg + s];
       uint32_t first = 0, tile = 0;
-      if (REC) {
+      if (WIN) {
         first = out.bucket_off[slot];
         tile = out.tile_off[slot];
       }
@@ -151,8 +152,10 @@ __global__ __launch_bounds__(kThreads) void k_sort_scatter(IvSet iv, uint32_t se
           *reinterpret_cast<float4*>(out.rec + pos) =
               make_float4(t0, dt / (float)n, __uint_as_float(ray), __uint_as_float(base));
           // the windows (64 rows of the leaf's bucket) whose first row is one of these samples
-          const uint32_t at = smp - first;
-          for (uint32_t w = (at + 63u) / 64u; 64u * w < at + n; ++w) out.win[4u * tile + w] = pos;
+          if (WIN) {
+            const uint32_t at = smp - first;
+            for (uint32_t w = (at + 63u) / 64u; 64u * w < at + n; ++w) out.win[4u * tile + w] = pos;
+          }
         }
       }
     }
@@ -213,9 +216,14 @@ __global__ __launch_bounds__(1024) void k_bucket_tiles(uint32_t seg, uint32_t n_
 // lane in a per-wave LDS row, and a prefix maximum over the row (seeded with the last
 // interval of the previous window) gives every lane the latest interval started at or
 // before it.
+//
+// REC: from the intervals' sorted records.  Otherwise each of five arrays is read at a sorted
+// interval's own place, a whole sector for four bytes: 184 us for the 23 M samples (1.7 M
+// intervals) of a training batch against 67, with the records' writing 39 -> 81 in the scatter.
+template <bool REC>
 __global__ __launch_bounds__(kThreads) void k_expand(
-    const uint32_t* __restrict__ sidx, const uint32_t* __restrict__ ssb, IvSet iv, int64_t r0,
-    int jitter, uint64_t seed, uint32_t* __restrict__ srec_ray, float* __restrict__ srec_t,
+    const uint32_t* __restrict__ sidx, const SortRec* __restrict__ rec, const uint32_t* __restrict__ ssb, IvSet iv,
+    int64_t r0, int jitter, uint64_t seed, uint32_t* __restrict__ srec_ray, float* __restrict__ srec_t,
     uint32_t* __restrict__ perm) {
   __shared__ uint32_t sh_base[kThreads + 1];
   __shared__ uint32_t sh_ray[kThreads], sh_rm[kThreads];
@@ -228,7 +236,15 @@ __global__ __launch_bounds__(kThreads) void k_expand(
     const uint32_t p0 = grp * kThreads;
     const uint32_t cnt = n_iv - p0 < (uint32_t)kThreads ? n_iv - p0 : (uint32_t)kThreads;
     const uint32_t p = p0 + threadIdx.x;
-    if (threadIdx.x < cnt) {
+    if (REC && threadIdx.x < cnt) {
+      const float4 r = *reinterpret_cast<const float4*>(rec + p);
+      sh_base[threadIdx.x] = ssb[p];
+      sh_ray[threadIdx.x] = __float_as_uint(r.z);
+      sh_rm[threadIdx.x] = __float_as_uint(r.w);
+      sh_t0[threadIdx.x] = r.x;
+      sh_delta[threadIdx.x] = r.y;
+      sh_u[threadIdx.x] = 0.5f;
+    } else if (threadIdx.x < cnt) {
       uint32_t i = sidx[p];
       uint32_t ray = iv.ray[i];
       uint32_t n = key_n(iv.key[i]);
@@ -318,8 +334,9 @@ hipError_t launch_sort_hist(const SortPlan& p, const uint32_t* iv_key, const uin
 hipError_t launch_sort_scatter(const SortPlan& p, const SortBufs& b, const IvSet& iv, hipStream_t st) {
   const uint32_t w = (uint32_t)sort_waves(p);
   const uint32_t grid = std::min<uint32_t>(((p.nseg_max + w - 1) / w + kDies - 1) / kDies * kDies, kMaxGrid);
-  hipLaunchKernelGGL((b.rec ? k_sort_scatter<true> : k_sort_scatter<false>), dim3(grid), dim3(64 * w),
-                     sizeof(uint32_t) * w * p.n_leaves, st, iv, p.seg, p.n_leaves, p.key_bits, b);
+  auto kern = !b.rec ? k_sort_scatter<false, false> : (b.win ? k_sort_scatter<true, true> : k_sort_scatter<true, false>);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * w), sizeof(uint32_t) * w * p.n_leaves, st, iv, p.seg, p.n_leaves,
+                     p.key_bits, b);
   return hipGetLastError();
 }
 
@@ -329,11 +346,11 @@ hipError_t launch_bucket_tiles(const SortPlan& p, const SortBufs& b, const uint3
   return hipGetLastError();
 }
 
-hipError_t launch_expand(const uint32_t* sidx, const uint32_t* ssb, const IvSet& iv, int64_t r0,
+hipError_t launch_expand(const uint32_t* sidx, const SortRec* rec, const uint32_t* ssb, const IvSet& iv, int64_t r0,
                          int jitter, uint64_t seed, uint32_t* srec_ray, float* srec_t, uint32_t* perm,
                          hipStream_t st) {
-  hipLaunchKernelGGL(k_expand, dim3(4096), dim3(kThreads), 0, st, sidx, ssb, iv, r0, jitter, seed,
-                     srec_ray, srec_t, perm);
+  hipLaunchKernelGGL((rec ? k_expand<true> : k_expand<false>), dim3(4096), dim3(kThreads), 0, st, sidx, rec, ssb, iv, r0,
+                     jitter, seed, srec_ray, srec_t, perm);
   return hipGetLastError();
 }
 
