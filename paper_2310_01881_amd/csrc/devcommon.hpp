@@ -72,4 +72,20 @@ __device__ __forceinline__ float lane_value(float v, int lane) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
+// N steps, each reading LDS operands (read(i)) and using them (use(i)), in order, with the reads
+// AHEAD steps in front and kept there: left to itself the compiler issues a step's reads right
+// before it needs them and waits for the round trip.
+template <int N, int AHEAD, typename READ, typename USE>
+__device__ __forceinline__ void read_ahead(READ read, USE use) {
+#pragma unroll
+  for (int i = 0; i < AHEAD && i < N; ++i) read(i);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (i + AHEAD < N) read(i + AHEAD);
+    __builtin_amdgcn_sched_barrier(0);
+    use(i);
+  }
+}
+
 }  // namespace amn

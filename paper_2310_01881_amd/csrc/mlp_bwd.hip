@@ -81,22 +81,6 @@ __device__ __forceinline__ bool pos_bf16(__bf16 v) {
   return __builtin_bit_cast(short, v) > 0;
 }
 
-// N steps, each reading LDS operands (read(i)) and using them (use(i)), in order, with the reads
-// AHEAD steps in front and kept there: left to itself the compiler issues a step's reads right
-// before it needs them and waits for the round trip.
-template <int N, int AHEAD, typename READ, typename USE>
-__device__ __forceinline__ void read_ahead(READ read, USE use) {
-#pragma unroll
-  for (int i = 0; i < AHEAD && i < N; ++i) read(i);
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    __builtin_amdgcn_sched_barrier(0);
-    if (i + AHEAD < N) read(i + AHEAD);
-    __builtin_amdgcn_sched_barrier(0);
-    use(i);
-  }
-}
-
 template <int H, int NH>
 __global__ __launch_bounds__(kThreadsB, 2) void k_mlp_bwd(
     Layout L, const uint8_t* __restrict__ packed_fwd, const uint8_t* __restrict__ packed_bwd,

@@ -1037,25 +1037,40 @@ __global__ __launch_bounds__(kThreads) void k_prop_train(const uint8_t* __restri
       }
       __syncthreads();
       // H2/H1 staged into s_dz above hold dZ for layers 1 and 0 (see the chain below)
-      const int n_items_l = rbo * cbi;
-      const int per = (n_items_l + 3) / 4;
+      // A wave's items are blocks of one output row block, so they share the operand from dZ, and
+      // the reads go four steps ahead (one wave per SIMD: each step waited for its own): 210 ->
+      // 201 us for 200 000 intervals.  The rest is the features' and the loss's functions.
+      const int per = rbo * cbi / 4;   // 2, 4 or 3
+      const int rb = wave * per / cbi, ci0 = wave * per % cbi;
+      f32x4 acc[4], accb = layer == 2 ? aB2 : (layer == 1 ? aB1 : aB0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (q < per) acc[q] = layer == 2 ? aW2[q < 2 ? q : 0] : (layer == 1 ? aW1[q] : aW0[q < 3 ? q : 0]);
+      float a[kTrItems / 4], bm[kTrItems / 4][4];
+      read_ahead<kTrItems / 4, 4>(
+          [&](int kb) {
+            a[kb] = ldf(s_dz, 16 * rb + m, 4 * kb + g);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if (q < per) bm[kb][q] = ldf(s_h, 16 * (ci0 + q) + m, 4 * kb + g);
+          },
+          [&](int kb) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if (q < per) acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kb], bm[kb][q], acc[q], 0, 0, 0);
+            accb = __builtin_amdgcn_mfma_f32_16x16x4f32(a[kb], 1.f, accb, 0, 0, 0);
+          });
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int item = wave * per + q;
-        if (q >= per || item >= n_items_l) break;
-        const int rb = item / cbi, ci = item % cbi;
-        f32x4 acc = layer == 2 ? aW2[q < 2 ? q : 0] : (layer == 1 ? aW1[q] : aW0[q < 3 ? q : 0]);
-        f32x4 accb = layer == 2 ? aB2 : (layer == 1 ? aB1 : aB0);
-        for (int kb = 0; kb < kTrItems / 4; ++kb) {
-          const float a = ldf(s_dz, 16 * rb + m, 4 * kb + g);
-          const float bm = ldf(s_h, 16 * ci + m, 4 * kb + g);
-          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bm, acc, 0, 0, 0);
-          if (ci == 0) accb = __builtin_amdgcn_mfma_f32_16x16x4f32(a, 1.f, accb, 0, 0, 0);
-        }
-        if (layer == 2) { aW2[q < 2 ? q : 0] = acc; if (ci == 0) aB2 = accb; }
-        else if (layer == 1) { aW1[q] = acc; if (ci == 0) aB1 = accb; }
-        else { aW0[q < 3 ? q : 0] = acc; if (ci == 0) aB0 = accb; }
+        if (q >= per) break;
+        if (layer == 2) aW2[q < 2 ? q : 0] = acc[q];
+        else if (layer == 1) aW1[q] = acc[q];
+        else aW0[q < 3 ? q : 0] = acc[q];
       }
+      // (layer 2: two waves hold one row block; the sums of the second are not read)
+      if (layer == 2) aB2 = accb;
+      else if (layer == 1) aB1 = accb;
+      else aB0 = accb;
       if (layer == 0) break;
       // chain: dH = W^T dZ, masked by the forward activation, becomes dZ of the layer below
       if (layer == 2) {
