@@ -107,8 +107,9 @@ __device__ __forceinline__ float row_last(float v) { return dpp_or_zero<0x15F, 0
 // row handles sample base + c: tau_j, then S_j = sum_{i<j} tau_i by a compensated (float pair)
 // prefix scan across the row plus the running total of earlier steps; T_j = exp(-S_j), w_j =
 // T_j (1 - e^-tau_j).  Early termination: the first lane whose T_{j+1} < eps keeps its sample
-// and later lanes (and steps) of its ray contribute nothing.  T_j is the neighbouring lane's
-// T_{j+1}, so one exponential per sample serves both.
+// and later lanes (and steps) of its ray contribute nothing, whatever they hold: a ray's result
+// depends neither on the rays beside it, which may march on, nor on what lies behind its stop.
+// T_j is the neighbouring lane's T_{j+1}, so one exponential per sample serves both.
 //
 // Sums run over windows of 64 samples (the four steps q = 0..3 of a window) in one fixed order,
 // that of a 64-lane prefix sum over rows of 16: with R_q the row's sum of step q, a window's sum
@@ -259,8 +260,11 @@ __global__ __launch_bounds__(kThreads, 8) void k_composite(
     const uint32_t stops = (uint32_t)(__ballot(stop) >> (lane & 48)) & 0xFFFFu;
     const bool now = stops != 0;
     const uint32_t first = (uint32_t)__ffs((int)stops) - 1u;
-    if (now && c > first) w = 0.f;
-    const float x = row_sums4(w, logisticf(z.y), logisticf(z.z), logisticf(z.w), t, bit0, bit1);
+    const bool counts_in = valid && !(now && c > first);
+    if (!counts_in) w = 0.f;
+    // (selected, not multiplied by that 0: a NaN or an infinity behind the stop must not count)
+    const float x = row_sums4(w, counts_in ? logisticf(z.y) : 0.f, counts_in ? logisticf(z.z) : 0.f,
+                              counts_in ? logisticf(z.w) : 0.f, counts_in ? t : 0.f, bit0, bit1);
     const float xa = row_sum_last(w);
     if (q & 1u) {
       sum = x + sum;

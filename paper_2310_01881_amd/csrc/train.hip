@@ -121,8 +121,8 @@ __global__ __launch_bounds__(kThreads) void k_comp_bwd(
     const bool valid = j <= J && U > 0;
     float tau = 0.f, delta = 0.f, t = 0.f;
     float4 z = {0.f, 0.f, 0.f, 0.f};
-    if (j < ns) sample(j, tau, delta, t, z);
-    const DF Sn = tau_scan(valid ? tau : 0.f, carry_at[st], lane);
+    if (valid) sample(j, tau, delta, t, z);   // (behind the stop nothing is read: it may hold a NaN)
+    const DF Sn = tau_scan(tau, carry_at[st], lane);
     const float Tn = df_exp_neg(Sn);
     float T = __shfl_up(Tn, 1, 64);   // the exclusive sum of a lane is the inclusive one of the lane before
     if (lane == 0) T = 1.f;

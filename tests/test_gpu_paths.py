@@ -280,3 +280,58 @@ def test_float32_training_step_forward(n_hidden, hidden):
     print("%dx%d: loss %.7f %.7f, gradient %.2e" % (n_hidden, hidden, loss, l2.item(), e))
     assert abs(l2.item() - loss) <= 5e-5 * loss
     assert e <= 5e-5
+
+
+@pytest.mark.parametrize("dtype", [am.AMNERF_F32, am.AMNERF_BF16])
+def test_samples_behind_a_stop_count_for_nothing(dtype):
+    """One leaf's colours are NaN, behind opaque leaves for some rays.  A ray that stops before it
+    gives the bits it gives with finite colours there: in a full launch (beside rays that march
+    on), alone, and in rounds; its gradient too.  Every ray that reaches the leaf is counted."""
+    scene = small_scene(s_max=192)
+    at = synth.sigma_bias_offset(scene.cfg.n_hidden, scene.cfg.hidden)
+    W = scene.W.copy()
+    W[1:5, at] = 300.0                        # opaque: a ray stops within a few samples
+    W[5:, at] = -9.0                          # all but empty
+    bad = W.copy()
+    bad[0, at + 1:at + 4] = np.nan
+    scene.W = W
+    ctx, tree, mlp = gpu_setup(scene, dtype)
+    master = to_dev(bad)
+    mlp_bad = am.Mlp(ctx, master, scene.cfg.n_hidden, scene.cfg.hidden, dtype, scene.n_sets)
+    o, d = synth.random_rays(4000, 15)
+    od, dd = to_dev(o), to_dev(d)
+    ref, st, used, off = ert.render(ctx, tree, mlp, od, dd, 192, 0)
+    assert st["n_nonfinite"] == 0
+    _, ins = fetch_inspect(ctx, 4000, scene.n_sets)
+    slot = np.repeat(ins["iv_slot"], ins["iv_n"])
+    first = np.array([np.append(np.flatnonzero(slot[off[r]:off[r + 1]] == 0), 1 << 20)[0] for r in range(4000)])
+    clean = used <= first
+    behind = np.flatnonzero(clean & (first < 1 << 20))
+    print("rays that stop before the leaf %d, that reach it %d" % (len(behind), (~clean).sum()), flush=True)
+    assert len(behind) > 100 and (~clean).sum() > 100
+    pick = torch.from_numpy(clean).to("cuda:0")
+    for flags in (0, am.AMNERF_ERT_ROUNDS):
+        out, st, used2, _ = ert.render(ctx, tree, mlp_bad, od, dd, 192, flags)
+        assert np.array_equal(used2[clean], used[clean])
+        assert st["n_nonfinite"] == (~clean).sum(), flags
+        for k in range(3):
+            assert torch.equal(out[k][pick], ref[k][pick]), (flags, k)
+    for r in behind[::len(behind) // 20]:
+        for flags in (0, am.AMNERF_ERT_ROUNDS):
+            out = ert.render(ctx, tree, mlp_bad, od[:, r:r + 1].contiguous(), dd[:, r:r + 1].contiguous(), 192, flags)[0]
+            for k in range(3):
+                assert torch.equal(out[k][0], ref[k][r]), (r, flags, k)
+    oc, dc = od[:, pick].contiguous(), dd[:, pick].contiguous()
+    n = oc.shape[1]
+    rng = np.random.default_rng(16)
+    g = [to_dev(rng.standard_normal(s).astype(np.float32)) for s in ((n, 3), n, n)]
+    grads = []
+    for m in (mlp, mlp_bad):
+        rgb = torch.empty((n, 3), device="cuda:0")
+        am.amnerf_render(ctx.h, tree.h, m.desc, oc, dc, 192, rgb)
+        grad = torch.empty_like(master)
+        am.amnerf_render_backward(ctx.h, tree.h, m.desc, oc, dc, g[0], grad, g[1], g[2])
+        grads.append(grad)
+    torch.cuda.synchronize()
+    assert torch.isfinite(grads[0]).all() and grads[0].abs().max() > 0
+    assert torch.equal(grads[0], grads[1])
