@@ -79,19 +79,16 @@ __device__ __forceinline__ void split8(const float v[8], bf16x8 part[3]) {
   for (int p = 0; p < 3; ++p) part[p] = __builtin_bit_cast(bf16x8, w[p]);
 }
 
-// The same for weights, each part rounded to nearest (a value that rounds to infinity, or is
-// not finite, keeps its truncated leading part alone).
+// The same for weights, each part rounded to nearest (a finite value that would round to infinity
+// keeps its truncated leading part; an infinity or a NaN is its leading part alone).
 __device__ __forceinline__ void split_weight(float w, __bf16 part[3]) {
+  const bool finite = fabsf(w) < __builtin_inff();
   __bf16 h = (__bf16)w;
-  if (!(fabsf((float)h) < __builtin_inff())) {
-    part[0] = (__bf16)high_part(w);
-    part[1] = part[2] = (__bf16)0.f;
-    return;
-  }
+  if (finite && !(fabsf((float)h) < __builtin_inff())) h = (__bf16)high_part(w);
   const float r = w - (float)h;
   part[0] = h;
-  part[1] = (__bf16)r;
-  part[2] = (__bf16)(r - (float)part[1]);
+  part[1] = finite ? (__bf16)r : (__bf16)0.f;
+  part[2] = finite ? (__bf16)(r - (float)part[1]) : (__bf16)0.f;
 }
 
 // Leaf b's float32 block (mlp_layout.hpp) into LDS as split fragments: fragment (layer, ob,
@@ -177,10 +174,15 @@ __device__ __forceinline__ void layer32(const uint8_t* frag, const float* bias, 
   __builtin_amdgcn_s_setprio(0);
 #pragma unroll
   for (int ob = 0; ob < OB; ++ob) {
-    // ReLU; an infinite value becomes the largest finite one, which splits without a NaN
+    // ReLU.  An infinite weight or input makes the small products infinities and NaNs of any kind
+    // (inf x 0, w2 inf of the other sign), but every such product has its leading one in the main
+    // sum, which is then what the float32 sum is: +inf must come out as +inf, -inf and NaN as 0.
+    // So the ReLU's maximum takes a third operand, which is +inf for a main sum of +inf and at
+    // most 0 for a finite one.
     float v[16];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) v[i] = __builtin_amdgcn_fmed3f(big[ob][i] + small[ob][i], 0.f, 3.402823466e38f);
+    for (int i = 0; i < 16; ++i)
+      v[i] = fmaxf(fmaxf(big[ob][i] + small[ob][i], 0.f), big[ob][i] - 3.402823466e38f);
     if constexpr (LAST) {
 #pragma unroll
       for (int q = 0; q < 16; q += 8) {

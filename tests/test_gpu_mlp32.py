@@ -66,3 +66,99 @@ def test_float32_outputs_per_sample(n_hidden, hidden, n_rays):
     err = np.abs(h["sample_out"].reshape(-1, 4) - z).max() / np.sqrt((z * z).mean())
     print("%d x %d: max error / rms %.2e" % (n_hidden, hidden, err))
     assert err < 32 * (n_hidden + 2) * 2.0 ** -24
+
+
+def _sample_outputs(ctx, n_rays):
+    """(leaf, ray, pre-activations) of the last render's samples, and its statistics."""
+    import paper_2310_01881_amd as am
+    st = am.amnerf_render_stats_get(ctx.h)
+    ni, ns = st["n_intervals"], st["n_samples"]
+    assert ns > 0
+    buf = {k: torch.empty(n, dtype=t, device="cuda") for k, n, t in
+           [("ray_iv_off", n_rays + 1, torch.int32), ("iv_slot", ni, torch.int32), ("iv_n", ni, torch.int32),
+            ("sample_out", 4 * ns, torch.float32)]}
+    am.amnerf_render_inspect(ctx.h, **buf)
+    h = {k: v.cpu().numpy() for k, v in buf.items()}
+    ray = np.repeat(np.arange(n_rays), np.diff(h["ray_iv_off"]))
+    return np.repeat(h["iv_slot"], h["iv_n"]), np.repeat(ray, h["iv_n"]), h["sample_out"].reshape(-1, 4), st
+
+
+def _blocks(W, n_hidden, hidden):
+    """Views of a parameter array: per layer the weights [set][out][in] and the biases."""
+    out, off = [], 0
+    for fi, fo in synth.layer_dims(n_hidden, hidden):
+        out.append((W[:, off:off + fi * fo].reshape(len(W), fo, fi), W[:, off + fi * fo:off + fi * fo + fo]))
+        off += fi * fo + fo
+    return out
+
+
+DIR = 27   # the first input that is the ray's direction, as it was given
+
+
+@pytest.mark.parametrize("n_hidden,hidden", [(1, 32), (2, 64), (4, 64), (8, 64)])
+@pytest.mark.parametrize("case", ["overflow", "infinite", "nan", "largest"])
+def test_values_that_are_not_finite(case, n_hidden, hidden):
+    """Hidden sums that overflow, infinite, NaN and largest finite weights: every pre-activation
+    is the infinity or NaN that float32 arithmetic gives (a ReLU of NaN is 0), finite ones to
+    1e-6 of their size, and the rays are counted.  The last shape runs on the float32
+    instructions."""
+    import paper_2310_01881_amd as am
+    cfg = synth.scaled(synth.C1, n_hidden=n_hidden, hidden=hidden, max_leaves=8, s_max=17)
+    scene = Scene(cfg)
+    rng = np.random.default_rng(22)
+    n_rays, L = 200, scene.n_sets
+    d = (np.array([[0.7], [0.6], [0.4]]) + rng.uniform(-0.05, 0.05, (3, n_rays))).astype(np.float32)
+    o = (0.5 - 1.5 * d + rng.uniform(-0.2, 0.2, d.shape)).astype(np.float32)
+    scene.W = np.zeros_like(scene.W)
+    b = _blocks(scene.W, n_hidden, hidden)
+    w0, b0 = b[0]
+    w0[:, :, DIR:DIR + 3] = rng.uniform(0.1, 1.0, (L, hidden, 3))     # every unit positive
+    for l in range(1, n_hidden):
+        b[l][0][:] = rng.uniform(0.1, 1.0, (L, hidden, hidden)) / hidden
+    wo = b[n_hidden][0]
+    wo[:] = rng.uniform(-1.0, 1.0, wo.shape)
+    wo[:, 0] = np.abs(wo[:, 0])                                       # density: positive
+    k = 5                                                             # the unit in question
+    if case == "overflow":
+        w0[:, k, DIR:DIR + 2] = 3e38
+    elif case == "infinite":
+        w0[:, k, DIR] = np.inf
+        w0[:, k + 1, DIR + 1] = -np.inf                               # off
+        if n_hidden > 1:
+            b[1][0][:, 3, k + 1] = np.inf                             # an infinite weight of an input of 0
+    elif case == "nan":
+        w0[:, k, DIR] = np.nan                                        # off
+        if n_hidden > 1:
+            b[1][0][:, 2, 7] = np.nan
+        wo[:, 0, 1] = np.inf
+    else:
+        w0[:, k, DIR:DIR + 3] = (np.float32(3.4028234e38) * np.float32(0.9999), 0.0, 0.0)
+        for l in range(1, n_hidden + 1):
+            b[l][0][:, :, k] = 0.0
+        if n_hidden > 1:
+            b[1][0][:, 0, k] = 1e-30
+        else:
+            wo[:, 1, k] = 1e-30
+    ctx, tree, mlp = gpu_setup(scene, am.AMNERF_F32)
+    am.render(ctx, tree, mlp, to_dev(o), to_dev(d), cfg.s_max)
+    slot, ray, z, st = _sample_outputs(ctx, n_rays)
+    ref = np.empty((L, n_rays, 4), np.float32)
+    with np.errstate(all="ignore"):
+        for s in range(L):
+            a = np.zeros((n_rays, 30), np.float64)                    # (weights of positions are 0)
+            a[:, DIR:DIR + 3] = d.T
+            for l in range(n_hidden + 1):
+                wl, bl = b[l][0][s].astype(np.float64), b[l][1][s].astype(np.float64)
+                a = ((a[:, None, :] * wl[None]).sum(axis=2) + bl).astype(np.float32)
+                if l < n_hidden:
+                    a = np.fmax(a, 0.0).astype(np.float64)
+            ref[s] = a
+    want = ref[slot, ray]
+    odd = ~np.isfinite(want)
+    print("%s %dx%d: %d of %d values not finite, %d rays counted" % (
+        case, n_hidden, hidden, odd.sum(), odd.size, st["n_nonfinite"]), flush=True)
+    assert odd.any() == (case != "largest")
+    assert np.array_equal(np.isnan(z), np.isnan(want))
+    assert np.array_equal(np.isposinf(z), np.isposinf(want)) and np.array_equal(np.isneginf(z), np.isneginf(want))
+    np.testing.assert_allclose(z[~odd], want[~odd], rtol=0, atol=1e-6 * max(1.0, np.abs(want[~odd]).max(initial=0.0)))
+    assert (st["n_nonfinite"] > 0) == odd.any()
