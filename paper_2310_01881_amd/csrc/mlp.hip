@@ -599,7 +599,7 @@ hipError_t launch_mlp(const MlpGeom& g, const void* packed, uint32_t n_leaves, c
     if (g.hidden == 64) return launch_typed<64, true>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
     return launch_typed<32, true>(L, packed, n_leaves, bucket_off, tile_off, counts, rows, o, d, ray_stride, r0, out, st);
   }
-  // float32: the split kernel (twice as fast) wherever its weights fit a compute unit's LDS,
+  // float32: the split kernel (1.4 times as fast) wherever its weights fit a compute unit's LDS,
   // which leaves 8 layers of 64 to the float32 matrix instructions.  A training step keeps
   // those too: its backward pass recomputes the activations with them, and what differs in the
   // last bit between the two (1e-7) an optimiser that divides by the gradients' size carries

@@ -2,14 +2,20 @@
 //
 // The float32 matrix instructions (16x16x4) run at a sixteenth of the bfloat16 rate, and the
 // float32 leaf MLP was bound by them (0.75 of what they reach).  A float32 value is exactly
-// the sum of three bfloat16 values of 8 significant bits each, x = x1 + x2 + x3 with |x2| <=
-// 2^-8 |x| and |x3| <= 2^-16 |x|, and a product of two such values is exact in float32.  So
-// w x is taken as w1 x1 + (w1 x2 + w2 x1 + w2 x2 + w1 x3 + w3 x1): six matrix products, what
-// is left out is w2 x3 + w3 x2 + w3 x3, below 2^-24 |w x| (2^-26 on average: the weights'
-// parts are rounded to nearest, so their signs mix).  The five small products are summed in
-// an accumulator of their own, where a rounding is 2^-8 of one in the main sum, and added to
-// it once: a 64-wide layer then rounds its main sum 5 times (4 steps of 16 and the addition)
+// the sum of three bfloat16 values of 8 significant bits each (the split of Henry, Tang and
+// Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for higher-precision
+// computations", 2019), and a product of two such values is exact in float32.  Activations are
+// split by truncation, |x2| < 2^-7 |x| and |x3| < 2^-15 |x|, weights to nearest, |w2| <= 2^-8 |w|
+// and |w3| <= 2^-17 |w|.  Of the nine partial products w x takes eight; w3 x3 alone is left out,
+// below 2^-32 |w x|.  The leading products w1 x1 have an accumulator of their own, the seven
+// small ones another, whose roundings are 2^-6 of one in the main sum at most and which is added
+// to it once: a 64-wide layer then rounds its main sum 5 times (4 steps of 16 and the addition)
 // where the float32 instruction rounds it 16 times.
+//
+// Error against float64: a single product's is the float32 instruction's (largest 2^-24.01, rms
+// 2^-24.6 over values with all low bits set; without w2 x3 and w3 x2 they were 2^-22.3 and
+// 2^-23.5), a sample's lower at every shape (1..7 layers of 32 and 64): 1.44e-7 -> 1.04e-7 of the
+// output's rms at 4x64.  (A main sum within 2^-8 of the largest float may overflow early.)
 //
 // Instruction: 32x32x16 (it sustains 1.6 times the rate of 16x16x32, and here the order of a
 // sum is free).  Its accumulator leaves lane (h = lane / 32, c = lane % 32) rows 8 j + 4 h + i
@@ -21,10 +27,9 @@
 // 4x64 leaf take 87 KB of LDS, so a compute unit holds one block: two waves per SIMD, one
 // splitting while the other multiplies).  The output layer (4 rows) runs on the vector units:
 // a 32-row matrix step would be seven eighths padding.
-// Measured on the 61 M samples of an 800x800 frame, 4x64: 15.2 -> 9.4 ms (30 720 executed FLOP
-// per sample and product: 1.2 PFLOP/s of bfloat16 products, matrix cores busy 61 % of 16.4 M
-// cycles); error against float64 per sample 1.44e-7 -> 1.04e-7 of the output's rms (and lower
-// at every shape tried, 1..7 layers of 32 and 64).  What is left: about 1 300 vector
+// Measured on the 61 M samples of an 800x800 frame, 4x64: 15.2 -> 11.1 ms (30 720 executed FLOP
+// per sample and product: 1.35 PFLOP/s of bfloat16 products, matrix cores busy 65 % of 20.7 M
+// cycles; 9.4 ms with six products, 12 with nine).  What is left: about 1 400 vector
 // instructions per 32 samples, half of them the splits, which the matrix time hides in part
 // (a wave's raised priority during its products gained 3 %; interleaving one output block's
 // splits with the other's products, and a static priority between a SIMD's two waves, nothing).
@@ -161,13 +166,15 @@ __device__ __forceinline__ void layer32(const uint8_t* frag, const float* bias, 
 #pragma unroll
       for (int p = 0; p < 3; ++p)
         A[ob][p] = *reinterpret_cast<const bf16x8*>(frag + (ob * KS + ks) * kFragBytes + p * 1024 + lane * 16);
-    // the products (part of the weights, part of the inputs, sum), alternating between blocks
-    constexpr int pa[6] = {2, 0, 0, 1, 1, 0}, pb[6] = {0, 0, 2, 1, 0, 1};
+    // the products (part of the weights, part of the inputs, sum), smallest first and the leading
+    // one last, alternating between blocks
+    constexpr int kProducts = 8;
+    constexpr int pa[kProducts] = {1, 2, 0, 2, 1, 0, 1, 0}, pb[kProducts] = {2, 1, 2, 0, 1, 1, 0, 0};
 #pragma unroll
-    for (int q = 0; q < 6; ++q)
+    for (int q = 0; q < kProducts; ++q)
 #pragma unroll
       for (int ob = 0; ob < OB; ++ob) {
-        f32x16& acc = q == 1 ? big[ob] : small[ob];
+        f32x16& acc = q == kProducts - 1 ? big[ob] : small[ob];
         acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[ob][pa[q]], B[ks][pb[q]], acc, 0, 0, 0);
       }
   }

@@ -162,3 +162,43 @@ def test_values_that_are_not_finite(case, n_hidden, hidden):
     assert np.array_equal(np.isposinf(z), np.isposinf(want)) and np.array_equal(np.isneginf(z), np.isneginf(want))
     np.testing.assert_allclose(z[~odd], want[~odd], rtol=0, atol=1e-6 * max(1.0, np.abs(want[~odd]).max(initial=0.0)))
     assert (st["n_nonfinite"] > 0) == odd.any()
+
+
+@pytest.mark.parametrize("n_hidden,hidden,layer", [(1, 32, 0), (1, 64, 0), (3, 32, 1), (4, 64, 2), (7, 64, 6), (8, 64, 3)])
+def test_a_product_keeps_its_24_bits(n_hidden, hidden, layer):
+    """Each output is one product w x (x a component of the direction, the other layers passing it
+    on unchanged), for values whose low bits are all set and random ones.  Bar: one rounding of
+    the result, and eight of sums below 2^-6 of it: 2^-24 (1 + 2^-3)."""
+    import paper_2310_01881_amd as am
+    cfg = synth.scaled(synth.C1, n_hidden=n_hidden, hidden=hidden, max_leaves=8, s_max=17)
+    scene = Scene(cfg)
+    rng = np.random.default_rng(21)
+    n_rays, L = 400, scene.n_sets
+    x = rng.uniform(0.25, 1.0, (3, n_rays)).astype(np.float32)
+    x[:, ::2] = np.float32(0.5) * np.float32(1 + 2.0 ** -7 - 2.0 ** -23)
+    x[1, ::4] = np.float32(1 - 2.0 ** -24)
+    x[2, ::8] = np.float32(0.5) * np.float32(1 + 2.0 ** -8 - 2.0 ** -23)
+    w = rng.uniform(0.5, 2.0, (L, hidden)).astype(np.float32)
+    w[:, ::2] = np.float32(1 + 2.0 ** -8 - 2.0 ** -16 + 2.0 ** -17 - 2.0 ** -23)
+    w[1::2, 1] = np.float32(2 - 2.0 ** -23)
+    w[:, 2] = np.float32(1 + 2.0 ** -8 + 2.0 ** -17 - 2.0 ** -23)
+    scene.W = np.zeros_like(scene.W)
+    b = _blocks(scene.W, n_hidden, hidden)
+    for l in range(n_hidden):
+        for j in range(hidden):
+            b[l][0][:, j, DIR + j % 3 if l == 0 else j] = w[:, j] if l == layer else 1.0
+    units = rng.integers(0, hidden, (L, 4))
+    units[:, :3] = (0, 1, 2)
+    for s in range(L):
+        for k in range(4):
+            b[n_hidden][0][s, k, units[s, k]] = 1.0
+    ctx, tree, mlp = gpu_setup(scene, am.AMNERF_F32)
+    o = (0.5 - 1.5 * x + rng.uniform(-0.2, 0.2, x.shape)).astype(np.float32)
+    am.render(ctx, tree, mlp, to_dev(o), to_dev(x), cfg.s_max)
+    slot, ray, z, _ = _sample_outputs(ctx, n_rays)
+    u = units[slot]
+    ref = w[slot[:, None], u].astype(np.float64) * x[u % 3, ray[:, None]].astype(np.float64)
+    e = np.abs(z - ref) / ref
+    print("%d x %d, layer %d: %d products, largest relative error 2^%.2f, rms 2^%.2f" % (
+        n_hidden, hidden, layer, e.size, np.log2(e.max()), np.log2(np.sqrt((e * e).mean()))))
+    assert e.max() <= 2.0 ** -24 * (1 + 2.0 ** -3)
