@@ -483,7 +483,10 @@ int amnerf_timing_collect_backward(amnerf_ctx* ctx, double* stage_ms_host, int64
  *   g_depth_dev   device float32[n_rays] or NULL (zero)
  *   g_opacity_dev device float32[n_rays] or NULL (zero)
  *   grad_dev      device float32[n_leaves][P], overwritten (master parameter layout)
- * Supported shapes: n_hidden 1 .. 4, hidden 32 or 64. */
+ * Supported shapes: n_hidden 1 .. 4, hidden 32 or 64.
+ * A pass recorded in a HIP graph (after an eager one of its sizes) differentiates, at each
+ * replay, the latest render of the same sizes, until a call on the context enlarges its
+ * workspaces, which moves them. */
 int amnerf_render_backward(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_mlp* mlp,
                            const amnerf_rays* rays, const float* g_rgb_dev,
                            const float* g_depth_dev, const float* g_opacity_dev,

@@ -127,7 +127,6 @@ struct amnerf_ctx {
   IvSet use = {};
   uint32_t *bucket_off = nullptr, *perm = nullptr, *tile_off = nullptr, *srec_ray = nullptr;
   uint32_t *sidx = nullptr, *ssb = nullptr;   // sorted intervals
-  bool expanded = false;          // the sample records (srec_ray, srec_t, perm) are written
   float *smp_out = nullptr, *srec_t = nullptr;
   uint32_t* ray_used = nullptr;   // samples composited per ray (the early-termination count)
   bool last_uses_arena3 = false;  // the last render's intervals live in the third arena
@@ -960,10 +959,9 @@ struct Work {
 // 16 bytes for an interval where those take 12 for a sample).
 size_t carve(char* base, uint64_t nr, uint64_t niv, uint64_t ns, const SortPlan& sp, Work& w, bool rounds, bool fused) {
   Carve c{base};
-  const uint64_t mat_n = (uint64_t)sp.n_leaves * sp.nseg_max;
-  w.trav_words = trav_state_words(nr);
-  w.chain_words = w.trav_words + scan_state_words(mat_n);
-  w.chain = c.take<uint64_t>(w.chain_words);
+  // What outlives the render (backward, calibration, inspection) comes first, at places that do
+  // not depend on the rows' source, the rounds or the sort's segments: a backward pass recorded
+  // in a graph finds them there whichever render of these sizes ran before its replay.
   w.iv_off = c.take<uint32_t>(nr + 1);
   w.smp_off = c.take<uint32_t>(nr + 1);
   w.iv_t0 = c.take<float>(niv);
@@ -971,13 +969,12 @@ size_t carve(char* base, uint64_t nr, uint64_t niv, uint64_t ns, const SortPlan&
   w.iv_key = c.take<uint32_t>(niv);
   w.iv_ray = c.take<uint32_t>(niv);
   w.iv_base = c.take<uint32_t>(niv);
-  w.mat = c.take<uint32_t>(mat_n + 1);
-  w.mat_smp = c.take<uint32_t>(mat_n + 1);
   w.sidx = c.take<uint32_t>(niv);
   w.ssb = c.take<uint32_t>(niv + 1);
   w.bucket_off = c.take<uint32_t>(sp.n_leaves + 1);
   w.tile_off = c.take<uint32_t>(sp.n_leaves + 1);
-  w.win = c.take<uint32_t>(fused ? 4 * (ns / kMlpTileRows + sp.n_leaves) : 0);
+  w.smp_out = c.take<float>(4 * ns);
+  w.ray_used = c.take<uint32_t>(nr);
   const size_t rec_at = (c.off + 255) / 256 * 256;
   w.srec_ray = c.take<uint32_t>(ns);
   w.srec_t = c.take<float>(ns);
@@ -990,8 +987,13 @@ size_t carve(char* base, uint64_t nr, uint64_t niv, uint64_t ns, const SortPlan&
     if (want > have) c.off = rec_at + want;
     w.rec_cap = (c.off - rec_at) / sizeof(SortRec);
   }
-  w.smp_out = c.take<float>(4 * ns);
-  w.ray_used = c.take<uint32_t>(nr);
+  const uint64_t mat_n = (uint64_t)sp.n_leaves * sp.nseg_max;
+  w.trav_words = trav_state_words(nr);
+  w.chain_words = w.trav_words + scan_state_words(mat_n);
+  w.chain = c.take<uint64_t>(w.chain_words);
+  w.mat = c.take<uint32_t>(mat_n + 1);
+  w.mat_smp = c.take<uint32_t>(mat_n + 1);
+  w.win = c.take<uint32_t>(fused ? 4 * (ns / kMlpTileRows + sp.n_leaves) : 0);
   const uint64_t nsr = rounds ? ns : 0, nrr = rounds ? nr : 0, lr = rounds ? sp.n_leaves + 1 : 0;
   w.r_flags = c.take<uint32_t>(nsr + 1);
   w.r_pos = c.take<uint32_t>(nsr + 1);
@@ -1284,7 +1286,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
     HIP_TRY(mark(3));
     if (!sb.rec)
       HIP_TRY(launch_expand(sb.sidx, placed.rec, sb.ssb, use, r0, jitter, p->jitter_seed, w.srec_ray, w.srec_t, w.perm,
-                            cs));
+                            nullptr, cs));
     HIP_TRY(mark(4));
     if (!rounds) {
       const RowSource rows = {sb.rec, sb.ssb, sb.win, w.srec_ray, w.srec_t, w.perm};
@@ -1364,7 +1366,6 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
   ctx->srec_t = wl->srec_t;
   ctx->sidx = sb.sidx;
   ctx->ssb = sb.ssb;
-  ctx->expanded = sb.rec == nullptr;
   ctx->ray_used = wl->ray_used;
   ctx->last_uses_arena3 = p->proposal != nullptr || occ != nullptr;
   ctx->last_tree = tree;
@@ -1429,13 +1430,13 @@ extern "C" int amnerf_render_stats_get(amnerf_ctx* ctx, amnerf_render_stats* out
 
 // The last render's sample records, for what reads them after it (the backward pass,
 // calibration, inspection): a render whose MLPs read the sorted intervals has not written them,
-// and their memory still holds the intervals' records, which nothing needs any more.
-static int ensure_expanded(amnerf_ctx* ctx, hipStream_t st) {
-  if (ctx->expanded) return AMNERF_OK;
-  const int jitter = (ctx->last_params.flags & AMNERF_JITTER) ? 1 : 0;
-  HIP_TRY(launch_expand(ctx->sidx, nullptr, ctx->ssb, ctx->use, 0, jitter, ctx->last_params.jitter_seed, ctx->srec_ray,
-                        ctx->srec_t, ctx->perm, st));
-  ctx->expanded = true;
+// and their memory held the intervals' records, which nothing needs any more.  Nothing on the
+// host remembers whether this has run: the launch is enqueued each time and the render's own
+// counters decide on the device, so that a reader in a graph, replayed after other renders, or
+// on another stream has its own before it.  Every run writes the same values.
+static int expand_records(amnerf_ctx* ctx, hipStream_t st) {
+  HIP_TRY(launch_expand(ctx->sidx, nullptr, ctx->ssb, ctx->use, 0, 0, 0, ctx->srec_ray, ctx->srec_t, ctx->perm,
+                        ctx->counts, st));
   return AMNERF_OK;
 }
 
@@ -1456,7 +1457,7 @@ extern "C" int amnerf_render_inspect(amnerf_ctx* ctx, const amnerf_inspect* o, v
   };
   const IvSet& u = ctx->use;
   if (o->perm) {
-    rc = ensure_expanded(ctx, st);
+    rc = expand_records(ctx, st);
     if (rc) return rc;
   }
   HIP_TRY(cp(o->ray_iv_off, u.iv_off, 4 * (nr + 1)));
@@ -1575,8 +1576,10 @@ int backward_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_mlp* ml
   }
   auto mark = [&](int k) -> hipError_t { return ev ? hipEventRecord(ev->ev[k], st) : hipSuccess; };
   if (alone) HIP_TRY(mark(AMNERF_BWD_STAGE_COMPOSITE));
-  rc = ensure_expanded(ctx, st);   // (counted with the compositing stage)
-  if (rc) return rc;
+  if (!in_step) {   // (a step's render has written them; counted with the compositing stage)
+    rc = expand_records(ctx, st);
+    if (rc) return rc;
+  }
   HIP_TRY(launch_comp_bwd(nr, ctx->use, ctx->smp_out, 0, jitter, p.jitter_seed, ctx->ray_used, g_rgb, g_depth,
                           g_opac, w.gpre, st));
   HIP_TRY(mark(AMNERF_BWD_STAGE_MLP));
@@ -1622,7 +1625,7 @@ extern "C" int amnerf_mlp_calibrate(amnerf_ctx* ctx, const amnerf_mlp_shape* s, 
     return fail(AMNERF_EINVAL, "amnerf_mlp_calibrate: %d parameter sets, the last render used %u", n_leaves,
                 ctx->last_leaves);
   HIP_TRY(hipSetDevice(ctx->device));
-  rc = ensure_expanded(ctx, (hipStream_t)stream);
+  rc = expand_records(ctx, (hipStream_t)stream);
   if (rc) return rc;
   HIP_TRY(launch_act_max(s->n_hidden, master, (uint32_t)n_leaves, ctx->bucket_off, ctx->tile_off, ctx->counts,
                          ctx->srec_ray, ctx->srec_t, rays->o_dev, rays->d_dev, rays->n_rays, 0, act_max,

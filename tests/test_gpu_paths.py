@@ -335,3 +335,45 @@ def test_samples_behind_a_stop_count_for_nothing(dtype):
     torch.cuda.synchronize()
     assert torch.isfinite(grads[0]).all() and grads[0].abs().max() > 0
     assert torch.equal(grads[0], grads[1])
+
+
+@pytest.mark.parametrize("dtype", [am.AMNERF_F32, am.AMNERF_BF16])
+def test_backward_recorded_in_a_graph(dtype):
+    """A backward pass recorded after an eager one, replayed after renders of other rays whose
+    leaf MLPs read sorted intervals (plain) or sample records (jittered, in rounds): the gradient
+    of an eager backward of the same render each time."""
+    scene = small_scene(s_max=96)
+    ctx, tree, mlp = gpu_setup(scene, dtype)
+    master = to_dev(scene.W)
+    n = 1500
+    o, d = (to_dev(a) for a in synth.random_rays(n, 19))
+    g = to_dev(np.random.default_rng(20).standard_normal((n, 3)).astype(np.float32))
+    rgb, eager, replayed = torch.empty((n, 3), device="cuda:0"), torch.empty_like(master), torch.empty_like(master)
+
+    def render(**kw):
+        am.amnerf_render(ctx.h, tree.h, mlp.desc, o, d, 96, rgb, **kw)
+
+    def backward(grad):
+        am.amnerf_render_backward(ctx.h, tree.h, mlp.desc, o, d, g, grad)
+
+    render(ert_rounds=True)   # the largest workspace of these: it must not move once recorded
+    render()
+    backward(eager)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        backward(replayed)
+    seen = []
+    for k, kw in enumerate([{}, {}, dict(jitter=True, seed=5), {}, dict(ert_rounds=True), {}]):
+        for t, a in zip((o, d), synth.random_rays(n, 30 + k)):
+            t.copy_(to_dev(a))
+        print("replay after a render with", kw, flush=True)
+        render(**kw)
+        replayed.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        backward(eager)
+        torch.cuda.synchronize()
+        assert torch.isfinite(eager).all() and torch.equal(replayed, eager), (k, kw)
+        seen.append(eager.clone())
+    assert not torch.equal(seen[0], seen[1])
