@@ -377,3 +377,63 @@ def test_backward_recorded_in_a_graph(dtype):
         assert torch.isfinite(eager).all() and torch.equal(replayed, eager), (k, kw)
         seen.append(eager.clone())
     assert not torch.equal(seen[0], seen[1])
+
+
+def pair_crossing(s, o, d):
+    """(s - o) / d as a float32 pair by division: TwoSum of the numerator, the division's exact
+    remainder (float64 holds it: two 24-bit factors), its quotient, normalised."""
+    s, o, d = (np.asarray(a, np.float32) for a in (s, o, d))
+    hi = s - o
+    bb = hi - s
+    lo = (s - (hi - bb)) + (-o - bb)
+    q0 = hi / d
+    r = (hi.astype(np.float64) - q0.astype(np.float64) * d.astype(np.float64)).astype(np.float32) + lo
+    q1 = r / d
+    h = q0 + q1
+    return h, q1 - (h - q0)
+
+
+def pair_pick(pairs, largest):
+    """Per element the largest or smallest of float pairs (high parts, then low parts)."""
+    h, l = pairs[0]
+    for a, b in pairs[1:]:
+        take = (h < a) | ((h == a) & (l < b)) if largest else (a < h) | ((a == h) & (b < l))
+        h, l = np.where(take, a, h), np.where(take, b, l)
+    return h, l
+
+
+def test_crossings_have_the_bits_of_a_division():
+    """The first interval of each ray, from inside the box to 2^18 away: entry and length bit for
+    bit those of crossings formed by division (later intervals take their exit from the stack,
+    whose low parts are shorter)."""
+    scene = small_scene(max_leaves=64, max_depth=9, s_max=33)
+    ctx, tree, mlp = gpu_setup(scene, am.AMNERF_F32)
+    rng = np.random.default_rng(14)
+    n = 60000
+    u = rng.standard_normal((3, n))
+    u /= np.linalg.norm(u, axis=0)
+    dist = 2.0 ** rng.uniform(-2, 18, n)
+    tgt = rng.uniform(0.05, 0.95, (3, n))
+    o = (tgt + u * dist).astype(np.float32)
+    d = (tgt - o.astype(np.float64))
+    d = (d / np.linalg.norm(d, axis=0)).astype(np.float32)
+    assert (np.abs(d) > 2.0 ** -100).all()
+    render_all(scene, ctx, tree, mlp, o, d, 33)
+    _, ins = fetch_inspect(ctx, n, scene.n_sets)
+    off = ins["ray_iv_off"].astype(np.int64)
+    r = np.flatnonzero(np.diff(off) > 0)
+    i = off[r]
+    o, d = o[:, r], d[:, r]
+    boxes = scene.otree.leaf_boxes()[ins["iv_slot"][i]].astype(np.float32) / np.float32(scene.cfg.grid_n)
+    near, far = [(np.zeros(len(r), np.float32),) * 2], []
+    for a in range(3):
+        near.append(pair_crossing(np.where(d[a] > 0, 0.0, 1.0), o[a], d[a]))
+        far.append(pair_crossing(np.where(d[a] > 0, boxes[:, 3 + a], boxes[:, a]), o[a], d[a]))
+    t0, l0 = pair_pick(near, True)
+    t1, l1 = pair_pick(far, False)
+    dt = (t1 - t0) + (l1 - l0)
+    print("rays %d, of them more than 2^12 away %d; other lengths %d" % (
+        len(r), (t0 > 4096).sum(), (ins["iv_dt"][i] != dt).sum()), flush=True)
+    assert (t0 > 4096).sum() > 500 and (t0 == 0).sum() > 500
+    assert np.array_equal(ins["iv_t0"][i], t0)
+    assert np.array_equal(ins["iv_dt"][i], dt)
