@@ -61,16 +61,23 @@ __device__ __forceinline__ DF plane_t(float s, float o, float d, float inv) {
   return {h, l};
 }
 
-// The same by division, for directions with a component so small that 1 / d overflows.
+// The same by division, for components that are so small that the quotient may overflow, or so
+// large that the reciprocal is no normal number.  Small ones are scaled by 2^64 (exact) and the
+// pair scaled back: t is then an infinity of the right sign where it exceeds the float range,
+// instead of the NaN of an infinity's remainder.
 __device__ __forceinline__ DF plane_t_div(float s, float o, float d) {
+#pragma clang fp contract(off)
+  const float sc = fabsf(d) < 0x1p-100f ? 0x1p64f : 1.f, ds = d * sc;
   DF num = two_sum(s, -o);
-  float q0 = num.hi / d;
-  float r = fmaf(-q0, d, num.hi);
+  float q0 = num.hi / ds;
+  if (isinf(q0)) return {q0, 0.f};
+  float r = fmaf(-q0, ds, num.hi);
   r += num.lo;
-  float q1 = r / d;
+  float q1 = r / ds;
   float h = q0 + q1;
   float l = q1 - (h - q0);
-  return {h, l};
+  h *= sc;
+  return {h, isinf(h) ? 0.f : l * sc};
 }
 
 // (bitwise: three compares and two mask operations, no branch)
@@ -217,9 +224,10 @@ __device__ int traverse_one(const DevNode* nodes, const Ahs ahs, const V3 o, con
 template <int B, bool AHS, typename Ahs, typename Put>
 __device__ __forceinline__ int traverse(const DevNode* nodes, const Ahs ahs, const V3 o, const V3 dir, int cap,
                                         uint2* st, Put put) {
-  // some ray of the wave has a nonzero component whose reciprocal overflows
-  auto tiny = [](float v) { return v != 0.f && fabsf(v) < 1.1754944e-38f; };
-  if (__ballot(tiny(dir.x) || tiny(dir.y) || tiny(dir.z)) != 0)
+  // some ray of the wave has a nonzero component for plane_t_div (origins within 2^27 cannot
+  // make the quotient of one of 2^-100 overflow)
+  auto odd = [](float v) { return v != 0.f && !(fabsf(v) >= 0x1p-100f && fabsf(v) <= 0x1p126f); };
+  if (__ballot(odd(dir.x) || odd(dir.y) || odd(dir.z)) != 0)
     return traverse_one<B, AHS, true>(nodes, ahs, o, dir, cap, st, put);
   return traverse_one<B, AHS, false>(nodes, ahs, o, dir, cap, st, put);
 }

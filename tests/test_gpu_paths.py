@@ -437,3 +437,23 @@ def test_crossings_have_the_bits_of_a_division():
     assert (t0 > 4096).sum() > 500 and (t0 == 0).sum() > 500
     assert np.array_equal(ins["iv_t0"][i], t0)
     assert np.array_equal(ins["iv_dt"][i], dt)
+
+
+@pytest.mark.parametrize("tiny", [1.4e-45, 1e-39, 5e-39, 1.17e-38, 2e-38])
+def test_tiny_direction_components(tiny):
+    """Components down to the smallest there is: the intervals are those of a component of zero
+    (the ray moves less than 1e-37 along it), the other planes' crossings the same to the bit."""
+    scene = small_scene(s_max=33)
+    ctx, tree, mlp = gpu_setup(scene, am.AMNERF_F32)
+    o, d = synth.random_rays(600, 4)
+    for r in range(0, 600, 3):
+        d[r % 9 // 3, r] = 0.0
+    small = d.copy()
+    for r in range(0, 600, 3):
+        small[r % 9 // 3, r] = np.float32(tiny) * (1 if r % 2 else -1)
+    got = []
+    for dd in (d, small):
+        render_all(scene, ctx, tree, mlp, o, dd, 33)
+        got.append(fetch_inspect(ctx, 600, scene.n_sets)[1])
+    for k in ("ray_iv_off", "iv_slot", "iv_n", "iv_t0", "iv_dt"):
+        assert np.array_equal(got[0][k], got[1][k]), k
