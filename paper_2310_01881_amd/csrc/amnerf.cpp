@@ -1121,35 +1121,6 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
   Work& w0 = ws[0];
   // early termination in rounds of 64-sample windows (a single window needs no rounds)
   const bool rounds = (p->flags & AMNERF_ERT_ROUNDS) && p->s_max > 64;
-  const int lanes_max = (uint64_t)R > chunk && !out->weights_dev && !static_ws ? ctx->render_lanes : 1;
-  // The MLPs read the sorted intervals, unless sample records are needed in any case (rounds
-  // compact them; jittered strata have no place in an interval's record) or the workspace is
-  // limited and only the layout with sample records fits it (the intervals' records may take
-  // 4 bytes per possible interval more).  Expanding first: 800x800 frame 2.38 against 2.08 ms,
-  // 64x64 87 against 54 us, 1920x1080 float8 7.01 against 6.00 ms (with the scans in one launch
-  // each).
-  bool fused = !rounds && !jitter && !in_step;
-  SortPlan sp = make_sort_plan(niv_max, L, fused);
-  size_t need = carve(nullptr, chunk, niv_max, ns_max, sp, w0, rounds, fused);
-  if (fused && ((static_ws && need > static_bytes) ||
-                (ctx->cap && need * (size_t)lanes_max + ctx->arena2_bytes + ctx->arena3_bytes > ctx->cap))) {
-    fused = false;
-    sp = make_sort_plan(niv_max, L, false);
-    need = carve(nullptr, chunk, niv_max, ns_max, sp, w0, rounds, false);
-  }
-  if (static_ws) {
-    if ((uint64_t)R > chunk)
-      return fail(AMNERF_ECAPACITY, "amnerf_render_static: %lld rays exceed one pass (%llu at s_max %d)",
-                  (long long)R, (unsigned long long)chunk, p->s_max);
-    if (need > static_bytes)
-      return fail(AMNERF_ECAPACITY, "amnerf_render_static: the call needs %zu bytes of workspace, the static "
-                  "workspace holds %zu", need, static_bytes);
-    carve(static_ws, chunk, niv_max, ns_max, sp, w0, rounds, fused);
-  } else {
-    rc = ensure_arena(ctx, need);
-    if (rc) return rc;
-    carve((char*)ctx->arena, chunk, niv_max, ns_max, sp, w0, rounds, fused);
-  }
   // More than one chunk (and no per-sample weights, whose offsets need the chunks in
   // order): chunk k runs on lane k mod n_lanes -- lanes beyond the caller's stream have their
   // own stream, workspace and counters -- so one chunk's latency-bound stages overlap
@@ -1157,10 +1128,57 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
   // caller's stream waits for them on exit, so the call stays asynchronous on `stream`.
   const bool pipe = (uint64_t)R > chunk && !out->weights_dev && !static_ws;
   const int n_lanes = pipe ? (int)std::min<uint64_t>((uint64_t)ctx->render_lanes, ((uint64_t)R + chunk - 1) / chunk) : 1;
-  for (int i = 1; i < n_lanes; ++i) {
-    rc = lane_prepare(ctx, i, need);
+  // The MLPs read the sorted intervals, unless sample records are needed in any case (rounds
+  // compact them; jittered strata have no place in an interval's record) or the workspace is
+  // limited and only the layout with sample records fits it (the intervals' records may take
+  // 4 bytes per possible interval more).  Expanding first: 800x800 frame 2.38 against 2.08 ms,
+  // 64x64 87 against 54 us, 1920x1080 float8 7.01 against 6.00 ms (with the scans in one launch
+  // each).
+  const bool want_fused = !rounds && !jitter && !in_step;
+  bool fused = false;
+  SortPlan sp = {};
+  size_t need = 0;
+  auto layout = [&](bool intervals) {
+    fused = intervals;
+    sp = make_sort_plan(niv_max, L, fused);
+    need = carve(nullptr, chunk, niv_max, ns_max, sp, w0, rounds, fused);
+  };
+  auto reserve = [&]() -> int {
+    int r = ensure_arena(ctx, need);
+    for (int i = 1; i < n_lanes && !r; ++i) r = lane_prepare(ctx, i, need);
+    return r;
+  };
+  if (static_ws) {
+    if ((uint64_t)R > chunk)
+      return fail(AMNERF_ECAPACITY, "amnerf_render_static: %lld rays exceed one pass (%llu at s_max %d)",
+                  (long long)R, (unsigned long long)chunk, p->s_max);
+    layout(want_fused);
+    if (fused && need > static_bytes) layout(false);
+    if (need > static_bytes)
+      return fail(AMNERF_ECAPACITY, "amnerf_render_static: the call needs %zu bytes of workspace, the static "
+                  "workspace holds %zu", need, static_bytes);
+    carve(static_ws, chunk, niv_max, ns_max, sp, w0, rounds, fused);
+  } else {
+    // Under a cap the workspaces are made for sample records, and the layout with intervals is
+    // taken where it fits them (they have an eighth to spare): what a cap admits, this call or a
+    // later one, is then the same whichever is taken.
+    layout(want_fused && !ctx->cap);
+    rc = reserve();
+    if (rc == AMNERF_ENOMEM && fused) {
+      (void)hipGetLastError();   // (the allocation's error is answered here)
+      layout(false);
+      rc = reserve();
+    }
     if (rc) return rc;
-    carve((char*)ctx->lanes[i - 1].arena, chunk, niv_max, ns_max, sp, ws[i], rounds, fused);
+    if (want_fused && ctx->cap) {
+      size_t room = ctx->arena_bytes;
+      for (int i = 1; i < n_lanes; ++i) room = std::min(room, ctx->lanes[i - 1].arena_bytes);
+      layout(true);
+      if (need > room) layout(false);
+    }
+    carve((char*)ctx->arena, chunk, niv_max, ns_max, sp, w0, rounds, fused);
+    for (int i = 1; i < n_lanes; ++i)
+      carve((char*)ctx->lanes[i - 1].arena, chunk, niv_max, ns_max, sp, ws[i], rounds, fused);
   }
   if (R == 0) HIP_TRY(launch_pass_begin(ctx->counts, true, nullptr, 0, st));
   for (int i = 1; i < n_lanes; ++i) {
@@ -1230,7 +1248,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
       const uint32_t niv_plain = ctx->counts_host[li].n_iv;
       const amnerf_proposal* q = p->proposal;
       const uint64_t niv_plan = (uint64_t)niv_plain + (uint64_t)nr * (uint64_t)std::min(q->cap, p->s_max);
-      SortPlan spp = make_sort_plan(niv_plan, L, fused);
+      SortPlan spp = make_sort_plan(niv_plan, L, fused && !ctx->cap);
       PropWork pw;
       rc = ensure_arena3_for(ctx, li, carve_prop(nullptr, nr, niv_plain, niv_plan, spp, pw));
       if (rc) return rc;
@@ -1254,7 +1272,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
       // (s_max + m) / 2 of them); buffers sized from the plain interval count
       const uint64_t niv_plain = ctx->counts_host[li].n_iv;
       const uint64_t niv_plan = (niv_plain + (uint64_t)nr * (uint64_t)p->s_max) / 2 + nr;
-      SortPlan spp = make_sort_plan(niv_plan, L, fused);
+      SortPlan spp = make_sort_plan(niv_plan, L, fused && !ctx->cap);
       PropWork pw;
       rc = ensure_arena3_for(ctx, li, carve_prop(nullptr, nr, 1, niv_plan, spp, pw));
       if (rc) return rc;

@@ -457,3 +457,58 @@ def test_tiny_direction_components(tiny):
         got.append(fetch_inspect(ctx, 600, scene.n_sets)[1])
     for k in ("ray_iv_off", "iv_slot", "iv_n", "iv_t0", "iv_dt"):
         assert np.array_equal(got[0][k], got[1][k]), k
+
+
+@pytest.mark.parametrize("backward", [False, True])
+def test_a_workspace_cap_decides_the_row_source_not_the_result(backward):
+    """Under a workspace cap a render takes the layout with sorted intervals only where it fits a
+    workspace made for sample records: with 255 samples per ray, the cap that a jittered render
+    (which has records in any case), or one and its backward, just fit is enough without jitter
+    too, and the bits are those of a context without a cap."""
+    scene = Scene(synth.scaled(synth.C2, grid_n=64, max_leaves=300, max_depth=12, n_hidden=2, hidden=32))
+    assert scene.n_sets >= 255
+    o, d = (to_dev(a) for a in synth.random_rays(3000, 17))
+    W = to_dev(scene.W)
+    g = torch.ones((3000, 3), device="cuda:0")
+
+    def run(cap, jitter):
+        ctx = am.Context(0, cap)
+        tree = am.Tree(ctx, scene.grid, scene.cfg.grid_n, scene.cfg.max_depth, scene.cfg.max_leaves)
+        mlp = am.Mlp(ctx, W, 2, 32, am.AMNERF_BF16, scene.n_sets)
+        rgb, grad = torch.empty((3000, 3), device="cuda:0"), torch.zeros_like(W)
+        try:
+            am.amnerf_render(ctx.h, tree.h, mlp.desc, o, d, 255, rgb, jitter=jitter)
+            if backward:
+                am.amnerf_render_backward(ctx.h, tree.h, mlp.desc, o, d, g, grad)
+        except am.AmnerfError as e:
+            assert e.code == am.AMNERF_ENOMEM
+            return None
+        torch.cuda.synchronize()
+        return rgb, grad
+
+    lo, hi = 1 << 20, 1 << 31
+    while hi - lo > 1 << 12:
+        mid = (lo + hi) // 2
+        if run(mid, True) is None:
+            lo = mid
+        else:
+            hi = mid
+    print("records fit %d bytes" % hi, flush=True)
+    free = run(0, False)
+    for cap in (hi, hi + (hi >> 6), hi + (hi >> 4), 2 * hi):
+        got = run(cap, False)
+        assert got is not None, cap
+        assert torch.equal(got[0], free[0]) and torch.equal(got[1], free[1]), cap
+
+
+def test_static_render_where_only_records_fit():
+    """Rays between the largest static call on sorted intervals and the largest on sample
+    records: the bits of the same render in the context's own workspace."""
+    scene = Scene(synth.scaled(synth.C2, grid_n=64, max_leaves=300, max_depth=12, n_hidden=2, hidden=32))
+    ctx, tree, mlp = gpu_setup(scene, am.AMNERF_BF16)
+    # per ray 36 bytes per interval and 28 per sample; 40 per interval with the intervals' records
+    n = int(am.amnerf_render_static_capacity() / (40 * 255 + 28 * 255)) + 40
+    o, d = (to_dev(a) for a in synth.random_rays(n, 18))
+    a, _, _, _ = ert.render(ctx, tree, mlp, o, d, 255, 0, static=True)
+    b, _, _, _ = ert.render(ctx, tree, mlp, o, d, 255, 0)
+    ert.compare(a, b, n)
