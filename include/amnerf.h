@@ -381,8 +381,9 @@ typedef struct {
   int64_t n_nonfinite;    /* rays whose rgb, depth or opacity is not finite */
   int64_t n_fallback;     /* rays rendered with every plain slot under a proposal */
   int64_t n_plain_samples;/* samples the plain sampler would have taken */
-  int64_t n_unreached;    /* interval entries the traversal left unwritten: always 0 (it walks
-                             every ray once, writing what it counts) */
+  int64_t n_unreached;    /* samples by which the counts in the interval entries, as the sort
+                             read them, and the rays' sample offsets disagree: 0, or an entry
+                             was left unwritten */
   int64_t n_composited;   /* samples composited before early termination (the stop sample
                              included); n_samples - n_composited were evaluated by the MLPs
                              but lie past the termination point */
@@ -435,7 +436,7 @@ typedef struct {
 int amnerf_render_inspect(amnerf_ctx* ctx, const amnerf_inspect* out, void* stream);
 
 /* ---- stage timing -------------------------------------------------------------------- */
-#define AMNERF_STAGE_TRAVERSE 0   /* both traversal passes and the per-ray offset scans */
+#define AMNERF_STAGE_TRAVERSE 0   /* traversal: intervals and the per-ray offsets */
 #define AMNERF_STAGE_PROPOSAL 1   /* proposal inference, selection and planned intervals */
 #define AMNERF_STAGE_SORT 2       /* slot histogram, scans, stable scatter, bucket/tile offsets */
 #define AMNERF_STAGE_EXPAND 3     /* sorted interval -> per-sample records (jittered renders and

@@ -325,8 +325,9 @@ __global__ __launch_bounds__(kThreads, 8) void k_composite(
 }
 
 // End of a chunk: counts->composited += sum of ray_used[0, nr) (block sums in a fixed order, one
-// integer atomic per block), and the chunk's totals are recorded for the host and the global
-// sample base advanced.  (As two launches 1.4 us more a pass: a 64x64 render of a small scene 49.3 -> 47.8 us.)
+// integer atomic per block), and the chunk's totals are recorded for the host, the samples of the
+// sorted intervals checked against the rays' offsets, and the global sample base advanced.  (As
+// two launches 1.4 us more a pass: a 64x64 render of a small scene 49.3 -> 47.8 us.)
 __global__ __launch_bounds__(kThreads) void k_chunk_finish(uint32_t nr, const uint32_t* __restrict__ ray_used,
                                                            ChunkCounts* __restrict__ counts, const uint32_t* smp_total,
                                                            const uint32_t* iv_total, const uint32_t* plain_total,
@@ -343,8 +344,10 @@ __global__ __launch_bounds__(kThreads) void k_chunk_finish(uint32_t nr, const ui
   for (int w = 0; w < kThreads / 64; ++w) t += sh[w];
   if (t) atomicAdd(reinterpret_cast<unsigned long long*>(&counts->composited), (unsigned long long)t);
   if (blockIdx.x != 0) return;
-  if (!rounds) counts->evaluated += *smp_total;   // (in rounds: added by each round's selection)
-  counts->smp_global += *smp_total;
+  const uint32_t n = *smp_total;
+  if (!rounds) counts->evaluated += n;   // (in rounds: added by each round's selection)
+  counts->unreached += n > counts->n_smp ? n - counts->n_smp : counts->n_smp - n;
+  counts->smp_global += n;
   counts->iv_global += *iv_total;
   counts->plain_smp += *plain_total;
 }

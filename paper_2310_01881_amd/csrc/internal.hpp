@@ -34,7 +34,8 @@ struct ChunkCounts {
   uint64_t nonfinite;   // rays with a non-finite output (accumulated over chunks)
   uint64_t fallback;    // rays that fell back to plain sampling under a proposal
   uint64_t plain_smp;   // samples of the plain sampler (before any proposal)
-  uint64_t unreached;   // always 0 (the traversal walks once, so no entry can be left unwritten)
+  uint64_t unreached;   // samples by which the intervals as written and the rays' offsets disagree
+                        // (accumulated; 0 unless an entry was left unwritten)
   uint64_t composited;  // samples composited before early termination (accumulated)
   uint64_t evaluated;   // samples the leaf MLPs evaluated (accumulated)
 };
