@@ -282,9 +282,10 @@ def test_float32_training_step_forward(n_hidden, hidden):
     assert e <= 5e-5
 
 
+@pytest.mark.parametrize("density", [False, True])
 @pytest.mark.parametrize("dtype", [am.AMNERF_F32, am.AMNERF_BF16])
-def test_samples_behind_a_stop_count_for_nothing(dtype):
-    """One leaf's colours are NaN, behind opaque leaves for some rays.  A ray that stops before it
+def test_samples_behind_a_stop_count_for_nothing(dtype, density):
+    """One leaf's colours (and density) are NaN, behind opaque leaves for some rays.  A ray that stops before it
     gives the bits it gives with finite colours there: in a full launch (beside rays that march
     on), alone, and in rounds; its gradient too.  Every ray that reaches the leaf is counted."""
     scene = small_scene(s_max=192)
@@ -293,7 +294,7 @@ def test_samples_behind_a_stop_count_for_nothing(dtype):
     W[1:5, at] = 300.0                        # opaque: a ray stops within a few samples
     W[5:, at] = -9.0                          # all but empty
     bad = W.copy()
-    bad[0, at + 1:at + 4] = np.nan
+    bad[0, at if density else at + 1:at + 4] = np.nan
     scene.W = W
     ctx, tree, mlp = gpu_setup(scene, dtype)
     master = to_dev(bad)
