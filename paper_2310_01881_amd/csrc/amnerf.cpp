@@ -1203,7 +1203,8 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
     int li;
     EvSet* ev;
   };
-  // phase 1 (first: of the lane's first chunk, which resets its counters): traversal, and the plain interval count on its way to the host (lane li's slot)
+  // phase 1: traversal, and the plain interval count on its way to the host (lane li's slot);
+  // first: of the lane's first chunk, which resets its counters
   auto phase1 = [&](int64_t r0, uint32_t nr, int li, bool first, Pending* pd) -> int {
     const hipStream_t cs = li ? ctx->lanes[li - 1].stream : st;
     ChunkCounts* const cc = li ? ctx->lanes[li - 1].counts : ctx->counts;
@@ -1218,8 +1219,9 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
     HIP_TRY(launch_pass_begin(cc, first, w.chain, w.chain_words, cs));
     // the MLP outputs' buffer (16 bytes per possible sample) is free until the MLPs run: the
     // traversal keeps its scratch rows (12 bytes per possible interval) there
-    HIP_TRY(launch_trav(tree->dev_nodes, ahs_tab, p->hcheck_footprint, (uint32_t)n_nodes, tree->depth, rays->o_dev, rays->d_dev, R, r0, nr, p->s_max, (uint32_t)iv_per_ray, w.smp_out, w.chain, w.iv_off,
-                        w.smp_off, w.iv_t0, w.iv_dt, w.iv_key, w.iv_ray, w.iv_base, cs));
+    HIP_TRY(launch_trav(tree->dev_nodes, ahs_tab, p->hcheck_footprint, (uint32_t)n_nodes, tree->depth, rays->o_dev,
+                        rays->d_dev, R, r0, nr, p->s_max, (uint32_t)iv_per_ray, w.smp_out, w.chain, w.iv_off, w.smp_off,
+                        w.iv_t0, w.iv_dt, w.iv_key, w.iv_ray, w.iv_base, cs));
     HIP_TRY(mark(1));
     if (wait_count)
       HIP_TRY(hipMemcpyAsync(&ctx->counts_host[li].n_iv, w.iv_off + nr, sizeof(uint32_t), hipMemcpyDeviceToHost, cs));

@@ -1,6 +1,7 @@
 // chain.hpp -- single-pass prefix sums across the blocks of one launch (chained scan with
-// look-back): every block publishes the sum of its own part, adds up what the blocks before
-// it have published, and publishes the total up to and including itself.
+// look-back; Merrill and Garland, "Single-pass parallel prefix scan with decoupled look-back",
+// 2016): every block publishes the sum of its own part, adds up what the blocks before it have
+// published, and publishes the total up to and including itself.
 //
 // Blocks take their number from a ticket when they start, so every block that a block waits
 // for is already running and publishes its own sum without waiting for anyone: the wait

@@ -352,7 +352,7 @@ __global__ __launch_bounds__(kThreads) void k_chunk_finish(uint32_t nr, const ui
   counts->plain_smp += *plain_total;
 }
 
-// Adds the second lane's running totals into the first lane's counters.
+// Adds another lane's running totals into the first lane's counters.
 __global__ void k_counts_merge(ChunkCounts* a, const ChunkCounts* b) {
   if (threadIdx.x != 0) return;
   a->smp_global += b->smp_global;

@@ -213,9 +213,9 @@ __device__ __forceinline__ void layer32(const uint8_t* frag, const float* bias, 
 template <int H, bool FUSED>
 __global__ __launch_bounds__(kThreads, H == 64 ? 2 : 4) void k_mlp32(
     Layout L, const uint8_t* __restrict__ packed, uint32_t n_leaves, const uint32_t* __restrict__ bucket_off,
-    const uint32_t* __restrict__ tile_off, const ChunkCounts* __restrict__ counts, const SortRec* __restrict__ sv_rec, const uint32_t* __restrict__ sv_ssb,
-    const uint32_t* __restrict__ sv_win, const uint32_t* __restrict__ sm_ray, const float* __restrict__ sm_t,
-    const uint32_t* __restrict__ sm_perm,
+    const uint32_t* __restrict__ tile_off, const ChunkCounts* __restrict__ counts,
+    const SortRec* __restrict__ sv_rec, const uint32_t* __restrict__ sv_ssb, const uint32_t* __restrict__ sv_win,
+    const uint32_t* __restrict__ sm_ray, const float* __restrict__ sm_t, const uint32_t* __restrict__ sm_perm,
     const float* __restrict__ o, const float* __restrict__ d, int64_t stride, int64_t r0, float* __restrict__ out) {
   extern __shared__ __align__(16) uint8_t lds[];
   constexpr int KS = H / 16;

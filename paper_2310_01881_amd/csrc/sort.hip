@@ -33,8 +33,6 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr uint32_t kMaxGrid = 16384;
 
-// A word of the matrix and of the running counts: intervals << 20 | samples (a segment holds
-// less than 4096 intervals of at most 255 samples).
 // Block numbers dealt so that each of the eight dies (blocks go to them in turn) has a run of
 // consecutive ones: k in [0, 8 ceil(n / 8)) -> number, n or more for none.  Each die has an L2
 // of its own, and what neighbouring segments write (matrix entries, a leaf's places) is
@@ -44,6 +42,8 @@ constexpr uint32_t kDies = 8;
 __device__ __forceinline__ uint32_t die_runs(uint32_t n) { return (n + kDies - 1) / kDies; }
 __device__ __forceinline__ uint32_t die_block(uint32_t k, uint32_t runs) { return (k & (kDies - 1)) * runs + k / kDies; }
 
+// A word of the matrix and of the running counts: intervals << 20 | samples (a segment holds
+// less than 4096 intervals of at most 255 samples).
 __global__ __launch_bounds__(kThreads) void k_sort_hist(const uint32_t* __restrict__ iv_key,
                                                         const uint32_t* __restrict__ n_iv_dev,
                                                         uint32_t seg, uint32_t n_leaves,
