@@ -127,6 +127,7 @@ struct amnerf_ctx {
   IvSet use = {};
   uint32_t *bucket_off = nullptr, *perm = nullptr, *tile_off = nullptr, *srec_ray = nullptr;
   uint32_t *sidx = nullptr, *ssb = nullptr;   // sorted intervals
+  uint32_t* unexpanded = nullptr;             // not 0: no sample records yet
   float *smp_out = nullptr, *srec_t = nullptr;
   uint32_t* ray_used = nullptr;   // samples composited per ray (the early-termination count)
   bool last_uses_arena3 = false;  // the last render's intervals live in the third arena
@@ -941,7 +942,7 @@ struct Work {
   uint32_t *iv_off, *smp_off;
   float *iv_t0, *iv_dt;
   uint32_t *iv_key, *iv_ray, *iv_base;
-  uint32_t *mat, *mat_smp, *sidx, *ssb, *bucket_off, *tile_off, *win;
+  uint32_t *mat, *mat_smp, *sidx, *ssb, *bucket_off, *tile_off, *win, *unexpanded;
   SortRec* rec;           // sorted interval records, in the memory of the sample records
   uint64_t rec_cap;
   uint32_t *srec_ray, *perm;
@@ -973,6 +974,7 @@ size_t carve(char* base, uint64_t nr, uint64_t niv, uint64_t ns, const SortPlan&
   w.ssb = c.take<uint32_t>(niv + 1);
   w.bucket_off = c.take<uint32_t>(sp.n_leaves + 1);
   w.tile_off = c.take<uint32_t>(sp.n_leaves + 1);
+  w.unexpanded = c.take<uint32_t>(1);
   w.smp_out = c.take<float>(4 * ns);
   w.ray_used = c.take<uint32_t>(nr);
   const size_t rec_at = (c.off + 255) / 256 * 256;
@@ -1243,7 +1245,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
     const IvSet plain = {w.iv_off, w.smp_off, w.iv_t0, w.iv_dt, w.iv_key, w.iv_ray, w.iv_base, w.iv_off + nr};
     use = plain;
     SortPlan spu = sp;
-    sb = {w.mat, w.mat_smp, w.sidx, w.ssb, w.rec, w.win, w.bucket_off, w.tile_off};
+    sb = {w.mat, w.mat_smp, w.sidx, w.ssb, w.rec, w.win, w.bucket_off, w.tile_off, w.unexpanded};
     uint64_t* sort_chain = w.chain + w.trav_words;
     if (wait_count) HIP_TRY(hipStreamSynchronize(cs));   // the chunk's plain interval count has arrived
     if (p->proposal) {
@@ -1266,7 +1268,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
       sel_mask = pw.mask;
       spu = spp;
       sb = {pw.mat, pw.mat_smp, pw.sidx, pw.ssb, niv_plan <= w.rec_cap ? w.rec : nullptr, w.win, w.bucket_off,
-            w.tile_off};
+            w.tile_off, w.unexpanded};
       sort_chain = pw.chain + pw.off_words;
     } else if (occ) {
       // empty-space skipping: the kept samples of each ray as runs of consecutive slots
@@ -1288,7 +1290,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
       sel_mask = pw.mask;
       spu = spp;
       sb = {pw.mat, pw.mat_smp, pw.sidx, pw.ssb, niv_plan <= w.rec_cap ? w.rec : nullptr, w.win, w.bucket_off,
-            w.tile_off};
+            w.tile_off, w.unexpanded};
       sort_chain = pw.chain + pw.off_words;
     }
     HIP_TRY(mark(2));
@@ -1386,6 +1388,7 @@ static int render_impl(amnerf_ctx* ctx, const amnerf_tree* tree, const amnerf_ml
   ctx->srec_t = wl->srec_t;
   ctx->sidx = sb.sidx;
   ctx->ssb = sb.ssb;
+  ctx->unexpanded = sb.unexpanded;
   ctx->ray_used = wl->ray_used;
   ctx->last_uses_arena3 = p->proposal != nullptr || occ != nullptr;
   ctx->last_tree = tree;
@@ -1451,12 +1454,13 @@ extern "C" int amnerf_render_stats_get(amnerf_ctx* ctx, amnerf_render_stats* out
 // The last render's sample records, for what reads them after it (the backward pass,
 // calibration, inspection): a render whose MLPs read the sorted intervals has not written them,
 // and their memory held the intervals' records, which nothing needs any more.  Nothing on the
-// host remembers whether this has run: the launch is enqueued each time and the render's own
-// counters decide on the device, so that a reader in a graph, replayed after other renders, or
-// on another stream has its own before it.  Every run writes the same values.
+// host remembers whether this has run: the launch is enqueued each time and a word that the
+// render left beside its arrays decides on the device, so that a reader in a graph, replayed
+// after other renders, or on another stream has its own before it.  Every run writes the same
+// values.
 static int expand_records(amnerf_ctx* ctx, hipStream_t st) {
   HIP_TRY(launch_expand(ctx->sidx, nullptr, ctx->ssb, ctx->use, 0, 0, 0, ctx->srec_ray, ctx->srec_t, ctx->perm,
-                        ctx->counts, st));
+                        ctx->unexpanded, st));
   return AMNERF_OK;
 }
 

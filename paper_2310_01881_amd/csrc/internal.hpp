@@ -28,7 +28,7 @@ struct ChunkCounts {
   uint32_t n_iv;        // intervals that carry samples (this chunk)
   uint32_t n_smp;       // samples (this chunk)
   uint32_t n_tiles;     // MLP work tiles (this chunk)
-  uint32_t unexpanded;  // 1: the pass has no sample records (its MLPs read the sorted intervals)
+  uint32_t pad;
   uint64_t smp_global;  // ray-major sample index of this chunk's first sample
   uint64_t iv_global;   // intervals of the chunks before this one
   uint64_t nonfinite;   // rays with a non-finite output (accumulated over chunks)
@@ -122,28 +122,29 @@ struct SortRec {
 // prefix sums; mat_smp the samples' prefix sums.  Per sorted interval: sidx its index, ssb its
 // first sorted sample (ssb[n_iv] the total), rec its record (centred strata).  win[4 t + w]: the
 // sorted interval of the first row of window w (64 rows) of tile t.  rec null: only sidx and
-// ssb are made.
+// ssb are made.  unexpanded: set to 1 by a pass with rec, whose MLPs read the sorted intervals
+// (it has no sample records), to 0 by one without.
 struct SortBufs {
   uint32_t *mat, *mat_smp, *sidx, *ssb;
   SortRec* rec;
   uint32_t* win;
-  uint32_t *bucket_off, *tile_off;
+  uint32_t *bucket_off, *tile_off, *unexpanded;
 };
 // small: shorter segments (a larger matrix) for few intervals.
 SortPlan make_sort_plan(uint64_t n_iv_max, uint32_t n_leaves, bool small);
 hipError_t launch_sort_hist(const SortPlan& p, const uint32_t* iv_key, const uint32_t* n_iv_dev,
                             uint32_t* mat, hipStream_t st);
 // bucket_off[b] = first sorted sample of leaf b; tile_off[b] = first MLP tile of leaf b;
-// also fills ssb's total and counts->n_iv, n_smp, n_tiles and unexpanded.
+// also fills ssb's total, unexpanded, and counts->n_iv, n_smp and n_tiles.
 hipError_t launch_bucket_tiles(const SortPlan& p, const SortBufs& b, const uint32_t* n_iv_dev, ChunkCounts* counts,
                                hipStream_t st);
 hipError_t launch_sort_scatter(const SortPlan& p, const SortBufs& b, const IvSet& iv, hipStream_t st);
 // One record per sorted sample: ray (chunk-local), t, ray-major sample index; from the sorted
 // interval records where rec is given (centred strata only).  if_unexpanded (may be null): the
-// launch does nothing unless the pass it counts is without sample records.
+// launch does nothing where that word is 0 (SortBufs::unexpanded of the pass).
 hipError_t launch_expand(const uint32_t* sidx, const SortRec* rec, const uint32_t* ssb, const IvSet& iv,
                          int64_t r0, int jitter, uint64_t seed, uint32_t* srec_ray,
-                         float* srec_t, uint32_t* perm, const ChunkCounts* if_unexpanded, hipStream_t st);
+                         float* srec_t, uint32_t* perm, const uint32_t* if_unexpanded, hipStream_t st);
 
 // Where the leaf MLPs read their rows from: the sorted intervals (rec not null), or sample
 // records.

@@ -207,7 +207,7 @@ __global__ __launch_bounds__(1024) void k_bucket_tiles(uint32_t seg, uint32_t n_
     counts->n_iv = n_iv;
     counts->n_smp = n_smp;
     counts->n_tiles = carry;
-    counts->unexpanded = out.rec != nullptr;
+    *out.unexpanded = out.rec != nullptr;
   }
 }
 
@@ -225,12 +225,12 @@ template <bool REC>
 __global__ __launch_bounds__(kThreads) void k_expand(
     const uint32_t* __restrict__ sidx, const SortRec* __restrict__ rec, const uint32_t* __restrict__ ssb, IvSet iv,
     int64_t r0, int jitter, uint64_t seed, uint32_t* __restrict__ srec_ray, float* __restrict__ srec_t,
-    uint32_t* __restrict__ perm, const ChunkCounts* __restrict__ if_unexpanded) {
+    uint32_t* __restrict__ perm, const uint32_t* __restrict__ if_unexpanded) {
   __shared__ uint32_t sh_base[kThreads + 1];
   __shared__ uint32_t sh_ray[kThreads], sh_rm[kThreads];
   __shared__ float sh_t0[kThreads], sh_delta[kThreads], sh_u[kThreads];
   __shared__ int sh_mark[kWaves][64];
-  if (if_unexpanded && !if_unexpanded->unexpanded) return;
+  if (if_unexpanded && *if_unexpanded == 0u) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint32_t n_iv = *iv.n_iv_dev;
   const uint32_t n_groups = (n_iv + kThreads - 1) / kThreads;
@@ -350,7 +350,7 @@ hipError_t launch_bucket_tiles(const SortPlan& p, const SortBufs& b, const uint3
 
 hipError_t launch_expand(const uint32_t* sidx, const SortRec* rec, const uint32_t* ssb, const IvSet& iv, int64_t r0,
                          int jitter, uint64_t seed, uint32_t* srec_ray, float* srec_t, uint32_t* perm,
-                         const ChunkCounts* if_unexpanded, hipStream_t st) {
+                         const uint32_t* if_unexpanded, hipStream_t st) {
   hipLaunchKernelGGL((rec ? k_expand<true> : k_expand<false>), dim3(4096), dim3(kThreads), 0, st, sidx, rec, ssb, iv, r0,
                      jitter, seed, srec_ray, srec_t, perm, if_unexpanded);
   return hipGetLastError();

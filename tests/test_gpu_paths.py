@@ -342,7 +342,8 @@ def test_samples_behind_a_stop_count_for_nothing(dtype, density):
 def test_backward_recorded_in_a_graph(dtype):
     """A backward pass recorded after an eager one, replayed after renders of other rays whose
     leaf MLPs read sorted intervals (plain) or sample records (jittered, in rounds): the gradient
-    of an eager backward of the same render each time."""
+    of an eager backward of the same render each time, also after a render in the static
+    workspace."""
     scene = small_scene(s_max=96)
     ctx, tree, mlp = gpu_setup(scene, dtype)
     master = to_dev(scene.W)
@@ -377,6 +378,11 @@ def test_backward_recorded_in_a_graph(dtype):
         torch.cuda.synchronize()
         assert torch.isfinite(eager).all() and torch.equal(replayed, eager), (k, kw)
         seen.append(eager.clone())
+        am.amnerf_render_static(ctx.h, tree.h, mlp.desc, o[:, :300].contiguous(), d[:, :300].contiguous(), 96, rgb)
+        replayed.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(replayed, eager), (k, kw, "after a render elsewhere")
     assert not torch.equal(seen[0], seen[1])
 
 
