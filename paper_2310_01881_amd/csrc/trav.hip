@@ -47,8 +47,8 @@ __device__ __forceinline__ float quotient(float a, float d, float inv) {
 // (s - o) / d as a normalised pair, inv the correctly rounded 1 / d: the quotient, the fused
 // (exact) remainder of it, and that remainder's quotient: the bits of the same steps with
 // divisions.  (With bare products for quotients the pair's error was three times that, 2^-45.2
-// against 2^-47; the traversal takes 46 us either way for a 64x64 tile, and 129 against 126 for an
-// 800x800 frame.)  No contraction: h - q0 must see the rounded q0.
+// against 2^-47, and the traversal of a 64x64 tile took 46 us instead of 48, of an 800x800 frame
+// 126 instead of 129.)  No contraction: h - q0 must see the rounded q0.
 __device__ __forceinline__ DF plane_t(float s, float o, float d, float inv) {
 #pragma clang fp contract(off)
   DF num = two_sum(s, -o);
